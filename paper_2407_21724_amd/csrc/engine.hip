@@ -1634,145 +1634,230 @@ __global__ __launch_bounds__(64) void k_translate_reg(TrLevels<float> L, int R) 
 // point as a receiving box of zero size,
 //   E(r) = -jk sum_p sum_s w_s T_L(khat_s, r - c_p) (U_th,p(s) th_s + U_ph,p(s) ph_s),
 // valid where r is farther from c_p than the particle's circumscribed
-// radius.  Block = kFldPts points x one RHS; thread = one sample s of the
-// leaf sphere (K <= kBlock).  Per chunk of kFldPar particles the block
-// stages, for every (point, particle) pair, the unit vector and the Hankel
-// coefficients -jk/(16 pi^2) (-j)^l (2l+1) h_l^(2)(k|D|) (FP64 recurrence,
-// stored FP32); each thread then sums its sample's Legendre series.
-constexpr int kFldPts = 8, kFldPar = 32, kFldMaxL = 16;
-static_assert(kFldPts * kFldPar == kBlock, "one (point, particle) pair per thread in the staging");
+// radius.  T_L is a Legendre series in khat_s . D (D the unit vector from c_p
+// to r), and with the real harmonics C_lm of Schmidt's normalisation
+// P_l(a . b) = sum_m C_lm(a) C_lm(b), so the sum over the K = 2 L^2 samples is
+// taken once per particle (k_fld_expand),
+//   A_p,lm = sum_s w_s C_lm(khat_s) (U_th th_s + U_ph ph_s),
+// and a point sums the (L + 1)^2 terms of each particle (k_fields),
+//   E(r) = -k^2 / (16 pi^2) sum_p sum_l (2l+1) (-j)^l h_l^(2)(k|r - c_p|) sum_m C_lm(D) A_p,lm.
+// The sum is the same one, term by term; it takes 3 (L + 1)^2 real-by-complex
+// products for a (point, particle) pair where the series at every sample took
+// K (L + 2) multiply-adds and a division per degree.
+constexpr int kFldL = 11, kFldLM = (kFldL + 1) * (kFldL + 1);  // highest degree, harmonics up to it
+constexpr int kFldRow = 3 * kFldLM;                           // A values of a particle: [lm][x, y, z]
+constexpr int kFldExpP = 8, kFldExpT = 448;                   // particles and threads per block of k_fld_expand
+static_assert(kFldRow <= kFldExpT, "one thread per expansion coefficient");
+constexpr double fld_sqrt(double v) {  // compile-time square root (Newton)
+  double x = v > 1 ? v : 1;
+  for (int i = 0; i < 60; ++i) x = 0.5 * (x + v / x);
+  return x;
+}
+// C_lm(u) = Q_l^m(u_z) Re or Im (u_x + j u_y)^m with
+// Q_l^m = a(l, m) u_z Q_{l-1}^m - b(l, m) Q_{l-2}^m from Q_m^m = d(m)
+constexpr double fld_a(int l, int m) { return (2 * l - 1) / fld_sqrt((double)(l - m) * (l + m)); }
+constexpr double fld_b(int l, int m) { return fld_sqrt((double)(l + m - 1) * (l - m - 1) / ((double)(l - m) * (l + m))); }
+constexpr double fld_d(int m) {
+  double v = m ? 2.0 : 1.0;  // 2 ((2m - 1)!!)^2 / (2m)!
+  for (int i = 1; i <= m; ++i) v *= (2.0 * i - 1) / (2.0 * i);
+  return fld_sqrt(v);
+}
+// (tabulated at compile time: called in device code they would run there)
+struct FldTab {
+  double a[kFldL + 1][kFldL + 1], b[kFldL + 1][kFldL + 1], d[kFldL + 1];
+};
+constexpr FldTab fld_tab() {
+  FldTab t{};
+  for (int l = 0; l <= kFldL; ++l) {
+    t.d[l] = fld_d(l);
+    for (int m = 0; m < l; ++m) {
+      t.a[l][m] = fld_a(l, m);
+      t.b[l][m] = l - m > 1 ? fld_b(l, m) : 0.0;
+    }
+  }
+  return t;
+}
+constexpr FldTab kFldTab = fld_tab();
+// Index of C_lm in a particle's expansion: l^2 for m = 0, then cosine and
+// sine of m = 1, ..., l.
+__host__ __device__ constexpr int fld_lm(int l, int m, int sine) { return l * l + (m ? 2 * m - 1 + sine : 0); }
+
+// A[r][p][row] = sum_k W[k][row] U[r][box(p)][k] (k = component, sample; W
+// real).  One thread per row and kFldExpP particles, whose patterns are
+// staged in LDS: a table value is read once for them (a small part of the
+// field sum: 0.1 ms for 6400 particles).
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_fields(int P, int K, int L, double k, const double* __restrict__ centers,
-                                                    const int* __restrict__ box_of, int nb0,
-                                                    const C2<T>* __restrict__ S0, const float* __restrict__ tab,
-                                                    int npts, const double* __restrict__ pts, C2<T>* __restrict__ E) {
-  __shared__ float2 cl[kFldPts * kFldPar][kFldMaxL + 1];
-  __shared__ float dh[kFldPts * kFldPar][3];
-  __shared__ float2 red[kBlock / 64][kFldPts * 3];
-  const int r = blockIdx.y, pt0 = blockIdx.x * kFldPts;
-  const int s = threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const bool live = s < K;
-  float ks[3] = {0, 0, 0};
-  if (live)
-    for (int c = 0; c < 3; ++c) ks[c] = tab[s * 10 + c];
-  C2<float> acc[kFldPts][2];  // per point: sums of T U_th and T U_ph
+__global__ __launch_bounds__(kFldExpT) void k_fld_expand(int P, int M2, int nb0, const int* __restrict__ box_of,
+                                                          const C2<T>* __restrict__ S0, const float* __restrict__ W,
+                                                          C2<float>* __restrict__ A) {
+  extern __shared__ unsigned char smem_raw[];
+  C2<float>* u = reinterpret_cast<C2<float>*>(smem_raw);  // [M2][kFldExpP]
+  const int r = blockIdx.y, p0 = blockIdx.x * kFldExpP, row = threadIdx.x;
+  for (int i = threadIdx.x; i < kFldExpP * M2; i += kFldExpT) {
+    const int t = i / M2, k = i - t * M2;
+    C2<float> v{0.f, 0.f};
+    if (p0 + t < P) {
+      const C2<T> z = S0[((size_t)r * nb0 + box_of[p0 + t]) * M2 + k];
+      v = C2<float>{(float)z.x, (float)z.y};
+    }
+    u[k * kFldExpP + t] = v;
+  }
+  __syncthreads();
+  if (row >= kFldRow) return;
+  C2<float> acc[kFldExpP];
 #pragma unroll
-  for (int q = 0; q < kFldPts; ++q) acc[q][0] = acc[q][1] = C2<float>{0.f, 0.f};
-  const C2<T>* __restrict__ Sr = S0 + (size_t)r * nb0 * 2 * K;
-  for (int pc = 0; pc < P; pc += kFldPar) {
-    __syncthreads();  // the previous chunk's coefficients are consumed
-    {
-      const int q = threadIdx.x / kFldPar, j = threadIdx.x % kFldPar;  // kBlock = kFldPts * kFldPar
-      const int p = pc + j, pt = pt0 + q;
-      if (p < P && pt < npts) {
-        const double dx = pts[3 * pt] - centers[3 * p], dy = pts[3 * pt + 1] - centers[3 * p + 1],
-                     dz = pts[3 * pt + 2] - centers[3 * p + 2];
-        const double D = sqrt(dx * dx + dy * dy + dz * dz), x = k * D;
-        dh[threadIdx.x][0] = (float)(dx / D);
-        dh[threadIdx.x][1] = (float)(dy / D);
-        dh[threadIdx.x][2] = (float)(dz / D);
-        // h_0 = j e^{-jx}/x, h_1 = e^{-jx}(j/x^2 - 1/x), h_{l+1} = (2l+1)/x h_l - h_{l-1}
-        const double cx = cos(x), sx = sin(x);  // e^{-jx} = cx - j sx
-        double h0r = sx / x, h0i = cx / x;
-        double h1r = sx / (x * x) - cx / x, h1i = cx / (x * x) + sx / x;
-        const double pr = 0.0, pi = -k / (16.0 * 3.14159265358979323846 * 3.14159265358979323846);  // -jk/(16 pi^2)
-        for (int l = 0; l <= L; ++l) {
-          double hr, hi;
-          if (l == 0) {
-            hr = h0r;
-            hi = h0i;
-          } else if (l == 1) {
-            hr = h1r;
-            hi = h1i;
-          } else {
-            hr = (2.0 * l - 1.0) / x * h1r - h0r;
-            hi = (2.0 * l - 1.0) / x * h1i - h0i;
-            h0r = h1r;
-            h0i = h1i;
-            h1r = hr;
-            h1i = hi;
-          }
-          // (-j)^l (2l+1) h_l, times the prefactor
-          double ar = (2.0 * l + 1.0) * hr, ai = (2.0 * l + 1.0) * hi, t;
-          switch (l & 3) {
-            case 1: t = ar; ar = ai; ai = -t; break;   // times -j
-            case 2: ar = -ar; ai = -ai; break;
-            case 3: t = ar; ar = -ai; ai = t; break;   // times +j
-            default: break;
-          }
-          cl[threadIdx.x][l] = make_float2((float)(pr * ar - pi * ai), (float)(pr * ai + pi * ar));
-        }
-      } else {
-        dh[threadIdx.x][0] = dh[threadIdx.x][1] = dh[threadIdx.x][2] = 0.f;
-        for (int l = 0; l <= L; ++l) cl[threadIdx.x][l] = make_float2(0.f, 0.f);
-      }
+  for (int t = 0; t < kFldExpP; ++t) acc[t] = C2<float>{0.f, 0.f};
+#pragma unroll 4
+  for (int k = 0; k < M2; ++k) {
+    const float wv = W[(size_t)k * kFldRow + row];
+#pragma unroll
+    for (int t = 0; t < kFldExpP; ++t) {
+      const C2<float> z = u[k * kFldExpP + t];
+      acc[t].x = fmadd(wv, z.x, acc[t].x);
+      acc[t].y = fmadd(wv, z.y, acc[t].y);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kFldExpP; ++t)
+    if (p0 + t < P) A[((size_t)r * P + p0 + t) * kFldRow + row] = acc[t];
+}
+
+// part[chunk][r][point][3]: the sums over a chunk of the particles.  One lane
+// per point; distance, phase and the Hankel recurrence are FP64, the harmonics
+// and the sums FP32.  A block's four waves are PW = 4 / pw groups of particles
+// times pw sets of 64 points (pw = 4 from 193 points on, fewer where a block
+// would have idle waves).  The expansions of fld_group particles pass through
+// LDS for the whole block and are read as broadcasts.  RB right-hand sides
+// share a pair's harmonics.  Bound by vector issue (FP64 distance, phase and
+// Hankel functions, then about 1000 FP32 multiply-adds a pair and RHS) and by
+// the broadcasts.  4096 points of 6400 particles: 42 ms with the Legendre
+// series at every sample, 3.0 ms now; with the expansions read through the
+// scalar unit 3.6 ms, and for 4 RHS 10.4 against 7.7 ms.
+template <int RB>
+constexpr int fld_group() { return RB == 1 ? 8 : 4; }  // particles staged at a time (28 to 55 KB)
+template <int RB>
+__global__ __launch_bounds__(256) void k_fields(int P, int L, double k, const double* __restrict__ centers,
+                                                const C2<float>* __restrict__ A, int npts,
+                                                const double* __restrict__ pts, int R, int per, int pw,
+                                                C2<float>* __restrict__ part) {
+  constexpr int FG = fld_group<RB>(), NV = kFldRow / 2;  // pairs of coefficients per particle
+  __shared__ CP<float> sA[FG * RB * NV];                 // [particle][RHS][pair]
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, PW = 4 / pw, sub = wave / pw;
+  const int pt = (blockIdx.x * pw + wave % pw) * 64 + lane, ch = blockIdx.y, r0 = blockIdx.z * RB;
+  const int pc = min(pt, npts - 1);
+  const double px = pts[3 * (size_t)pc], py = pts[3 * (size_t)pc + 1], pz = pts[3 * (size_t)pc + 2];
+  const int p0 = ch * per, p1 = min(P, p0 + per);
+  const double kpi = k / 3.14159265358979323846, ik = 1.0 / k;
+  C2<float> e[RB][3];
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+#pragma unroll
+    for (int c = 0; c < 3; ++c) e[b][c] = C2<float>{0.f, 0.f};
+  for (int g0 = p0; g0 < p1; g0 += FG) {
+    __syncthreads();  // the previous group has been read
+    for (int i = threadIdx.x; i < FG * RB * NV; i += 256) {
+      const int row = i / NV, q = i - row * NV;
+      // rows past the chunk or the batch: the last ones again (not used)
+      const int p = min(g0 + row / RB, p1 - 1), r = min(r0 + row % RB, R - 1);
+      sA[i] = reinterpret_cast<const CP<float>*>(A + ((size_t)r * P + p) * kFldRow)[q];
     }
     __syncthreads();
-    if (!live) continue;
-    const int nj = min(kFldPar, P - pc);
-    for (int j = 0; j < nj; ++j) {
-      const int p = pc + j;
-      const C2<T>* Up = Sr + (size_t)box_of[p] * 2 * K;
-      const C2<float> ut{(float)Up[s].x, (float)Up[s].y}, up{(float)Up[K + s].x, (float)Up[K + s].y};
+    for (int t = sub; t < FG; t += PW) {
+      const int p = g0 + t;
+      if (p >= p1) break;
+      const C2<float>* __restrict__ At = &sA[t * RB * NV].a;
+      const double dx = px - uni(centers)[3 * p], dy = py - uni(centers)[3 * p + 1], dz = pz - uni(centers)[3 * p + 2];
+      const double d2 = fmadd(dx, dx, fmadd(dy, dy, dz * dz)), dist = sqrt(d2), id = 1.0 / dist, xi = id * ik;  // xi = 1 / (k D)
+      const float ux = (float)(dx * id), uy = (float)(dy * id), uz = (float)(dz * id);
+      double sx, cx;
+      sincospi(kpi * dist, &sx, &cx);
+      // g_l = (-j)^l h_l^(2)(kD): g_{l+1} = -j (2l + 1) / (kD) g_l + g_{l-1}
+      double gr = sx * xi, gi = cx * xi;                          // g_l
+      double hr = fmadd(cx, xi, sx) * xi, hi = fmadd(-sx, xi, cx) * xi;  // g_{l+1}
+      float q1[kFldL + 1], q2[kFldL + 1], cm[kFldL + 1], sm[kFldL + 1];  // Q_{l-1}^m, Q_{l-2}^m, (ux + j uy)^m
+      cm[0] = 1.f;
+      sm[0] = 0.f;
 #pragma unroll
-      for (int q = 0; q < kFldPts; ++q) {
-        const int e = q * kFldPar + j;
-        const float mu = ks[0] * dh[e][0] + ks[1] * dh[e][1] + ks[2] * dh[e][2];
-        // T = sum_l c_l P_l(mu) by the Legendre recurrence
-        float p0 = 1.f, p1 = mu;
-        float2 c = cl[e][0];
-        C2<float> tt{c.x, c.y};
-        c = cl[e][1];
-        tt.x = fmadd(c.x, p1, tt.x);
-        tt.y = fmadd(c.y, p1, tt.y);
-        for (int l = 1; l < L; ++l) {
-          const float p2 = ((2.f * l + 1.f) * mu * p1 - (float)l * p0) / (float)(l + 1);
-          c = cl[e][l + 1];
-          tt.x = fmadd(c.x, p2, tt.x);
-          tt.y = fmadd(c.y, p2, tt.y);
-          p0 = p1;
-          p1 = p2;
+      for (int l = 0; l <= kFldL; ++l) {
+        if (l > L) break;
+        if (l) {
+          cm[l] = fmadd(cm[l - 1], ux, -(sm[l - 1] * uy));
+          sm[l] = fmadd(cm[l - 1], uy, sm[l - 1] * ux);
         }
-        cfma(acc[q][0], tt, ut);
-        cfma(acc[q][1], tt, up);
+        C2<float> z[RB][3];
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) z[b][c] = C2<float>{0.f, 0.f};
+#pragma unroll
+        for (int m = 0; m <= l; ++m) {
+          float q;
+          if (m == l) q = (float)kFldTab.d[m];
+          else if (m == l - 1) q = (float)kFldTab.a[l][m] * uz * q1[m];
+          else q = fmadd((float)kFldTab.a[l][m] * uz, q1[m], -(float)kFldTab.b[l][m] * q2[m]);
+          q2[m] = m == l ? 0.f : q1[m];
+          q1[m] = q;
+#pragma unroll
+          for (int sine = 0; sine < (m ? 2 : 1); ++sine) {
+            const float v = m == 0 ? q : q * (sine ? sm[m] : cm[m]);
+#pragma unroll
+            for (int b = 0; b < RB; ++b)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) {
+                const C2<float> a = At[b * kFldRow + fld_lm(l, m, sine) * 3 + c];
+                z[b][c].x = fmadd(v, a.x, z[b][c].x);
+                z[b][c].y = fmadd(v, a.y, z[b][c].y);
+              }
+          }
+        }
+        const C2<float> cl{(float)((2 * l + 1) * gr), (float)((2 * l + 1) * gi)};
+#pragma unroll
+        for (int b = 0; b < RB; ++b)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) cfma(e[b][c], cl, z[b][c]);
+        const double f = (2 * l + 3) * xi, nr = fmadd(f, hi, gr), ni = fmadd(-f, hr, gi);
+        gr = hr;
+        gi = hi;
+        hr = nr;
+        hi = ni;
       }
     }
   }
-  // E += -jk w_s (A th_s + B ph_s), summed over the samples (threads)
-  float th[3] = {0, 0, 0}, ph[3] = {0, 0, 0}, ws = 0;
-  if (live) {
-    for (int c = 0; c < 3; ++c) {
-      th[c] = tab[s * 10 + 3 + c];
-      ph[c] = tab[s * 10 + 6 + c];
+  if (pt >= npts) return;
+#pragma unroll
+  for (int b = 0; b < RB; ++b)
+    if (r0 + b < R)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) part[(((size_t)(ch * PW + sub) * R + r0 + b) * npts + pt) * 3 + c] = e[b][c];
+}
+
+// E = scale * the sum of the nch parts, in FP64: a block takes 16 values, 16
+// threads each (with few points the parts are many: one thread per value
+// took 0.8 ms for 10 points of 10,000 particles, half of the call)
+template <typename T>
+__global__ __launch_bounds__(256) void k_fld_sum(size_t cnt, int nch, double scale, const C2<float>* __restrict__ part,
+                                                  C2<T>* __restrict__ E) {
+  __shared__ double red[16][17][2];
+  const int v = threadIdx.x & 15, row = threadIdx.x >> 4;
+  const size_t i = (size_t)blockIdx.x * 16 + v;
+  double x = 0, y = 0;
+  if (i < cnt) {
+#pragma unroll 4
+    for (int c = row; c < nch; c += 16) {
+      const C2<float> z = part[(size_t)c * cnt + i];
+      x += z.x;
+      y += z.y;
     }
-    ws = tab[s * 10 + 9];
   }
-  const float kf = (float)k;
-#pragma unroll
-  for (int q = 0; q < kFldPts; ++q)
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      // v = A th_c + B ph_c, times -jk w_s
-      const float vx = acc[q][0].x * th[c] + acc[q][1].x * ph[c], vy = acc[q][0].y * th[c] + acc[q][1].y * ph[c];
-      float ox = kf * ws * vy, oy = -kf * ws * vx;
-      for (int o = 32; o > 0; o >>= 1) {
-        ox += __shfl_xor(ox, o);
-        oy += __shfl_xor(oy, o);
-      }
-      if (lane == 0) red[wave][q * 3 + c] = make_float2(ox, oy);
-    }
+  red[row][v][0] = x;
+  red[row][v][1] = y;
   __syncthreads();
-  if (threadIdx.x < kFldPts * 3) {
-    const int q = threadIdx.x / 3, c = threadIdx.x % 3, pt = pt0 + q;
-    if (pt < npts) {
-      float2 o = make_float2(0.f, 0.f);
-      for (int w = 0; w < kBlock / 64; ++w) {
-        o.x += red[w][threadIdx.x].x;
-        o.y += red[w][threadIdx.x].y;
-      }
-      E[((size_t)r * npts + pt) * 3 + c] = C2<T>{(T)o.x, (T)o.y};
-    }
+  if (row || i >= cnt) return;
+  for (int c = 1; c < 16; ++c) {
+    x += red[c][v][0];
+    y += red[c][v][1];
   }
+  E[i] = C2<T>{(T)(scale * x), (T)(scale * y)};
 }
 
 // -------------------------------------------------------------------- rhs --
@@ -2311,8 +2396,8 @@ class EngineT final : public Engine {
     nx0_ = u.nx0;
     ny0_ = u.ny0;
     if (int rc = put_i(box_of_, u.box_of, err)) return rc;
-    // field evaluation: particle centres, and the leaf sphere's directions,
-    // unit vectors and weights [K0][khat, th_hat, ph_hat, w]
+    // field evaluation: particle centres, and the leaf samples' weights in
+    // the harmonic expansion [component][sample][lm][x, y, z]
     fld_k_ = u.k;
     fld_L_ = ntl_ > 0 ? tr.lv[0].L : 0;
     {
@@ -2323,17 +2408,32 @@ class EngineT final : public Engine {
         cen[3 * p + 2] = u.centers[p].z;
       }
       if (int rc = put_raw(fld_cen_, cen.data(), cen.size(), err)) return rc;
-      if (ntl_ > 0) {
+      if (ntl_ > 0 && fld_L_ <= kFldL) {
         const LevelGrid& g = tr.lv[0];
-        std::vector<float> tab((size_t)g.K * 10);
+        std::vector<float> tab((size_t)2 * g.K * kFldRow, 0.f);
         for (int s = 0; s < g.K; ++s) {
-          const V3 v[3] = {g.khat[s], g.th_hat[s], g.ph_hat[s]};
-          for (int c = 0; c < 3; ++c) {
-            tab[(size_t)s * 10 + 3 * c] = (float)v[c].x;
-            tab[(size_t)s * 10 + 3 * c + 1] = (float)v[c].y;
-            tab[(size_t)s * 10 + 3 * c + 2] = (float)v[c].z;
+          const V3 kh = g.khat[s], e[2] = {g.th_hat[s], g.ph_hat[s]};
+          double q1[kFldL + 1], q2[kFldL + 1];
+          cd ex(1.0, 0.0), pw[kFldL + 1];
+          for (int l = 0; l <= fld_L_; ++l, ex *= cd(kh.x, kh.y)) {
+            pw[l] = ex;
+            for (int m = 0; m <= l; ++m) {
+              const double q = m == l       ? kFldTab.d[m]
+                               : m == l - 1 ? kFldTab.a[l][m] * kh.z * q1[m]
+                                            : kFldTab.a[l][m] * kh.z * q1[m] - kFldTab.b[l][m] * q2[m];
+              q2[m] = m == l ? 0.0 : q1[m];
+              q1[m] = q;
+              for (int sine = 0; sine < (m ? 2 : 1); ++sine) {
+                const double v = g.w[s] * q * (sine ? pw[m].imag() : pw[m].real());
+                for (int h = 0; h < 2; ++h) {
+                  float* row = &tab[((size_t)h * g.K + s) * kFldRow + 3 * fld_lm(l, m, sine)];
+                  row[0] = (float)(v * e[h].x);
+                  row[1] = (float)(v * e[h].y);
+                  row[2] = (float)(v * e[h].z);
+                }
+              }
+            }
           }
-          tab[(size_t)s * 10 + 9] = (float)g.w[s];
         }
         if (int rc = put_raw(fld_tab_, tab.data(), tab.size(), err)) return rc;
       }
@@ -3396,7 +3496,7 @@ class EngineT final : public Engine {
       return -1;
     }
     const Lvl& L0 = lv_[0];
-    if (L0.K > kBlock || fld_L_ > kFldMaxL) {
+    if (L0.K > kBlock || fld_L_ > kFldL) {
       err = "fields: the leaf sphere has more than " + std::to_string(kBlock) + " samples";
       return -1;
     }
@@ -3418,10 +3518,36 @@ class EngineT final : public Engine {
     }
     if ((size_t)npts * 3 * sizeof(double) > fld_pts_.bytes) HIP_TRY(fld_pts_.alloc((size_t)npts * 3 * sizeof(double)));
     HIP_TRY(hipMemcpyAsync(fld_pts_.p, points, (size_t)npts * 3 * sizeof(double), hipMemcpyHostToDevice, st));
-    launch(none, k_fields<T>, dim3((npts + kFldPts - 1) / kFldPts, R), dim3(kBlock), 0u, st, P_, L0.K, fld_L_,
-           fld_k_, fld_cen_.template as<double>(), box_of_.template as<int>(), L0.nx * L0.ny,
-           (const CT*)L0.S.template as<CT>(), fld_tab_.template as<float>(), npts,
-           (const double*)fld_pts_.template as<double>(), reinterpret_cast<CT*>(Ev));
+    // the expansions, in the incoming leaf patterns' buffer (free between
+    // products) or, where its sphere is too coarse for them, one of their own
+    const size_t a_bytes = (size_t)R * P_ * kFldRow * sizeof(C2<float>);
+    if (a_bytes > L0.G.bytes && a_bytes > fld_exp_.bytes) HIP_TRY(fld_exp_.alloc(a_bytes));
+    C2<float>* A = (a_bytes > L0.G.bytes ? fld_exp_ : L0.G).template as<C2<float>>();
+    launch(none, k_fld_expand<T>, dim3((P_ + kFldExpP - 1) / kFldExpP, R), dim3(kFldExpT),
+           (uint32_t)(kFldExpP * M2_ * sizeof(C2<float>)), st, P_, M2_, L0.nx * L0.ny,
+           (const int*)box_of_.template as<int>(), (const CT*)L0.S.template as<CT>(),
+           (const float*)fld_tab_.template as<float>(), A);
+    // sets of 64 points per block, and chunks of particles for about kFldBlocks
+    // blocks, each a multiple of the particles staged together (4096 points of
+    // 6400 particles: 3.6, 3.2, 3.0 ms with 1024, 2048, 4096 blocks).  Neither
+    // depends on R, so a right-hand side's sums do not depend on the batch.
+    const int rb = R >= 3 ? 4 : R, pw = npts > 128 ? 4 : npts > 64 ? 2 : 1;
+    const int nwp = (npts + 64 * pw - 1) / (64 * pw), nrg = (R + rb - 1) / rb, fg = fld_group<1>();
+    const int want = std::max(1, std::min((P_ + fg - 1) / fg, (kFldBlocks + nwp - 1) / nwp));
+    const int per = ((P_ + want - 1) / want + fg - 1) / fg * fg, nch = (P_ + per - 1) / per, nsum = nch * (4 / pw);
+    const size_t cnt = (size_t)R * npts * 3;
+    if (nsum * cnt * sizeof(C2<float>) > fld_part_.bytes) HIP_TRY(fld_part_.alloc(nsum * cnt * sizeof(C2<float>)));
+    C2<float>* part = fld_part_.template as<C2<float>>();
+    auto sum_terms = [&](auto kernel) {
+      launch(none, kernel, dim3(nwp, nch, nrg), dim3(256), 0u, st, P_, fld_L_, fld_k_,
+             (const double*)fld_cen_.template as<double>(), (const C2<float>*)A, npts,
+             (const double*)fld_pts_.template as<double>(), R, per, pw, part);
+    };
+    if (rb == 1) sum_terms(k_fields<1>);
+    else if (rb == 2) sum_terms(k_fields<2>);
+    else sum_terms(k_fields<4>);
+    launch(none, k_fld_sum<T>, dim3((unsigned)((cnt + 15) / 16)), dim3(256), 0u, st, cnt, nsum,
+           -fld_k_ * fld_k_ / (16.0 * kPi * kPi), (const C2<float>*)part, reinterpret_cast<CT*>(Ev));
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));  // the host point array may be released on return
     return 0;
@@ -3681,6 +3807,8 @@ class EngineT final : public Engine {
   const Tree* tree_ = nullptr;
   DevMem box_of_, class_of_, order_, tile_start_, tile_count_, tile_class_;
   DevMem fld_cen_, fld_tab_, fld_pts_;  // field evaluation: centres, leaf sample table, points
+  DevMem fld_exp_, fld_part_;           // expansions, chunk sums
+  static constexpr int kFldBlocks = 4096;  // target of k_fields
   double fld_k_ = 0;
   int fld_L_ = 0;
   DevMem Rm_, Qm_, rm_off_, qm_off_;
