@@ -59,6 +59,10 @@ struct mlfma_ctx {
   std::shared_ptr<std::map<NearKey, std::vector<cd>>> near_cache =
       std::make_shared<std::map<NearKey, std::vector<cd>>>();  // n x n row-major blocks
   std::unique_ptr<Engine> eng;
+  struct GuessTablesDelete {
+    void operator()(GuessTables* t) const { guess_tables_destroy(t); }
+  };
+  std::unique_ptr<GuessTables, GuessTablesDelete> guess_tab;  // device tables of mlfma_learned_guess
 };
 
 namespace {
@@ -948,17 +952,16 @@ int mlfma_mlp_train_step(mlfma_mlp* net, const float* X_dev, const float* T_dev,
 }
 
 namespace {
-// features [R][P][C + 11] and incident phases [R][P] of the learned guess:
+// features [R][P][C + 11] of the learned guess:
 // one-hot class of p, class_param / scale of the 8 neighbouring sites (0 if
 // empty), khat_x, khat_y, and the distance in sites to the nearest edge of
 // the lattice, capped at kEdgeCap and divided by it
 constexpr int kEdgeCap = 6;
 int guess_nfeat(const mlfma_ctx* ctx) { return ctx->C + 11; }
 void guess_features(const mlfma_ctx* ctx, const double* class_param, double scale, int R, const double* khat,
-                    std::vector<float>& X, std::vector<cd>& phase) {
+                    std::vector<float>& X) {
   const int P = ctx->P, nf = guess_nfeat(ctx);
   X.assign((size_t)R * P * nf, 0.f);
-  phase.assign((size_t)R * P, cd(1.0, 0.0));
   for (int r = 0; r < R; ++r) {
     const V3 kh{khat[3 * r], khat[3 * r + 1], khat[3 * r + 2]};
     for (int p = 0; p < P; ++p) {
@@ -978,8 +981,6 @@ void guess_features(const mlfma_ctx* ctx, const double* class_param, double scal
       f[slot++] = (float)kh.y;
       const int edge = std::min(std::min(ix, iy), std::min(ctx->nx - 1 - ix, ctx->ny - 1 - iy));
       f[slot] = (float)std::min(edge, kEdgeCap) / kEdgeCap;
-      const double a = -kK0 * dot(kh, ctx->centers[p]);
-      phase[(size_t)r * P + p] = cd(std::cos(a), std::sin(a));
     }
   }
 }
@@ -990,8 +991,7 @@ int mlfma_guess_features(mlfma_ctx* ctx, const double* class_param, double scale
   if (!ctx || !class_param || !khat || !X_host || R < 1 || !(scale > 0)) return MLFMA_EINVAL;
   return guarded(ctx, [&]() -> int {
     std::vector<float> X;
-    std::vector<cd> phase;
-    guess_features(ctx, class_param, scale, R, khat, X, phase);
+    guess_features(ctx, class_param, scale, R, khat, X);
     std::memcpy(X_host, X.data(), X.size() * sizeof(float));
     return MLFMA_OK;
   });
@@ -1005,12 +1005,27 @@ int mlfma_learned_guess(mlfma_ctx* ctx, mlfma_mlp* net, const double* class_para
     const int N = ctx->N, n = 2 * N, P = ctx->P;
     if (mlp_inputs(net->m) != guess_nfeat(ctx) || mlp_outputs(net->m) != 2 * n)
       return fail(ctx, MLFMA_EINVAL, "network must have n_classes + 11 inputs and 4N outputs");
-    std::vector<float> X;
-    std::vector<cd> phase;
-    guess_features(ctx, class_param, scale, R, khat, X, phase);
+    if (!ctx->guess_tab) ctx->guess_tab.reset(guess_tables_create());
+    std::vector<double> cen((size_t)3 * P);
+    for (int p = 0; p < P; ++p) {
+      cen[3 * p] = ctx->centers[p].x;
+      cen[3 * p + 1] = ctx->centers[p].y;
+      cen[3 * p + 2] = ctx->centers[p].z;
+    }
+    GuessInput in;
+    in.khat = khat;
+    in.class_param = class_param;
+    in.scale = scale;
+    in.k = kK0;
+    in.P = P;
+    in.C = ctx->C;
+    in.nx = ctx->nx;
+    in.ny = ctx->ny;
+    in.edge_cap = kEdgeCap;
     std::string err;
-    int rc = mlp_guess(net->m, X, phase, R, P, N * 2, ctx->tp.precision == MLFMA_C128 ? 1 : 0, x_dev, stream,
-                       err);
+    int rc = guess_tables_fill(ctx->guess_tab.get(), ctx->cls, ctx->box_of, ctx->part_of_box, cen, in, err);
+    if (!rc)
+      rc = mlp_guess(net->m, in, R, n, ctx->tp.precision == MLFMA_C128 ? 1 : 0, x_dev, stream, err);
     return rc ? fail(ctx, rc == -1 ? MLFMA_EINVAL : rc, err) : MLFMA_OK;
   });
 }

@@ -1,12 +1,15 @@
-// Learned initial guess network on gfx950: FP32 matrix-core GEMMs with LDS
-// tiles for the layers and their gradients, plus the elementwise kernels of
-// the loss, the ReLU masks, the bias gradients and Adam.  See mlp.hpp.
+// Learned initial guess network on gfx950, FP32 on the matrix cores.  Small
+// batches take one launch per layer and direction (k_layer), large ones a
+// kernel that runs a tile of samples through the whole network (k_net); in
+// training k_net_grad then forms all weight gradients and applies Adam.  See
+// mlp.hpp.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
 #include <complex>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "mlp.hpp"
@@ -26,147 +29,443 @@ namespace {
 constexpr int kT = 256;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// C(m, n) (+)= sum_k A(m, k) B(k, n) with arbitrary element strides:
-// A(m, k) = A[m*sa0 + k*sa1], B(k, n) = B[k*sb0 + n*sb1], C at m*sc0 + n*sc1.
-// Epilogue: + bias[m] (if set), then ReLU (relu) or a multiply by
-// (mask(m, n) > 0) with mask at m*sc0 + n*sc1 (if set).  Block tile 64 x 64,
-// K in chunks of 16 through LDS; wave w owns rows [16w, 16w + 16) as four
-// 16 x 16 tiles of v_mfma_f32_16x16x4f32 (A[i][k] from lane i + 16k, B[k][j]
-// from lane j + 16k, result row 4*(lane/16) + v, column lane % 16).
-struct Gemm {
-  const float* A;
-  const float* B;
-  float* C;
-  const float* bias;
-  const float* mask;
-  long sa0, sa1, sb0, sb1, sc0, sc1;
-  int M, N, K, accumulate, relu;
+// All products contract over k in steps of 16 with a k-permutation inside each
+// step: of v_mfma_f32_16x16x4f32 (A[i][k] from lane i + 16k, B[k][j] from lane
+// j + 16k, result row 4*(lane/16) + v, column lane % 16) lane (i, kq) holds the
+// consecutive values 4 kq .. 4 kq + 3 of its row and column, and MFMA q
+// contracts over kq, so that operands come in 16-byte loads.
+__device__ __forceinline__ int pad16(int v) { return (v + 15) & ~15; }
+// Elements k .. k + 3 of row r of a row-major [rows][K] matrix (row stride ld),
+// zero past its end; vec: 16-byte loads are aligned and K a multiple of 4.
+__device__ __forceinline__ f32x4 row4(const float* __restrict__ A, int rows, int K, long ld, bool vec, int r, int k) {
+  f32x4 o;
+  const long at = (long)min(r, rows - 1) * ld;
+  if (vec) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(A + at + min(k, K - 4));
+    return r < rows && k < K ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float v = A[at + min(k + q, K - 1)];
+    o[q] = r < rows && k + q < K ? v : 0.f;
+  }
+  return o;
+}
+// The same of column r of a [K][rows] matrix.
+__device__ __forceinline__ f32x4 col4(const float* __restrict__ A, int rows, int K, int r, int k) {
+  f32x4 o;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float v = A[(long)min(k + q, K - 1) * rows + min(r, rows - 1)];
+    o[q] = r < rows && k + q < K ? v : 0.f;
+  }
+  return o;
+}
+
+// ------------------------------------------------------ one layer a launch --
+// out[sample][m] = sum_k W(m, k) in[sample][k], W the layer's matrix or (back)
+// its transpose, with the layer's epilogue.  A block takes 16 features x 16
+// samples, its four waves a quarter of k each, all of a wave's loads for K up
+// to 256 in flight at once: 256 samples of the 256-wide layers make 256 blocks
+// of one memory latency.  Bound by that latency and the launch for the batches
+// it is used for (n < kNetFrom): a training step of 256 samples took
+// 412 us with a 64 x 64 LDS GEMM per product (16 chunks of k, one at a time)
+// and takes 60 us now; 101 us with k_net, whose 16 blocks leave most of the
+// chip idle.
+struct LayerArgs {
+  const float* W;     // [M][K], back: [K][M]
+  const float* bias;  // forward
+  const float* in;    // [n][ldi]
+  const float* T;     // last layer in training: targets [n][M]
+  const float* mask;  // back: the layer's inputs, feature-major [M][ldn]
+  float* out;         // [n][ldo], sample-major (may be null)
+  float* outT;        // training: feature-major [M][ldn]
+  float* inT;         // first layer in training: its inputs, feature-major [K][ldn]
+  double* part;       // last layer in training: squared error of each block
+  int M, K, n, ldi, ldo, ldn, relu, back, vecw, veci;
 };
-
-__global__ __launch_bounds__(kT) void k_gemm(Gemm g) {
-  __shared__ float As[64][17];
-  __shared__ float Bs[16][65];
-  const int m0 = blockIdx.x * 64, n0 = blockIdx.y * 64;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int i = lane & 15, kq = lane >> 4;
-  f32x4 acc[4];
-  for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = 0; k0 < g.K; k0 += 16) {
-    for (int e = threadIdx.x; e < 64 * 16; e += kT) {
-      const int r = e / 16, c = e % 16;
-      const int m = m0 + r, k = k0 + c;
-      As[r][c] = (m < g.M && k < g.K) ? g.A[(long)m * g.sa0 + (long)k * g.sa1] : 0.f;
-      const int kb = e / 64, nb = e % 64;
-      const int k2 = k0 + kb, n = n0 + nb;
-      Bs[kb][nb] = (k2 < g.K && n < g.N) ? g.B[(long)k2 * g.sb0 + (long)n * g.sb1] : 0.f;
-    }
-    __syncthreads();
+__global__ __launch_bounds__(256) void k_layer(LayerArgs a) {
+  __shared__ f32x4 red[3][64];
+  const int tm = (a.M + 15) / 16, m0 = (blockIdx.x % tm) * 16, n0 = (blockIdx.x / tm) * 16;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int nk = pad16(a.K) / 16, k0 = wave * nk / 4, k1 = (wave + 1) * nk / 4;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  constexpr int U = 4;
+  for (int s = k0; s < k1; s += U) {
+    f32x4 x[U], y[U];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
-      const float a = As[wave * 16 + i][kk * 4 + kq];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[kk * 4 + kq][t * 16 + i], acc[t], 0, 0, 0);
+    for (int u = 0; u < U; ++u) {
+      const int k = s + u < k1 ? 16 * (s + u) + 4 * kq : a.K;  // past the wave's range: zeros
+      x[u] = a.back ? col4(a.W, a.M, a.K, m0 + i, k) : row4(a.W, a.M, a.K, a.K, a.vecw, m0 + i, k);
+      y[u] = row4(a.in, a.n, a.K, a.ldi, a.veci, n0 + i, k);
     }
-    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][q], y[u][q], acc, 0, 0, 0);
   }
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int m = m0 + wave * 16 + 4 * kq + v, n = n0 + t * 16 + i;
-      if (m >= g.M || n >= g.N) continue;
-      const long o = (long)m * g.sc0 + (long)n * g.sc1;
-      float c = acc[t][v];
-      if (g.accumulate) c += g.C[o];
-      if (g.bias) c += g.bias[m];
-      if (g.relu) c = fmaxf(c, 0.f);
-      if (g.mask && !(g.mask[o] > 0.f)) c = 0.f;
-      g.C[o] = c;
+  if (a.inT && m0 == 0)
+    for (int e = threadIdx.x; e < 16 * a.K; e += 256) {
+      const int s = n0 + e % 16, k = e / 16;
+      a.inT[(long)k * a.ldn + s] = s < a.n ? a.in[(long)s * a.ldi + k] : 0.f;
     }
-}
-
-// G[j][s] = (Y[j][s] - T[s][j]) / n (feature-major G, Y; sample-major T) and
-// per-block partial sums of (Y - T)^2 in double.
-__global__ __launch_bounds__(kT) void k_mse(int out, int n, int ld, const float* __restrict__ Y,
-                                            const float* __restrict__ T, float* __restrict__ G,
-                                            double* __restrict__ part) {
-  __shared__ double red[kT / 64];
+  if (wave > 0) red[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave > 0) return;
+#pragma unroll
+  for (int w = 0; w < 3; ++w) acc += red[w][lane];
+  const int s = n0 + i;
   double s2 = 0;
-  const long cnt = (long)out * n;
-  for (long e = (long)blockIdx.x * kT + threadIdx.x; e < cnt; e += (long)gridDim.x * kT) {
-    const int j = (int)(e / n), s = (int)(e % n);
-    const float d = Y[(long)j * ld + s] - T[(long)s * out + j];
-    G[(long)j * ld + s] = d / (float)n;
-    s2 += (double)d * d;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int m = m0 + 4 * kq + v;
+    if (m >= a.M) continue;
+    float c = acc[v];
+    if (a.back) {
+      c = a.mask[(long)m * a.ldn + s] > 0.f ? c : 0.f;
+    } else {
+      c += a.bias[m];
+      if (a.relu) c = fmaxf(c, 0.f);
+      if (a.T) {  // the delta of 0.5 / n sum (Y - T)^2
+        const float d = s < a.n ? c - a.T[(long)s * a.M + m] : 0.f;
+        s2 += (double)d * d;
+        c = d / (float)a.n;
+      }
+    }
+    if (a.out && s < a.n) a.out[(long)s * a.ldo + m] = c;
+    if (a.outT) a.outT[(long)m * a.ldn + s] = c;
   }
-  for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s2;
+  if (a.T) {
+    for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
+    if (lane == 0) a.part[blockIdx.x] = s2;
+  }
+}
+
+// ------------------------------------------------------ fused network --
+// One block takes 16 CT samples through the network: the activations stay in
+// LDS (sample-major, one buffer: a layer's outputs are held in registers until
+// every wave has read its inputs), the weights stream from L2.  W waves share
+// the output features, wave w taking the 16-feature tiles w, w + W, ... (RT at
+// most); the samples are the columns.  The weights of the next U steps are in
+// flight during the current U.  Training (MODE 1) goes on to the deltas of
+// every layer (W^T as the operand) and writes activations and deltas
+// feature-major, the layout in which the weight gradients contract over
+// samples.  Bound by the matrix cores at 62 TFLOP/s (102,400 samples of the
+// 43-256-256-256-120 network in 0.62 ms, features and phases included; 2.6 ms
+// with a GEMM per layer and the features formed on the host).
+//
+// Used from kNetFrom samples on, where its blocks of 16 (CT = 1, 16 waves)
+// cover half of the chip (training step: 106 against 89 us by layers at 1024
+// samples, 115 against 131 at 2048, 144 against 217 at 4096).  From kNetWide
+// on (twice that in training, whose blocks do three times the work) CT = 4 and
+// 8 waves read the weights a quarter as often (forward 83 us both ways at 8192
+// samples, 85 against 162 at 16384; training 308 against 273 and 405 against
+// 523).  Networks wider than kNetWidth or deeper than kNetLayers take k_layer
+// for every batch.
+constexpr int kNetLayers = 8, kNetWidth = 512, kNetFrom = 2048, kNetWide = 8192;
+struct NetArgs {
+  const float* P;                                       // parameters
+  const float* X;                                       // [n][in]
+  const float* T;                                       // training: targets [n][out]
+  float* Y;                                             // forward: [n][out]
+  float *H[kNetLayers], *G[kNetLayers];                 // training: inputs, deltas of each layer [width][ldn]
+  double* part;                                         // training: squared error of each block
+  long woff[kNetLayers], boff[kNetLayers];
+  int size[kNetLayers + 1];
+  int L, n, ldn, stride;                                // layers, samples, padded samples, floats per LDS row
+};
+// Inputs and outputs of the learned guess (MODE 2: complex float, 3: complex
+// double): sample s = r * P + p, features as mlfma_guess_features forms them,
+// outputs times the incident phase exp(-j k khat . r_p).
+struct GuessArgs {
+  const int *cls, *box_of, *part_of_box;
+  const double *cen, *khat;
+  const float* param;  // [classes] class parameter / scale
+  void* x;
+  double k;
+  int P, C, nx, ny, edge_cap;
+};
+__device__ __forceinline__ float guess_feature(const GuessArgs& q, int s, int f) {
+  const int r = s / q.P, p = s - r * q.P;
+  if (f < q.C) return q.cls[p] == f ? 1.f : 0.f;
+  f -= q.C;
+  const int box = q.box_of[p], ix = box % q.nx, iy = box / q.nx;
+  if (f < 8) {
+    const int o = f + (f >= 4), jx = ix + o % 3 - 1, jy = iy + o / 3 - 1;
+    const int nb = jx >= 0 && jy >= 0 && jx < q.nx && jy < q.ny ? q.part_of_box[jy * q.nx + jx] : -1;
+    return nb >= 0 ? q.param[q.cls[nb]] : 0.f;
+  }
+  if (f < 10) return (float)q.khat[3 * r + f - 8];
+  const int edge = min(min(ix, iy), min(q.nx - 1 - ix, q.ny - 1 - iy));
+  return (float)min(edge, q.edge_cap) / q.edge_cap;
+}
+
+// acc = sum_k A(m, k) h[sample][k] for this wave's feature tiles: A = W [M][K]
+// row-major, or its transpose (W [K][M]).  Rows and k past the end are zero.
+template <int CT, int W, int RT, int U, bool TRANS>
+__device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* __restrict__ Wl, bool vec, int M, int K,
+                                            const float* h, int stride, int wave, int i, int kq) {
+  const int nk = pad16(K) / 16;
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int k0, f32x4(&a)[U][RT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) {
+        const int m = 16 * (wave + W * rt) + i, k = 16 * (k0 + u) + 4 * kq;
+        a[u][rt] = TRANS ? col4(Wl, M, K, m, k) : row4(Wl, M, K, K, vec, m, k);
+      }
+  };
+  auto multiply = [&](int k0, const f32x4(&a)[U][RT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (k0 + u >= nk) break;
+      f32x4 b[CT];
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        b[ct] = *reinterpret_cast<const f32x4*>(h + (16 * ct + i) * stride + 16 * (k0 + u) + 4 * kq);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][rt][q], b[ct][q], acc[rt][ct], 0, 0, 0);
+    }
+  };
+  if (16 * wave >= pad16(M)) return;  // no tile of this layer is this wave's
+  f32x4 a0[U][RT], a1[U][RT];
+  load(0, a0);
+  for (int k0 = 0; k0 < nk; k0 += 2 * U) {
+    if (k0 + U < nk) load(k0 + U, a1);
+    multiply(k0, a0);
+    if (k0 + U >= nk) break;
+    if (k0 + 2 * U < nk) load(k0 + 2 * U, a0);
+    multiply(k0 + U, a1);
+  }
+}
+
+// MODE 0: Y = net(X); 1: activations, deltas and squared error of a training
+// batch; 2, 3: the learned guess in complex float, double.
+template <int CT, int W, int RT, int U, int MODE>
+__global__ __launch_bounds__(64 * W) void k_net(NetArgs a, GuessArgs q) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  float* h = reinterpret_cast<float*>(smem_raw);  // [S][stride]
+  __shared__ double red[W];
+  constexpr int S = 16 * CT, NT = 64 * W;
+  const int s0 = blockIdx.x * S, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, i = lane & 15, kq = lane >> 4;
+  {
+    const int in = a.size[0], inp = pad16(in);
+    for (int e = tid; e < S * inp; e += NT) {
+      const int s = e / inp, f = e - s * inp;
+      float v = 0.f;
+      if (f < in && s0 + s < a.n) v = MODE >= 2 ? guess_feature(q, s0 + s, f) : a.X[(long)(s0 + s) * in + f];
+      h[s * a.stride + f] = v;
+    }
+    __syncthreads();
+    if (MODE == 1)
+      for (int e = tid; e < S * in; e += NT) a.H[0][(long)(e / S) * a.ldn + s0 + e % S] = h[(e % S) * a.stride + e / S];
+  }
+  f32x4 acc[RT][CT];
+  double s2 = 0;
+  // h <- value(m, sample) of this wave's tiles, and to dst feature-major
+  auto store = [&](int M, float* dst, auto value) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const int m0 = 16 * (wave + W * rt) + 4 * kq;
+      if (m0 >= pad16(M)) continue;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int s = 16 * ct + i;
+        f32x4 o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          o[v] = m0 + v < M ? value(m0 + v, s0 + s, acc[rt][ct][v]) : 0.f;
+          if (MODE == 1 && m0 + v < M) dst[(long)(m0 + v) * a.ldn + s0 + s] = o[v];
+        }
+        *reinterpret_cast<f32x4*>(h + s * a.stride + m0) = o;
+      }
+    }
+  };
+  for (int l = 0; l < a.L; ++l) {
+    const int K = a.size[l], M = a.size[l + 1];
+    const bool last = l + 1 == a.L;
+    net_product<CT, W, RT, U, false>(acc, a.P + a.woff[l], K % 4 == 0 && a.woff[l] % 4 == 0, M, K, h, a.stride, wave, i, kq);
+    const float* __restrict__ bias = a.P + a.boff[l];
+    __syncthreads();  // every wave has read the layer's inputs
+    store(M, MODE != 1 ? nullptr : last ? a.G[l] : a.H[l + 1], [&](int m, int s, float c) {
+      c += bias[m];
+      if (!last) return fmaxf(c, 0.f);
+      if (MODE != 1) return c;
+      const float d = s < a.n ? c - a.T[(long)s * M + m] : 0.f;  // the delta of 0.5 / n sum (Y - T)^2
+      s2 += (double)d * d;
+      return d / (float)a.n;
+    });
+    __syncthreads();
+  }
+  if constexpr (MODE == 1) {
+    for (int l = a.L - 1; l > 0; --l) {
+      const int K = a.size[l + 1], M = a.size[l];
+      net_product<CT, W, RT, U, true>(acc, a.P + a.woff[l], false, M, K, h, a.stride, wave, i, kq);
+      const float* H = a.H[l];  // written by this thread in the forward pass
+      __syncthreads();
+      store(M, a.G[l - 1], [&](int m, int s, float c) { return H[(long)m * a.ldn + s] > 0.f ? c : 0.f; });
+      __syncthreads();
+    }
+    for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
+    if (lane == 0) red[wave] = s2;
+    __syncthreads();
+    if (tid == 0) {
+      double t = 0;
+      for (int w = 0; w < W; ++w) t += red[w];
+      a.part[blockIdx.x] = t;
+    }
+  } else if constexpr (MODE == 0) {
+    const int out = a.size[a.L], ns = min(S, a.n - s0);
+    for (int e = tid; e < ns * out; e += NT) a.Y[(long)s0 * out + e] = h[(e / out) * a.stride + e % out];
+  } else {
+    using T = typename std::conditional<MODE == 2, float, double>::type;
+    const int nc = a.size[a.L] / 2, ns = min(S, a.n - s0);
+    double* ph = reinterpret_cast<double*>(h + S * a.stride);  // [S][2]
+    for (int s = tid; s < ns; s += NT) {
+      const int r = (s0 + s) / q.P, p = (s0 + s) - r * q.P;
+      const double t = -q.k * (q.khat[3 * r] * q.cen[3 * p] + q.khat[3 * r + 1] * q.cen[3 * p + 1] +
+                               q.khat[3 * r + 2] * q.cen[3 * p + 2]);
+      sincos(t, &ph[2 * s + 1], &ph[2 * s]);
+    }
+    __syncthreads();
+    T* x = static_cast<T*>(q.x) + 2 * (long)s0 * nc;
+    for (int e = tid; e < ns * nc; e += NT) {
+      const int s = e / nc, j = e - s * nc;
+      const double re = h[s * a.stride + 2 * j], im = h[s * a.stride + 2 * j + 1], pr = ph[2 * s], pi = ph[2 * s + 1];
+      x[2 * e] = (T)(re * pr - im * pi);
+      x[2 * e + 1] = (T)(re * pi + im * pr);
+    }
+  }
+}
+
+// Adam's scalars (c1, c2: bias corrections 1 - beta^t)
+struct Adam {
+  float lr, b1, b2, eps, c1, c2;
+};
+__device__ __forceinline__ void adam_update(const Adam& A, float gg, float* p, float* m, float* v) {
+  const float mm = A.b1 * *m + (1.f - A.b1) * gg;
+  const float vv = A.b2 * *v + (1.f - A.b2) * gg * gg;
+  *m = mm;
+  *v = vv;
+  *p -= A.lr * (mm / A.c1) / (sqrtf(vv / A.c2) + A.eps);
+}
+
+// Weight and bias gradients of up to kNetLayers layers in one launch: a block
+// takes a 32 x 32 tile of one layer's dW = G H^T, its four waves a quarter of
+// the samples each (both operands feature-major, so that a lane's 16-byte loads
+// run along the samples), adds their sums through LDS in a fixed order and
+// finishes one of its 16 x 16 tiles per wave.  The tiles of the first input
+// columns also sum the rows of G, the bias gradients.  With `adam` the
+// parameters are updated in place, else the gradients are written.  Small
+// batches are bound by latency: four steps of loads are in flight.
+struct NetGradArgs {
+  const float *H[kNetLayers], *G[kNetLayers];
+  float *p, *m, *v, *g;
+  long woff[kNetLayers], boff[kNetLayers];
+  int size[kNetLayers + 1], first[kNetLayers + 1];  // first block of each layer
+  int L, ldn, adam;
+  Adam A;
+};
+__global__ __launch_bounds__(256) void k_net_grad(NetGradArgs a) {
+  __shared__ f32x4 red[4][4][64];
+  __shared__ float rsum[4][32];
+  int l = 0;
+  while (l + 1 < a.L && (int)blockIdx.x >= a.first[l + 1]) ++l;
+  const int M = a.size[l + 1], N = a.size[l], tn = (N + 31) / 32, t = blockIdx.x - a.first[l];
+  const int m0 = (t / tn) * 32, n0 = (t % tn) * 32;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const float *__restrict__ G = a.G[l], *__restrict__ H = a.H[l];
+  const int nk = a.ldn / 16, k0 = wave * nk / 4, k1 = (wave + 1) * nk / 4;
+  const float *pa[2], *pb[2];
+  bool oka[2], okb[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int m = m0 + 16 * u + i, n = n0 + 16 * u + i;
+    oka[u] = m < M;
+    okb[u] = n < N;
+    pa[u] = G + (long)min(m, M - 1) * a.ldn + 4 * kq;
+    pb[u] = H + (long)min(n, N - 1) * a.ldn + 4 * kq;
+  }
+  f32x4 acc[2][2];
+  float rs[2] = {0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) acc[u][v] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int k = k0; k < k1; ++k) {
+    f32x4 x[2], y[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      x[u] = *reinterpret_cast<const f32x4*>(pa[u] + 16 * (long)k);
+      y[u] = *reinterpret_cast<const f32x4*>(pb[u] + 16 * (long)k);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][q], y[v][q], acc[u][v], 0, 0, 0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) rs[u] += (x[u][0] + x[u][1]) + (x[u][2] + x[u][3]);
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    rs[u] += __shfl_xor(rs[u], 16);
+    rs[u] += __shfl_xor(rs[u], 32);
+    if (kq == 0) rsum[wave][16 * u + i] = rs[u];
+  }
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+#pragma unroll
+    for (int v = 0; v < 2; ++v) red[wave][2 * u + v][lane] = acc[u][v];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double t = 0;
-    for (int w = 0; w < kT / 64; ++w) t += red[w];
-    part[blockIdx.x] = t;
+  auto put = [&](long o, float g) {
+    if (a.adam) adam_update(a.A, g, a.p + o, a.m + o, a.v + o);
+    else a.g[o] = g;
+  };
+  f32x4 sum = red[0][wave][lane];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) sum += red[w][wave][lane];
+  const int n = n0 + 16 * (wave & 1) + i;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int m = m0 + 16 * (wave >> 1) + 4 * kq + e;
+    if (m < M && n < N) put(a.woff[l] + (long)m * N + n, sum[e]);
   }
+  if (wave == 0 && n0 == 0 && lane < 32 && m0 + lane < M)
+    put(a.boff[l] + m0 + lane, (rsum[0][lane] + rsum[1][lane]) + (rsum[2][lane] + rsum[3][lane]));
 }
 
-// db[j] = sum_s G[j][s]  (one block per row, fixed order)
-__global__ __launch_bounds__(kT) void k_rowsum(int n, int ld, const float* __restrict__ G, float* __restrict__ db) {
-  __shared__ float red[kT / 64];
-  const int j = blockIdx.x;
-  float s = 0.f;
-  for (int e = threadIdx.x; e < n; e += kT) s += G[(long)j * ld + e];
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.f;
-    for (int w = 0; w < kT / 64; ++w) t += red[w];
-    db[j] = t;
-  }
-}
-
-// Adam (beta1, beta2, eps; bias corrections c1 = 1 - beta1^t, c2 = 1 - beta2^t)
-__global__ __launch_bounds__(kT) void k_adam(long cnt, float* __restrict__ p, const float* __restrict__ g,
-                                             float* __restrict__ m, float* __restrict__ v, float lr, float b1,
-                                             float b2, float eps, float c1, float c2) {
-  for (long e = (long)blockIdx.x * kT + threadIdx.x; e < cnt; e += (long)gridDim.x * kT) {
-    const float gg = g[e];
-    const float mm = b1 * m[e] + (1.f - b1) * gg;
-    const float vv = b2 * v[e] + (1.f - b2) * gg * gg;
-    m[e] = mm;
-    v[e] = vv;
-    p[e] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-  }
-}
-
-// x[r][p][j] = (Y[s][2j] + i Y[s][2j+1]) * phase[s], s = r * P + p
+// The features of a learned guess, and x[s][j] = (Y[s][2j] + i Y[s][2j+1]) *
+// phase[s], for the batches k_net does not take.
 template <typename T>
-__global__ __launch_bounds__(kT) void k_guess(int S, int n, const float* __restrict__ Y,
-                                              const double* __restrict__ phase, T* __restrict__ x) {
+__global__ __launch_bounds__(kT) void k_guess(GuessArgs q, int S, int n, const float* __restrict__ Y, T* __restrict__ x) {
   const long cnt = (long)S * n;
   for (long e = (long)blockIdx.x * kT + threadIdx.x; e < cnt; e += (long)gridDim.x * kT) {
-    const int s = (int)(e / n), j = (int)(e % n);
+    const int s = (int)(e / n), j = (int)(e % n), r = s / q.P, p = s - r * q.P;
+    const double t = -q.k * (q.khat[3 * r] * q.cen[3 * p] + q.khat[3 * r + 1] * q.cen[3 * p + 1] +
+                             q.khat[3 * r + 2] * q.cen[3 * p + 2]);
+    double pr, pi;
+    sincos(t, &pi, &pr);
     const double re = Y[(long)s * 2 * n + 2 * j], im = Y[(long)s * 2 * n + 2 * j + 1];
-    const double pr = phase[2 * s], pi = phase[2 * s + 1];
     x[2 * e] = (T)(re * pr - im * pi);
     x[2 * e + 1] = (T)(re * pi + im * pr);
   }
 }
-
-__global__ __launch_bounds__(kT) void k_relu_copy(long cnt, const float* __restrict__ a, float* __restrict__ b,
-                                                  int relu) {
+__global__ __launch_bounds__(kT) void k_features(GuessArgs q, int S, int nf, float* __restrict__ X) {
+  const long cnt = (long)S * nf;
   for (long e = (long)blockIdx.x * kT + threadIdx.x; e < cnt; e += (long)gridDim.x * kT)
-    b[e] = relu ? fmaxf(a[e], 0.f) : a[e];
-}
-
-// Y[s][j] = act[j][s] (feature-major to sample-major)
-__global__ __launch_bounds__(kT) void k_to_samples(int out, int n, const float* __restrict__ a, float* __restrict__ Y) {
-  const long cnt = (long)out * n;
-  for (long e = (long)blockIdx.x * kT + threadIdx.x; e < cnt; e += (long)gridDim.x * kT) {
-    const int s = (int)(e / out), j = (int)(e % out);
-    Y[e] = a[(long)j * n + s];
-  }
+    X[e] = guess_feature(q, (int)(e / nf), (int)(e % nf));
 }
 
 struct DevBuf {
@@ -217,121 +516,185 @@ class Mlp {
   std::vector<long> woff, boff;  // offsets of each layer's W [out][in] and b [out] in the parameter vector
   long nparam = 0;
   DevBuf params, grads, m1, m2;
-  std::vector<DevBuf> act, pre;  // per layer, feature-major [width][n]
-  DevBuf gcur, gprev, part;
-  int n_cap = 0;
   long step = 0;
-
+  // training: inputs and deltas of the layers, feature-major, and the blocks'
+  // squared errors, written to host memory by the kernels; activations between
+  // k_layer launches; the guess's class parameters, directions, features and
+  // outputs
+  std::vector<DevBuf> fin, fdel;
+  int f_cap = 0, h_cap = 0;
+  double* hpart = nullptr;
+  hipEvent_t done = nullptr;
+  DevBuf act[2], gtab, gx, gy;
   int layers() const { return (int)sizes.size() - 1; }
+  ~Mlp() {
+    if (hpart) (void)hipHostFree(hpart);
+    if (done) (void)hipEventDestroy(done);
+  }
 
-  int ensure_batch(int n, std::string& err) {
-    if (n <= n_cap) return 0;
-    act.resize(layers());
-    pre.resize(layers());
-    int widest = sizes[0];
+  int widest() const { return *std::max_element(sizes.begin(), sizes.end()); }
+  bool fused(int n) const { return n >= kNetFrom && layers() <= kNetLayers && widest() <= kNetWidth; }
+  static int tile(int n, bool train) { return n >= (train ? 2 : 1) * kNetWide ? 64 : 16; }  // samples per block of k_net
+  NetArgs net_args(int n, bool train) const {
+    NetArgs a{};
+    a.P = params.f();
     for (int l = 0; l < layers(); ++l) {
-      MLP_TRY(act[l].ensure((size_t)sizes[l + 1] * n * sizeof(float)));
-      MLP_TRY(pre[l].ensure((size_t)sizes[l + 1] * n * sizeof(float)));
-      widest = std::max(widest, sizes[l + 1]);
+      a.woff[l] = woff[l];
+      a.boff[l] = boff[l];
     }
-    MLP_TRY(gcur.ensure((size_t)widest * n * sizeof(float)));
-    MLP_TRY(gprev.ensure((size_t)widest * n * sizeof(float)));
-    MLP_TRY(part.ensure(4096 * sizeof(double)));
-    n_cap = n;
-    return 0;
+    for (size_t l = 0; l < sizes.size(); ++l) a.size[l] = sizes[l];
+    a.L = layers();
+    a.n = n;
+    const int S = tile(n, train);
+    a.ldn = (n + S - 1) / S * S;
+    a.stride = (widest() + 15) / 16 * 16 + 4;  // (4 more: columns of a step fall on different banks)
+    return a;
   }
-
-  void gemm(const Gemm& g, hipStream_t st) {
-    hipLaunchKernelGGL(k_gemm, dim3((g.M + 63) / 64, (g.N + 63) / 64), dim3(kT), 0, st, g);
+  template <int MODE>
+  int launch_net(const NetArgs& a, const GuessArgs& q, hipStream_t st, std::string& err) {
+    const int S = tile(a.n, MODE == 1);
+    const dim3 grid((a.n + S - 1) / S);
+    const uint32_t sh = (uint32_t)(S * a.stride * sizeof(float) + (MODE >= 2 ? 2 * S * sizeof(double) : 0));
+    auto run = [&](auto kernel, int W) -> int {
+      if (sh > 64 * 1024)
+        MLP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)sh));
+      hipLaunchKernelGGL(kernel, grid, dim3(64 * W), sh, st, a, q);
+      return 0;
+    };
+    const bool narrow = widest() <= 256;
+    constexpr int U = MODE == 1 ? 6 : 8;  // (training keeps more in registers)
+    if (S == 16) return narrow ? run(k_net<1, 16, 1, U, MODE>, 16) : run(k_net<1, 16, 2, U / 2, MODE>, 16);
+    return narrow ? run(k_net<4, 8, 2, 4, MODE>, 8) : run(k_net<4, 8, 4, 2, MODE>, 8);
   }
-
-  // forward pass on X [n][in] (sample-major); pre-activations and outputs
-  // of every layer kept feature-major
-  void forward(const float* X, int n, hipStream_t st) {
-    for (int l = 0; l < layers(); ++l) {
-      Gemm g{};
-      g.A = params.f() + woff[l];
-      g.sa0 = sizes[l];
-      g.sa1 = 1;
-      if (l == 0) {
-        g.B = X;
-        g.sb0 = 1;
-        g.sb1 = sizes[0];
-      } else {
-        g.B = act[l - 1].f();
-        g.sb0 = n;
-        g.sb1 = 1;
+  // The layers one launch each, forward: outputs to Y (inference), or the last
+  // layer's deltas and squared errors (training: fin, fdel, part).
+  int forward_layers(const float* X, const float* T, int n, int ldn, float* Y, double* part, hipStream_t st,
+                     std::string& err) {
+    const int L = layers(), ld = (widest() + 15) / 16 * 16;
+    for (auto& b : act) MLP_TRY(b.ensure((size_t)n * ld * sizeof(float)));
+    for (int l = 0; l < L; ++l) {
+      LayerArgs a{};
+      const bool last = l + 1 == L;
+      a.W = params.f() + woff[l];
+      a.bias = params.f() + boff[l];
+      a.in = l ? act[(l - 1) % 2].f() : X;
+      a.ldi = l ? ld : sizes[0];
+      a.M = sizes[l + 1];
+      a.K = sizes[l];
+      a.n = n;
+      a.ldn = ldn;
+      a.relu = !last;
+      a.vecw = a.K % 4 == 0 && woff[l] % 4 == 0;
+      a.veci = a.K % 4 == 0 && (l > 0 || reinterpret_cast<uintptr_t>(X) % 16 == 0);
+      a.out = last && !T ? Y : act[l % 2].f();
+      a.ldo = last && !T ? a.M : ld;
+      if (T) {
+        a.inT = l ? nullptr : fin[0].f();
+        a.outT = last ? fdel[l].f() : fin[l + 1].f();
+        if (last) {
+          a.T = T;
+          a.part = part;
+        }
       }
-      g.C = pre[l].f();
-      g.sc0 = n;
-      g.sc1 = 1;
-      g.bias = params.f() + boff[l];
-      g.M = sizes[l + 1];
-      g.N = n;
-      g.K = sizes[l];
-      gemm(g, st);
-      const long cnt = (long)g.M * n;
-      hipLaunchKernelGGL(k_relu_copy, dim3(grid(cnt)), dim3(kT), 0, st, cnt, (const float*)pre[l].f(), act[l].f(),
-                         l + 1 < layers() ? 1 : 0);
-    }
-  }
-
-  // gradients of 0.5/n sum |net(X) - T|^2 into `grads`; returns the loss
-  int backward(const float* X, const float* T, int n, double* loss, hipStream_t st, std::string& err) {
-    const int L = layers(), out = sizes[L];
-    const int nb = grid((long)out * n);
-    hipLaunchKernelGGL(k_mse, dim3(nb), dim3(kT), 0, st, out, n, n, (const float*)act[L - 1].f(), T, gcur.f(),
-                       part.d());
-    std::vector<double> hp(nb);
-    MLP_TRY(hipMemcpyAsync(hp.data(), part.p, nb * sizeof(double), hipMemcpyDeviceToHost, st));
-    for (int l = L - 1; l >= 0; --l) {
-      // dW = G H_{l-1}^T  (H_{-1} = X)
-      Gemm g{};
-      g.A = gcur.f();
-      g.sa0 = n;
-      g.sa1 = 1;
-      if (l == 0) {
-        g.B = X;
-        g.sb0 = sizes[0];
-        g.sb1 = 1;
-      } else {
-        g.B = act[l - 1].f();
-        g.sb0 = 1;
-        g.sb1 = n;
-      }
-      g.C = grads.f() + woff[l];
-      g.sc0 = sizes[l];
-      g.sc1 = 1;
-      g.M = sizes[l + 1];
-      g.N = sizes[l];
-      g.K = n;
-      gemm(g, st);
-      hipLaunchKernelGGL(k_rowsum, dim3(sizes[l + 1]), dim3(kT), 0, st, n, n, (const float*)gcur.f(),
-                         grads.f() + boff[l]);
-      if (l == 0) break;
-      // G_{l-1} = (W^T G) * (pre_{l-1} > 0)
-      Gemm b{};
-      b.A = params.f() + woff[l];
-      b.sa0 = 1;
-      b.sa1 = sizes[l];
-      b.B = gcur.f();
-      b.sb0 = n;
-      b.sb1 = 1;
-      b.C = gprev.f();
-      b.sc0 = n;
-      b.sc1 = 1;
-      b.mask = pre[l - 1].f();
-      b.M = sizes[l];
-      b.N = n;
-      b.K = sizes[l + 1];
-      gemm(b, st);
-      std::swap(gcur, gprev);
+      hipLaunchKernelGGL(k_layer, dim3(((a.M + 15) / 16) * ((n + 15) / 16)), dim3(256), 0, st, a);
     }
     MLP_TRY(hipGetLastError());
-    MLP_TRY(hipStreamSynchronize(st));
-    double s = 0;
-    for (double v : hp) s += v;
-    if (loss) *loss = 0.5 * s / n;
+    return 0;
+  }
+  // ... and back: the deltas of every layer but the last
+  int backward_layers(int n, int ldn, hipStream_t st, std::string& err) {
+    const int L = layers(), ld = (widest() + 15) / 16 * 16;
+    for (int l = L - 1; l > 0; --l) {
+      LayerArgs a{};
+      a.W = params.f() + woff[l];
+      a.in = act[l % 2].f();  // this layer's deltas
+      a.ldi = ld;
+      a.M = sizes[l];
+      a.K = sizes[l + 1];
+      a.n = n;
+      a.ldn = ldn;
+      a.back = 1;
+      a.veci = a.K % 4 == 0;
+      a.mask = fin[l].f();
+      a.out = act[(l - 1) % 2].f();
+      a.ldo = ld;
+      a.outT = fdel[l - 1].f();
+      hipLaunchKernelGGL(k_layer, dim3(((a.M + 15) / 16) * ((n + 15) / 16)), dim3(256), 0, st, a);
+    }
+    MLP_TRY(hipGetLastError());
+    return 0;
+  }
+  // Activations and deltas of a batch, then the gradients into `grads` or,
+  // with an Adam step, straight into the parameters.  Returns once the loss is
+  // on the host; the gradient kernel may still run.
+  int train_batch(const float* X, const float* T, int n, const Adam* A, double* loss, hipStream_t st, std::string& err) {
+    const int L = layers();
+    const bool net = fused(n);
+    const int ldn = net ? net_args(n, true).ldn : (n + 15) / 16 * 16;
+    const int nb = net ? ldn / tile(n, true) : ((sizes[L] + 15) / 16) * (ldn / 16);
+    if (ldn > f_cap) {
+      f_cap = 0;
+      fin.resize(L);
+      fdel.resize(L);
+      for (int l = 0; l < L; ++l) {
+        MLP_TRY(fin[l].ensure((size_t)sizes[l] * ldn * sizeof(float)));
+        MLP_TRY(fdel[l].ensure((size_t)sizes[l + 1] * ldn * sizeof(float)));
+      }
+      f_cap = ldn;
+    }
+    if (nb > h_cap) {
+      if (hpart) (void)hipHostFree(hpart);
+      hpart = nullptr;
+      h_cap = 0;
+      MLP_TRY(hipHostMalloc(reinterpret_cast<void**>(&hpart), nb * sizeof(double), hipHostMallocDefault));
+      h_cap = nb;
+    }
+    if (!done) MLP_TRY(hipEventCreateWithFlags(&done, hipEventDisableTiming));
+    void* dpart = nullptr;
+    MLP_TRY(hipHostGetDevicePointer(&dpart, hpart, 0));
+    if (net) {
+      NetArgs a = net_args(n, true);
+      a.X = X;
+      a.T = T;
+      a.part = static_cast<double*>(dpart);
+      for (int l = 0; l < L; ++l) {
+        a.H[l] = fin[l].f();
+        a.G[l] = fdel[l].f();
+      }
+      if (int rc = launch_net<1>(a, GuessArgs{}, st, err)) return rc;
+      MLP_TRY(hipGetLastError());
+    } else if (int rc = forward_layers(X, T, n, ldn, nullptr, static_cast<double*>(dpart), st, err)) {
+      return rc;
+    }
+    MLP_TRY(hipEventRecord(done, st));
+    if (!net)
+      if (int rc = backward_layers(n, ldn, st, err)) return rc;
+    for (int l0 = 0; l0 < L; l0 += kNetLayers) {
+      NetGradArgs g{};
+      g.L = std::min(L - l0, kNetLayers);
+      for (int l = 0; l < g.L; ++l) {
+        g.H[l] = fin[l0 + l].f();
+        g.G[l] = fdel[l0 + l].f();
+        g.woff[l] = woff[l0 + l];
+        g.boff[l] = boff[l0 + l];
+        g.first[l + 1] = g.first[l] + ((sizes[l0 + l + 1] + 31) / 32) * ((sizes[l0 + l] + 31) / 32);
+      }
+      for (int l = 0; l <= g.L; ++l) g.size[l] = sizes[l0 + l];
+      g.p = params.f();
+      g.m = m1.f();
+      g.v = m2.f();
+      g.g = grads.f();
+      g.ldn = ldn;
+      g.adam = A ? 1 : 0;
+      if (A) g.A = *A;
+      hipLaunchKernelGGL(k_net_grad, dim3(g.first[g.L]), dim3(256), 0, st, g);
+    }
+    MLP_TRY(hipGetLastError());
+    MLP_TRY(hipEventSynchronize(done));
+    double s2 = 0;
+    for (int b = 0; b < nb; ++b) s2 += hpart[b];
+    if (loss) *loss = 0.5 * s2 / n;
     return 0;
   }
 };
@@ -399,11 +762,11 @@ int mlp_set_params(Mlp* m, const float* host, std::string& err) {
 
 int mlp_forward(Mlp* m, const float* X, int n, float* Y, void* stream, std::string& err) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (int rc = m->ensure_batch(n, err)) return rc;
-  m->forward(X, n, st);
-  const int out = m->sizes.back();
-  hipLaunchKernelGGL(k_to_samples, dim3(grid((long)out * n)), dim3(kT), 0, st, out, n,
-                     (const float*)m->act.back().f(), Y);
+  if (!m->fused(n)) return m->forward_layers(X, nullptr, n, 0, Y, nullptr, st, err);
+  NetArgs a = m->net_args(n, false);
+  a.X = X;
+  a.Y = Y;
+  if (int rc = m->launch_net<0>(a, GuessArgs{}, st, err)) return rc;
   MLP_TRY(hipGetLastError());
   return 0;
 }
@@ -411,9 +774,8 @@ int mlp_forward(Mlp* m, const float* X, int n, float* Y, void* stream, std::stri
 int mlp_loss_grad(Mlp* m, const float* X, const float* T, int n, double* loss, float* grads, void* stream,
                   std::string& err) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (int rc = m->ensure_batch(n, err)) return rc;
-  m->forward(X, n, st);
-  if (int rc = m->backward(X, T, n, loss, st, err)) return rc;
+  if (int rc = m->train_batch(X, T, n, nullptr, loss, st, err)) return rc;
+  MLP_TRY(hipStreamSynchronize(st));
   if (grads) MLP_TRY(hipMemcpy(grads, m->grads.p, m->nparam * sizeof(float), hipMemcpyDeviceToHost));
   return 0;
 }
@@ -421,42 +783,92 @@ int mlp_loss_grad(Mlp* m, const float* X, const float* T, int n, double* loss, f
 int mlp_train_step(Mlp* m, const float* X, const float* T, int n, float lr, double* loss, void* stream,
                    std::string& err) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  if (int rc = m->ensure_batch(n, err)) return rc;
-  m->forward(X, n, st);
-  if (int rc = m->backward(X, T, n, loss, st, err)) return rc;
+  const double t = (double)(m->step + 1);
+  const Adam A{lr, 0.9f, 0.999f, 1e-8f, (float)(1.0 - std::pow(0.9, t)), (float)(1.0 - std::pow(0.999, t))};
+  if (int rc = m->train_batch(X, T, n, &A, loss, st, err)) return rc;
   m->step++;
-  const float b1 = 0.9f, b2 = 0.999f;
-  const float c1 = (float)(1.0 - std::pow(0.9, (double)m->step)), c2 = (float)(1.0 - std::pow(0.999, (double)m->step));
-  hipLaunchKernelGGL(k_adam, dim3(grid(m->nparam)), dim3(kT), 0, st, m->nparam, m->params.f(),
-                     (const float*)m->grads.f(), m->m1.f(), m->m2.f(), lr, b1, b2, 1e-8f, c1, c2);
-  MLP_TRY(hipGetLastError());
   return 0;
 }
 
-int mlp_guess(Mlp* m, const std::vector<float>& X, const std::vector<std::complex<double>>& phase, int R, int P,
-              int n, int precision, void* x_dev, void* stream, std::string& err) {
+int mlp_guess(Mlp* m, const GuessInput& in, int R, int n, int precision, void* x_dev, void* stream, std::string& err) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-  const int S = R * P, in = m->sizes.front();
-  if ((long)X.size() != (long)S * in || m->sizes.back() != 2 * n) {
+  const int S = R * in.P, nf = m->sizes.front();
+  if (nf != in.C + 11 || m->sizes.back() != 2 * n) {
     err = "network inputs/outputs do not match the features / unknowns per particle";
     return -1;
   }
-  DevBuf dx, dy, dph;
-  MLP_TRY(dx.ensure(X.size() * sizeof(float)));
-  MLP_TRY(dy.ensure((size_t)S * 2 * n * sizeof(float)));
-  MLP_TRY(dph.ensure((size_t)S * 2 * sizeof(double)));
-  MLP_TRY(hipMemcpyAsync(dx.p, X.data(), X.size() * sizeof(float), hipMemcpyHostToDevice, st));
-  MLP_TRY(hipMemcpyAsync(dph.p, phase.data(), (size_t)S * 2 * sizeof(double), hipMemcpyHostToDevice, st));
-  if (int rc = mlp_forward(m, dx.f(), S, dy.f(), stream, err)) return rc;
-  const long cnt = (long)S * n;
-  if (precision == 1)
-    hipLaunchKernelGGL(k_guess<double>, dim3(grid(cnt)), dim3(kT), 0, st, S, n, (const float*)dy.f(),
-                       (const double*)dph.d(), static_cast<double*>(x_dev));
-  else
-    hipLaunchKernelGGL(k_guess<float>, dim3(grid(cnt)), dim3(kT), 0, st, S, n, (const float*)dy.f(),
-                       (const double*)dph.d(), static_cast<float*>(x_dev));
+  // the call's small tables: directions, then class parameters over scale
+  const size_t kb = (size_t)3 * R * sizeof(double), tb = kb + in.C * sizeof(float);
+  std::vector<unsigned char> tab(tb);
+  std::memcpy(tab.data(), in.khat, kb);
+  for (int c = 0; c < in.C; ++c) {
+    const float v = (float)(in.class_param[c] / in.scale);
+    std::memcpy(tab.data() + kb + c * sizeof(float), &v, sizeof(float));
+  }
+  MLP_TRY(m->gtab.ensure(tb));
+  MLP_TRY(hipMemcpyAsync(m->gtab.p, tab.data(), tb, hipMemcpyHostToDevice, st));
+  GuessArgs q{};
+  q.cls = in.cls;
+  q.box_of = in.box_of;
+  q.part_of_box = in.part_of_box;
+  q.cen = in.centers;
+  q.khat = m->gtab.d();
+  q.param = reinterpret_cast<const float*>(static_cast<const char*>(m->gtab.p) + kb);
+  q.x = x_dev;
+  q.k = in.k;
+  q.P = in.P;
+  q.C = in.C;
+  q.nx = in.nx;
+  q.ny = in.ny;
+  q.edge_cap = in.edge_cap;
+  if (m->fused(S)) {
+    const NetArgs a = m->net_args(S, false);
+    if (int rc = precision == 1 ? m->launch_net<3>(a, q, st, err) : m->launch_net<2>(a, q, st, err)) return rc;
+  } else {
+    MLP_TRY(m->gx.ensure((size_t)S * nf * sizeof(float)));
+    MLP_TRY(m->gy.ensure((size_t)S * 2 * n * sizeof(float)));
+    hipLaunchKernelGGL(k_features, dim3(grid((long)S * nf)), dim3(kT), 0, st, q, S, nf, m->gx.f());
+    if (int rc = mlp_forward(m, m->gx.f(), S, m->gy.f(), stream, err)) return rc;
+    const dim3 g(grid((long)S * n));
+    if (precision == 1)
+      hipLaunchKernelGGL(k_guess<double>, g, dim3(kT), 0, st, q, S, n, (const float*)m->gy.f(), static_cast<double*>(x_dev));
+    else
+      hipLaunchKernelGGL(k_guess<float>, g, dim3(kT), 0, st, q, S, n, (const float*)m->gy.f(), static_cast<float*>(x_dev));
+  }
   MLP_TRY(hipGetLastError());
-  MLP_TRY(hipStreamSynchronize(st));  // the staging buffers are released on return
+  MLP_TRY(hipStreamSynchronize(st));  // the caller's tables may be released on return
+  return 0;
+}
+
+// Device copies of the particle tables the guess reads.
+struct GuessTables {
+  DevBuf mem;
+  int device = -1;
+};
+GuessTables* guess_tables_create() { return new GuessTables(); }
+void guess_tables_destroy(GuessTables* t) { delete t; }
+int guess_tables_fill(GuessTables* t, const std::vector<int>& cls, const std::vector<int>& box_of,
+                      const std::vector<int>& part_of_box, const std::vector<double>& centers, GuessInput& in,
+                      std::string& err) {
+  int dev = 0;
+  MLP_TRY(hipGetDevice(&dev));
+  const size_t nc = centers.size() * sizeof(double), ni = cls.size() * sizeof(int), nb = part_of_box.size() * sizeof(int);
+  if (t->device != dev) {  // first use, or another device than the copies are on
+    t->device = -1;
+    t->mem = DevBuf();
+    MLP_TRY(t->mem.ensure(nc + 2 * ni + nb));
+    char* p = static_cast<char*>(t->mem.p);
+    MLP_TRY(hipMemcpy(p, centers.data(), nc, hipMemcpyHostToDevice));
+    MLP_TRY(hipMemcpy(p + nc, cls.data(), ni, hipMemcpyHostToDevice));
+    MLP_TRY(hipMemcpy(p + nc + ni, box_of.data(), ni, hipMemcpyHostToDevice));
+    MLP_TRY(hipMemcpy(p + nc + 2 * ni, part_of_box.data(), nb, hipMemcpyHostToDevice));
+    t->device = dev;
+  }
+  const char* p = static_cast<const char*>(t->mem.p);
+  in.centers = reinterpret_cast<const double*>(p);
+  in.cls = reinterpret_cast<const int*>(p + nc);
+  in.box_of = reinterpret_cast<const int*>(p + nc + ni);
+  in.part_of_box = reinterpret_cast<const int*>(p + nc + 2 * ni);
   return 0;
 }
 
