@@ -39,7 +39,7 @@ ENGINE_SRC = os.path.join(ROOT, "paper_2407_21724_amd", "csrc", "engine.hip")
 KERNELS = [
     ("aggregate_l", "k_agg_stream", "hbm"),
     ("translate", "k_translate_reg", "hbm"),          # FP32: every level in one launch, tiles in registers
-    ("disaggregate_l", "k_dis_stream", "hbm"),
+    ("disaggregate_l", "k_dis_mfma", "hbm"),
     ("near_sum", "k_near_sum", "hbm"),
 ]
 

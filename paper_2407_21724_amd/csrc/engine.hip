@@ -881,6 +881,7 @@ struct InterpArgs {
   const int* wlo;            // [nst][2] first input column of each half-wave's window
   int nxc, nyc, ntc, npc, nxp, nyp, ntp, npp;
   int R, nst, nch, wlen, ntap;
+  int scols;                 // disaggregation: columns per strip
 };
 
 template <typename T>
@@ -1070,23 +1071,57 @@ __global__ __launch_bounds__(64) void k_agg_stream(InterpArgs<T> A) {
 }
 
 // G_c += W_c^-1 I^T W_P (conj(phase_c) G_P) for the four children c of a
-// parent box: the transposed stencils, streamed over the parent's rows.  A
-// lane holds one child column (and its partner half a turn on); per parent
-// row it forms the transposed phi stencil of the conjugate-phased parent row
-// for each child, and adds it with the transposed theta weights into the
-// `order` extended child rows that row reaches; an extended row is finished
-// (added to the child's pattern) once no later parent row reaches it.  A
-// pole reflection's sum belongs to the partner column's child row, which is
-// the lane exchange of the transposed stencil.  Chunks own disjoint ranges
-// of extended rows (the reflections with their rows).
-template <typename T, int ORD, int NT, int SW>
-__global__ __launch_bounds__(64) void k_dis_stream(InterpArgs<T> A) {
-  constexpr int G = kIStrip / SW;
-  extern __shared__ unsigned char smem_raw[];
-  C2<T>* lds = reinterpret_cast<C2<T>*>(smem_raw);  // [2 buffers][G][4 children][2 halves][wlen]
+// parent box: the transposed stencils, streamed over the parent's rows, the phi
+// stencils on the matrix cores.  A wave takes (RHS, parent box, component,
+// strip of at most 16 child columns with the same strip half a turn on, row
+// chunk) for all four children, two parent rows at a time.  It stages the rows'
+// windows, times the children's conjugate phases, as 16 real vectors (child,
+// row, re/im) over the window's KW columns; the transposed phi stencils of the
+// strip are a KW x 16 banded matrix, held in KW / 4 registers for the whole
+// walk, so a strip's stencils are KW / 4 16 x 16 x 4 products.  A result lane
+// holds one column of one child, re and im of both rows: the transposed theta
+// stencils add them into the `order` extended child rows that a parent row
+// reaches, and an extended row is finished (added to the child's pattern) once
+// no later parent row reaches it.  A pole reflection's sum belongs to the
+// column half a turn on: the other strip's value in the same lane.  Chunks own
+// disjoint ranges of extended rows (the reflections with their rows).
+//
+// The zeros of the band cost the matrix cores KW / taps = 3 to 4 times the
+// stencil's products, on a unit that is idle otherwise; the vector unit is left
+// with the phases and the theta stencils, and the LDS reads fall to a fifth of
+// a per-column gather's.  Against that gather (one lane per column, all four
+// children's taps on the vector unit, one row at a time) the levels of the
+// 200 x 200 lens at 16 RHS take 6.4 ms instead of 7.3 ms, 2.7 to 3.9 TB/s of the
+// 4.7 TB/s that a copy reaches, and those of the 40 x 40 array at one RHS, a
+// chain of rows, 17 to 19 us each instead of 29 to 43.  Eight waves per SIMD
+// would need 64 registers, which spills; a wave over several RHS (2, 4, 8)
+// measured the same to 2% slower.
+template <typename T>
+struct Mfma16;  // 16 x 16 x 4 product, and the row of result register v in lane group g
+template <>
+struct Mfma16<float> {
+  typedef float vec2 __attribute__((ext_vector_type(2)));
+  typedef float vec4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ vec4 mul(float a, float b, vec4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static constexpr __device__ int row(int g, int v) { return 4 * g + v; }
+};
+template <>
+struct Mfma16<double> {
+  typedef double vec2 __attribute__((ext_vector_type(2)));
+  typedef double vec4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ vec4 mul(double a, double b, vec4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  static constexpr __device__ int row(int g, int v) { return g + 4 * v; }
+};
+// PK (KW <= 32): both halves' windows are staged by one load per row.
+template <typename T, int ORD, int KW>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 1))) void k_dis_mfma(InterpArgs<T> A) {
+  using MM = Mfma16<T>;
+  constexpr bool PK = KW <= 32;
+  constexpr int NL = PK ? 1 : 2;    // loads per row (halves of the row)
+  constexpr int LS = KW + 2;        // values per staged vector (2 more: rows on different banks)
+  __shared__ T lds[2][16][LS];      // [half][vector of child, 2 row + re/im][window column]
   const int nbp = A.nxp * A.nyp, nbc = A.nxc * A.nyc;
-  const int ncomp = 2 / G;
-  const int total = A.R * nbp * ncomp * A.nst * A.nch;
+  const int total = A.R * nbp * 2 * A.nst * A.nch;
   const int item = xcd_block(blockIdx.x, total);
   if (item >= total) return;
   int t = item;
@@ -1094,170 +1129,180 @@ __global__ __launch_bounds__(64) void k_dis_stream(InterpArgs<T> A) {
   t /= A.nch;
   const int st = t % A.nst;
   t /= A.nst;
-  const int comp0 = G == 2 ? 0 : t % 2;
-  t /= ncomp;
+  const int comp = t & 1;
+  t >>= 1;
   const int pb = t % nbp, r = t / nbp;
-  const int lane = threadIdx.x, h = lane >> 5, g = (lane >> 4) & (G - 1), li = lane & (SW - 1);
-  const int comp = comp0 + g;
-  const int hc = A.npc >> 1, cc = st * SW + li;
-  const bool valid = cc < hc;
-  const int c = (valid ? cc : st * SW) + h * hc;  // idle lanes repeat the strip's first column
+  const int lane = threadIdx.x, i = lane & 15, q = lane >> 4;  // result column and child; k group of the operands
+  const int hc = A.npc >> 1, hp = A.npp >> 1, cc = st * A.scols + i;
+  const bool colok = i < A.scols && cc < hc;
+  const int c0 = colok ? cc : st * A.scols;  // idle lanes repeat the strip's first column
   const int Kc = A.ntc * A.npc, Kp = A.ntp * A.npp;
-  const int wl = A.wlen, nbuf = G * 8 * wl;
-  T w[NT];
+  const int wlo = uni(A.wlo)[st];
+  // the band: lane (column i, group q) holds rows 8 s + 2 q + (0, 1) of it
+  typename MM::vec2 w[KW / 8];
+  {
+    int off = A.colb[c0] - wlo;
+    if (off < 0) off += A.npp;
 #pragma unroll
-  for (int k = 0; k < NT; ++k) w[k] = A.colw[c * NT + k];
-  int off = A.colb[c] - uni(A.wlo)[st * 2 + h];
-  if (off < 0) off += A.npp;
-  const int lofs = (g * 4 * 2 + h) * wl + off;
-  const int PI = pb % A.nxp, PJ = pb / A.nxp;
-  // the four children's patterns at this lane's column, as offsets into
-  // this RHS's child patterns (-1: no child, or an idle lane)
+    for (int s = 0; s < KW / 8; ++s)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int k = 8 * s + 2 * q + e - off;
+        const T v = A.colw[c0 * A.ntap + min(max(k, 0), A.ntap - 1)];
+        w[s][e] = colok && k >= 0 && k < A.ntap ? v : T(0);
+      }
+  }
+  // this lane's column of its child in both strips, as offsets into this RHS's
+  // child patterns (a missing child or column: a valid address, not written)
+  const int PI = pb % A.nxp, PJ = pb / A.nxp, ci = 2 * PI + (q & 1), cj = 2 * PJ + (q >> 1);
+  const bool has = colok && ci < A.nxc && cj < A.nyc;
   C2<T>* __restrict__ dstr = A.dst + (size_t)r * nbc * 2 * Kc;
-  int co[4];
-  unsigned cmask = 0;  // children this lane writes
+  const int co = has ? ((cj * A.nxc + ci) * 2 + comp) * Kc + c0 : 0;
+  // staging: lane -> window column wk of half lh (PK) or of both halves
+  const int wk = PK ? lane & 31 : lane, lh = PK ? lane >> 5 : 0;
+  const bool stage = wk < KW;
+  const C2<T>* __restrict__ gpr = A.src + ((size_t)r * nbp + pb) * 2 * Kp + (size_t)comp * Kp;
+  int scol[NL];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int ci = 2 * PI + (q & 1), cj = 2 * PJ + (q >> 1);
-    const bool has = valid && ci < A.nxc && cj < A.nyc;
-    co[q] = has ? ((cj * A.nxc + ci) * 2 + comp) * Kc + c : 0;
-    if (has) cmask |= 1u << q;
-  }
-  // staging: parent value v of a row (component gg, half hh, window column
-  // k) times the conjugate phases of the four children goes to slots
-  // ((gg * 4 + q) * 2 + hh) * wl + k
-  constexpr int KS = 3 * kIStage / 8;
-  const int nv = G * 2 * wl;
-  const C2<T>* __restrict__ gpr = A.src + ((size_t)r * nbp + pb) * 2 * Kp;
-  // (every lane loads KS values; a value past the windows reads column 0
-  // and goes to spare slots after the buffer, so that no load is
-  // conditional and the next row's loads stay in flight)
-  int scol[KS], sslot[KS], sgo[KS];
-#pragma unroll
-  for (int k = 0; k < KS; ++k) {
-    const int v = lane + 64 * k;
-    scol[k] = 0;
-    sslot[k] = nbuf + lane;
-    sgo[k] = comp0 * Kp;
-    if (v < nv) {
-      const int kk = v % wl, rest = v / wl, hh = rest & 1, gg = rest >> 1;
-      scol[k] = (uni(A.wlo)[st * 2 + hh] + kk) % A.npp;
-      sslot[k] = (gg * 8 + hh) * wl + kk;
-      sgo[k] = (comp0 + gg) * Kp + scol[k];
-    }
-  }
+  for (int u = 0; u < NL; ++u) scol[u] = (wlo + min(wk, KW - 1) + (PK ? lh : u) * hp) % A.npp;
   const int E0 = uni(A.chunk)[ch], E1 = uni(A.chunk)[ch + 1];
   const int pfirst = uni(A.chunk_p)[2 * ch], plast = uni(A.chunk_p)[2 * ch + 1];
   const int half = ORD / 2, nvr = A.ntc + ORD;
-  C2<T> ng[KS], ne1[KS], ne2[KS];
+  C2<T> ng[2][NL];
+  CP<T> ne[2];  // (unpacked: of the first half; the phases half a turn on are the conjugates)
   auto fetch = [&](int p) {
-    const int ro = p * A.npp;
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-      ng[k] = at32(gpr, sgo[k] + ro);
-      const CP<T> e = at32(A.E, ro + scol[k]);
-      ne1[k] = e.a;
-      ne2[k] = e.b;
+    for (int v = 0; v < 2; ++v) {
+      const int ro = min(p + v, plast) * A.npp;
+#pragma unroll
+      for (int u = 0; u < NL; ++u) ng[v][u] = at32(gpr, ro + scol[u]);
+      ne[v] = at32(A.E, ro + scol[0]);
     }
   };
   fetch(pfirst);
-  C2<T> acc[4][ORD];
+  C2<T> acc[2][ORD];
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int a = 0; a < ORD; ++a) acc[q][a] = C2<T>{0, 0};
+    for (int a = 0; a < ORD; ++a) acc[h][a] = C2<T>{0, 0};
   int ew = uni(A.s0)[pfirst];  // extended child row held in acc[.][0]
-  // the oldest held row's translated child values: loaded once per parent
-  // row, every row the same loads (so that the next row's loads, issued
-  // after them, stay in flight while the flush waits for these)
-  C2<T> pend[4];
-  auto load_pend = [&]() {
-    const int o = uni(A.vrow)[min(ew, nvr - 1)] * A.npc;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) pend[q] = at32(dstr, co[q] + o);
+  // the translated child values of the two oldest held rows, loaded once per
+  // pair of parent rows ahead of the next pair's values
+  C2<T> pend[2][2];
+  auto load_pend = [&](int e, C2<T>(&d)[2]) {
+    const int o = uni(A.vrow)[min(e, nvr - 1)] * A.npc;
+    d[0] = at32(dstr, co + o);
+    d[1] = at32(dstr, co + o + hc);
   };
-  load_pend();
-  // adds the oldest held row to its child row (if this chunk owns it) and
-  // shifts the window
-  auto flush = [&]() {
+  // adds the oldest held row to its child row (if this chunk owns it), d its
+  // child values (on return the sums), and shifts the window
+  auto flush = [&](C2<T>(&d)[2]) {
     if (ew >= E0 && ew < E1) {
       const int o = uni(A.vrow)[ew] * A.npc;
 #pragma unroll
-      for (int q = 0; q < 4; ++q)
-        if ((cmask >> q) & 1) at32(dstr, co[q] + o) = C2<T>{pend[q].x + acc[q][0].x, pend[q].y + acc[q][0].y};
+      for (int h = 0; h < 2; ++h) {
+        d[h] = C2<T>{d[h].x + acc[h][0].x, d[h].y + acc[h][0].y};
+        if (has) at32(dstr, co + o + h * hc) = d[h];
+      }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int a = 0; a + 1 < ORD; ++a) acc[q][a] = acc[q][a + 1];
-      acc[q][ORD - 1] = C2<T>{0, 0};
+      for (int a = 0; a + 1 < ORD; ++a) acc[h][a] = acc[h][a + 1];
+      acc[h][ORD - 1] = C2<T>{0, 0};
     }
     ++ew;
   };
-  for (int p = pfirst; p <= plast; ++p) {
-    const int spp = uni(A.s0)[p];
-    if (ew < spp) {
-      flush();
-      while (ew < spp) {  // a second row finished by the same parent row (rare)
-        load_pend();
-        flush();
+  // flushes until row `to` is the oldest; the first two rows' values are in
+  // pend, of which `used` are spent.  Two neighbouring extended rows may be one
+  // child row (the pole between them): the second then adds to the sums.
+  auto advance = [&](int to, int& used) {
+    while (ew < to) {
+      if (used == 0) {
+        flush(pend[0]);
+      } else if (used == 1) {
+        if (uni(A.vrow)[min(ew, nvr - 1)] == uni(A.vrow)[ew - 1] && ew - 1 >= E0) {
+          pend[1][0] = pend[0][0];
+          pend[1][1] = pend[0][1];
+        }
+        flush(pend[1]);
+      } else {
+        C2<T> d[2];
+        load_pend(ew, d);
+        flush(d);
       }
+      ++used;
     }
-    load_pend();
-    C2<T>* buf = lds + (p & 1) * (nbuf + 6 * wl + 64);
+  };
+  for (int p = pfirst; p <= plast; p += 2) {
     // child 0: E1 g, child 1: conj(E2) g, child 2: E2 g, child 3: conj(E1) g
 #pragma unroll
-    for (int k = 0; k < KS; ++k) {
-        C2<T>* d = buf + sslot[k];
-        d[0] = cmul(ne1[k], ng[k]);
-        d[2 * wl] = cmul_conj_a(ne2[k], ng[k]);
-        d[4 * wl] = cmul(ne2[k], ng[k]);
-        d[6 * wl] = cmul_conj_a(ne1[k], ng[k]);
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int u = 0; u < NL; ++u) {
+        const int h = PK ? lh : u;
+        C2<T> e1 = ne[v].a, e2 = ne[v].b;
+        if (!PK && u) e1.y = -e1.y, e2.y = -e2.y;
+        const C2<T> g = ng[v][u];
+        const C2<T> f[4] = {cmul(e1, g), cmul_conj_a(e2, g), cmul(e2, g), cmul_conj_a(e1, g)};
+        if (stage)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            lds[h][MM::row(k, 2 * v)][wk] = f[k].x;
+            lds[h][MM::row(k, 2 * v + 1)][wk] = f[k].y;
+          }
       }
-    fetch(min(p + 1, plast));
+    load_pend(ew, pend[0]);
+    load_pend(ew + 1, pend[1]);
+    fetch(p + 2);
     __syncthreads();
-    C2<T> f[4];
+    typename MM::vec4 f[2];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const C2<T>* __restrict__ lw = buf + lofs + q * 2 * wl;
-      C2<T> v{0, 0};
+    for (int h = 0; h < 2; ++h) {
+      f[h] = typename MM::vec4{0, 0, 0, 0};
 #pragma unroll
-      for (int k = 0; k < NT; ++k) {
-        const C2<T> z = lw[k];
-        v.x = fmadd(w[k], z.x, v.x);
-        v.y = fmadd(w[k], z.y, v.y);
+      for (int s = 0; s < KW / 8; ++s) {
+        const typename MM::vec2 a = *reinterpret_cast<const typename MM::vec2*>(&lds[h][i][8 * s + 2 * q]);
+        f[h] = MM::mul(a[0], w[s][0], f[h]);
+        f[h] = MM::mul(a[1], w[s][1], f[h]);
       }
-      f[q] = v;
     }
-    const auto tw = uni(A.thw) + p * ORD;
-    if (spp < half || spp + ORD > half + A.ntc) {  // a tap on a pole reflection
-      C2<T> gx[4];
+    __syncthreads();
+    int used = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) gx[q] = shfl_x32(f[q]);
+    for (int v = 0; v < 2; ++v) {
+      if (p + v > plast) break;
+      const int spp = uni(A.s0)[p + v];
+      advance(spp, used);
+      const auto tw = uni(A.thw) + (p + v) * ORD;
+      const C2<T> f0{f[0][2 * v], f[0][2 * v + 1]}, f1{f[1][2 * v], f[1][2 * v + 1]};
+      if (spp < half || spp + ORD > half + A.ntc) {  // a tap on a pole reflection
 #pragma unroll
-      for (int a = 0; a < ORD; ++a) {
-        const bool fl = uni(A.vflip)[spp + a] != 0;
+        for (int a = 0; a < ORD; ++a) {
+          const bool fl = uni(A.vflip)[spp + a] != 0;
+          const C2<T> z0 = fl ? f1 : f0, z1 = fl ? f0 : f1;
+          acc[0][a].x = fmadd(tw[a], z0.x, acc[0][a].x);
+          acc[0][a].y = fmadd(tw[a], z0.y, acc[0][a].y);
+          acc[1][a].x = fmadd(tw[a], z1.x, acc[1][a].x);
+          acc[1][a].y = fmadd(tw[a], z1.y, acc[1][a].y);
+        }
+      } else {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const C2<T> z = fl ? gx[q] : f[q];
-          acc[q][a].x = fmadd(tw[a], z.x, acc[q][a].x);
-          acc[q][a].y = fmadd(tw[a], z.y, acc[q][a].y);
+        for (int a = 0; a < ORD; ++a) {
+          acc[0][a].x = fmadd(tw[a], f0.x, acc[0][a].x);
+          acc[0][a].y = fmadd(tw[a], f0.y, acc[0][a].y);
+          acc[1][a].x = fmadd(tw[a], f1.x, acc[1][a].x);
+          acc[1][a].y = fmadd(tw[a], f1.y, acc[1][a].y);
         }
       }
-    } else {
-#pragma unroll
-      for (int a = 0; a < ORD; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          acc[q][a].x = fmadd(tw[a], f[q].x, acc[q][a].x);
-          acc[q][a].y = fmadd(tw[a], f[q].y, acc[q][a].y);
-        }
     }
   }
   const int eend = min(E1, nvr);
   while (ew < eend) {
-    flush();
-    load_pend();
+    load_pend(ew, pend[0]);
+    load_pend(ew + 1, pend[1]);
+    int used = 0;
+    advance(min(ew + 2, eend), used);
   }
 }
 
@@ -2319,8 +2364,9 @@ class EngineT final : public Engine {
   // batch needs fewer chunks to fill the chip.
   struct Itp {
     int order = 0;
-    int a_nst = 0, a_wlen = 0, d_nst = 0, d_wlen = 0, d_ntap = 0;
-    int a_sw = kIStrip, d_sw = kIStrip;         // strip widths (16: two components per wave)
+    int a_nst = 0, a_wlen = 0, d_nst = 0, d_ntap = 0;
+    int a_sw = kIStrip;                         // aggregation strip width (16: two components per wave)
+    int m_cols = 0, m_kw = 0;                   // k_dis_mfma: columns per strip, window columns (a multiple of 8)
     int a_ends = 3;                              // most parent rows ending at one extended child row
     int a_rows = 0, d_rows = 0;                 // rows per chunk set by the tuner (0: planner)
     int a_nch[8] = {}, d_nch[8] = {};           // chunks per batch-size bucket
@@ -2690,11 +2736,24 @@ class EngineT final : public Engine {
     return 0;
   }
 
-  // Streamed interpolation plan of level l (parent) and l - 1 (child):
-  // tables and, for each batch-size bucket, row chunks so that a launch has
-  // about kStreamItems waves.  agg_rows: parent rows per aggregation chunk,
-  // dis_rows: extended child rows per disaggregation chunk (0: planner).
-  // Chunking changes only which wave computes an output, not its arithmetic.
+  // Chunks of a pattern's rows for a launch of `waves` waves or more with
+  // `base` waves per chunk, each chunk at least `least` rows.  A chunk repeats
+  // the `order` - 1 rows of the stencil around it, so that cutting pays only
+  // where a launch waits for its chains of rows, not for the chip: up to about
+  // two waves per SIMD down to a few rows each, and for the longer rows of the
+  // coarse levels (14 rows and more) up to four.  Measured over rows per chunk:
+  // aggregation into the top level of the 40 x 40 array at one RHS 31.7 us with
+  // one chunk, 13.9 with 12 rows, 9.2 with 3; into the second of the 200 x 200
+  // lens 50.6 with one chunk, 56 with two; disaggregation out of the top level
+  // of the 40 x 40 array 70, 25.5 (12 rows), 19.4 (4), 18.9 (2).
+  static int chunks_for(size_t base, size_t waves, int rows, int least) {
+    return std::max(1, (int)std::min<size_t>((waves + base - 1) / base, (size_t)(rows / least)));
+  }
+  // Streamed interpolation plan of level l (parent) and l - 1 (child): tables
+  // and, for each batch-size bucket, row chunks (chunks_for).  agg_rows: parent
+  // rows per aggregation chunk, dis_rows: extended child rows per
+  // disaggregation chunk (0: planner).  Chunking changes only which wave
+  // computes an output, not its arithmetic.
   int plan_level(int l, int agg_rows, int dis_rows, std::string& err) {
     const Lvl &C = lv_[l - 1], &Pp = lv_[l];
     const LevelGrid &gc = tree_->lv[l - 1], &gp = tree_->lv[l];
@@ -2785,9 +2844,7 @@ class EngineT final : public Engine {
       cnt_d[c] = cnt;
       ntap = std::max(ntap, cnt);
     }
-    // (10 taps, the finest levels' count with 6-point stencils, only with those)
-    ntap = ntap <= 8 ? 8 : ntap <= 10 && ORD == 6 ? 10 : ntap <= 12 ? 12 : ntap <= 16 ? 16 : -1;
-    if (ntap < 0) {
+    if (ntap > 16) {
       err = "interpolation: more than 16 transposed phi taps at level " + std::to_string(l);
       return -1;
     }
@@ -2818,12 +2875,39 @@ class EngineT final : public Engine {
     };
     std::vector<int> wlo_a, wlo_d;
     I.a_wlen = windows(Pp.np, C.np, colb_a, ORD, wlo_a, I.a_nst, I.a_sw, true);
-    I.d_wlen = windows(C.np, Pp.np, colb_d, ntap, wlo_d, I.d_nst, I.d_sw, false);
     I.d_ntap = ntap;
-    // staged values per lane and row: the aggregation's four children (4, or
-    // 6 with two components per wave), the disaggregation's parent (3)
-    const int ks_a = I.a_sw == kIStrip ? kIStage / 2 : 3 * kIStage / 4, ks_d = 3 * kIStage / 8;
-    if ((kIStrip / I.a_sw) * 8 * I.a_wlen > 64 * ks_a || (kIStrip / I.d_sw) * 2 * I.d_wlen > 64 * ks_d) {
+    // k_dis_mfma: strips of equal width, at most 16 columns of half a row and
+    // at most 48 window columns; the other half's windows and stencils are
+    // these half a turn on
+    const int hc = C.np / 2, hp = Pp.np / 2;
+    for (int c = 0; c < hc; ++c)
+      if (colb_d[c + hc] != (colb_d[c] + hp) % Pp.np || cnt_d[c + hc] != cnt_d[c]) {
+        err = "interpolation: phi stencils are not periodic over half a turn at level " + std::to_string(l);
+        return -1;
+      }
+    int taps = 0, wl = 0;
+    for (int c = 0; c < hc; ++c) taps = std::max(taps, cnt_d[c]);
+    for (int most = std::min(16, hc);; --most) {
+      I.d_nst = (hc + most - 1) / most;
+      I.m_cols = (hc + I.d_nst - 1) / I.d_nst;
+      wlo_d.assign(I.d_nst, 0);
+      wl = 0;
+      for (int st2 = 0; st2 < I.d_nst; ++st2) {
+        const int c0 = st2 * I.m_cols, c1 = std::min(c0 + I.m_cols, hc) - 1;
+        wlo_d[st2] = colb_d[c0];
+        wl = std::max(wl, (colb_d[c1] - colb_d[c0] + Pp.np) % Pp.np + taps);
+      }
+      if (wl <= 48 || most == 1) break;
+    }
+    I.m_kw = wl <= 24 ? 24 : wl <= 32 ? 32 : wl <= 40 ? 40 : 48;
+    if (wl > I.m_kw) {
+      err = "interpolation: phi windows too wide at level " + std::to_string(l);
+      return -1;
+    }
+    // staged values per lane and row of the aggregation's four children: 4, or
+    // 6 with two components per wave
+    const int ks_a = I.a_sw == kIStrip ? kIStage / 2 : 3 * kIStage / 4;
+    if ((kIStrip / I.a_sw) * 8 * I.a_wlen > 64 * ks_a) {
       err = "interpolation: phi windows too wide at level " + std::to_string(l);
       return -1;
     }
@@ -2837,19 +2921,17 @@ class EngineT final : public Engine {
       // aggregation: chunks of parent rows
       const size_t base_a = Rb * nbp * (I.a_sw == kIStrip ? 2 : 1) * I.a_nst;
       int na = agg_rows > 0 ? (Pp.nt + agg_rows - 1) / agg_rows
-                            : (int)std::min<size_t>((kStreamItems + base_a - 1) / base_a,
-                                                    (size_t)std::max(1, Pp.nt / (2 * ORD)));
+                            : std::max(chunks_for(base_a, 2000, Pp.nt, 3), chunks_for(base_a, 4000, Pp.nt, 14));
       na = std::max(1, std::min(na, Pp.nt));
       I.a_nch[b] = na;
       I.a_coff[b] = (int)ca.size();
       for (int i = 0; i <= na; ++i) ca.push_back((int)((long long)i * Pp.nt / na));
       // disaggregation: chunks of extended child rows; interior cuts in
       // [ORD, nt_c] so that a pole reflection stays with its row
-      const size_t base_d = Rb * nbp * (I.d_sw == kIStrip ? 2 : 1) * I.d_nst;
+      const size_t base_d = Rb * nbp * 2 * I.d_nst;
       const int span = C.nt - ORD;
       int nd = dis_rows > 0 ? (nvr + dis_rows - 1) / dis_rows
-                            : (int)std::min<size_t>((kStreamItems + base_d - 1) / base_d,
-                                                    (size_t)std::max(1, C.nt / (2 * ORD)));
+                            : chunks_for(base_d, sizeof(T) == 4 ? 2500 : 1500, nvr, 4);
       nd = span <= 0 ? 1 : std::max(1, std::min(nd, span + 1));
       I.d_nch[b] = nd;
       I.d_coff[b] = (int)cdv.size();
@@ -3320,26 +3402,18 @@ class EngineT final : public Engine {
     }
   }
 
-  // the disaggregation kernel of a stencil order, tap count and strip width
-  template <int ORD, int NT>
-  void launch_dis_nt(Pending& pr, bool two, dim3 g, uint32_t sh, hipStream_t st, const InterpArgs<T>& A) {
-    if (two)
-      launch(pr, k_dis_stream<T, ORD, NT, 16>, g, dim3(64), sh, st, A);
-    else
-      launch(pr, k_dis_stream<T, ORD, NT, 32>, g, dim3(64), sh, st, A);
+  // the disaggregation kernel of a stencil order and window length
+  template <int ORD>
+  void launch_dis_order(Pending& pr, int kw, dim3 g, hipStream_t st, const InterpArgs<T>& A) {
+    launch(pr, kw == 24   ? k_dis_mfma<T, ORD, 24>
+               : kw == 32 ? k_dis_mfma<T, ORD, 32>
+               : kw == 40 ? k_dis_mfma<T, ORD, 40>
+                          : k_dis_mfma<T, ORD, 48>,
+           g, dim3(64), 0u, st, A);
   }
-  void launch_dis(Pending& pr, int order, int ntap, bool two, dim3 g, uint32_t sh, hipStream_t st,
-                  const InterpArgs<T>& A) {
-    if (order == 6) {
-      if (ntap == 8) launch_dis_nt<6, 8>(pr, two, g, sh, st, A);
-      else if (ntap == 10) launch_dis_nt<6, 10>(pr, two, g, sh, st, A);
-      else if (ntap == 12) launch_dis_nt<6, 12>(pr, two, g, sh, st, A);
-      else launch_dis_nt<6, 16>(pr, two, g, sh, st, A);
-    } else {
-      if (ntap == 8) launch_dis_nt<4, 8>(pr, two, g, sh, st, A);
-      else if (ntap == 12) launch_dis_nt<4, 12>(pr, two, g, sh, st, A);
-      else launch_dis_nt<4, 16>(pr, two, g, sh, st, A);
-    }
+  void launch_dis(Pending& pr, int order, int kw, dim3 g, hipStream_t st, const InterpArgs<T>& A) {
+    if (order == 6) launch_dis_order<6>(pr, kw, g, st, A);
+    else launch_dis_order<4>(pr, kw, g, st, A);
   }
 
   // Arguments of the streamed interpolation between level l - 1 (child) and
@@ -3371,8 +3445,9 @@ class EngineT final : public Engine {
     A.R = R;
     A.nst = agg ? I.a_nst : I.d_nst;
     A.nch = agg ? I.a_nch[bk] : I.d_nch[bk];
-    A.wlen = agg ? I.a_wlen : I.d_wlen;
+    A.wlen = agg ? I.a_wlen : 0;
     A.ntap = agg ? I.order : I.d_ntap;
+    A.scols = I.m_cols;
     return A;
   }
 
@@ -3460,14 +3535,13 @@ class EngineT final : public Engine {
         const Lvl &L = lv_[l], &Pp = lv_[l + 1];
         const Itp& I = it_[l + 1];
         InterpArgs<T> A = interp_args(l + 1, R, bk, false);
-        const int items = R * Pp.nx * Pp.ny * (I.d_sw == kIStrip ? 2 : 1) * I.d_nst * I.d_nch[bk];
+        const int items = R * Pp.nx * Pp.ny * 2 * I.d_nst * I.d_nch[bk];
         // algorithmic bytes: the parent pattern read once (the child's
         // translated pattern is read and written once more by this kernel)
         auto pr = begin("disaggregate_l" + std::to_string(l), cb * 2.0 * R * (double)Pp.nx * Pp.ny * Pp.K,
                         2.0 * R * (double)Pp.nx * Pp.ny * 2 * 4 *
                             (4.0 * (double)Pp.nt * L.np * I.d_ntap + 4.0 * (double)Pp.nt * L.np * I.order));
-        const uint32_t sh = (uint32_t)(2 * ((kIStrip / I.d_sw) * 8 * I.d_wlen + 6 * I.d_wlen + 64) * sizeof(CT));
-        launch_dis(pr, I.order, I.d_ntap, I.d_sw != kIStrip, dim3(xcd_grid(items)), sh, st, A);
+        launch_dis(pr, I.order, I.m_kw, dim3(xcd_grid(items)), st, A);
       }
       // with the receive on k_gemm_lds, the class-pair near sum goes into its store
       if (near && near_grouped) near_sum();
@@ -3672,7 +3746,6 @@ class EngineT final : public Engine {
   int rt_np_ = 4, rt_recv_ = 4;  // MFMA GEMM row tiles (of 16) per block: near+projection, receive
   static constexpr size_t kLdsBudget = 48 * 1024;  // preferred tile size (occupancy)
   static constexpr size_t kLdsMax = 64 * 1024;     // hard limit per block
-  static constexpr size_t kStreamItems = 4096;  // waves per streamed interpolation launch (target)
 
   template <typename U>
   static int put_raw(DevMem& d, const U* h, size_t count, std::string& err) {
