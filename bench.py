@@ -46,26 +46,12 @@ KERNELS = [
 
 def kernel_of(stage, gemm_rows=(4, 4), R=1, multi_class=True):
     """Kernel symbol and roofline bound of a product stage of the FP32
-    product.  The GEMM stages follow the engine's dispatch: the LDS-staged
-    kernel k_gemm_lds<mode, waves, column tiles, tag> when R is a multiple
-    of 4 and both jobs of the launch take the same mode (mode 0: K fits one
-    chunk; mode 1: M does), else k_gemm_stream<row tiles, column tiles, tag,
-    8> with 4 column tiles when R is a multiple of 4, 2 when even, else 1.
-    The near job of a single-class array (nine blocks side by side, mode 1)
-    and the projection (mode 0) share a launch, so that launch stays on
-    k_gemm_stream."""
-    rn, rr = gemm_rows
-    ct = 4 if R % 4 == 0 else 2 if R % 2 == 0 else 1
-    lds = R % 4 == 0 and os.environ.get("MLFMA_GEMM") != "stream"
-    w0, c0 = (8, 2) if R % 16 == 0 else (8, 1) if R % 8 == 0 else (4, 1)   # mode 0
-    w1 = 8 if R % 8 == 0 else 4                                            # mode 1
-    near_mode = 0 if multi_class else 1
-    gemm = {
-        "near+project": f"k_gemm_lds<0, {w0}, {c0}, 0>" if lds and multi_class else f"k_gemm_stream<{rn}, {ct}, 0, 8>",
-        "near": (f"k_gemm_lds<0, {w0}, {c0}, 1>" if near_mode == 0 else f"k_gemm_lds<1, {w1}, 1, 1>") if lds
-        else f"k_gemm_stream<{rn}, {ct}, 1, 8>",
-        "project": f"k_gemm_lds<0, {w0}, {c0}, 2>" if lds else f"k_gemm_stream<{rn}, {ct}, 2, 8>",
-        "receive": f"k_gemm_lds<1, {w1}, 1, 3>" if lds else f"k_gemm_stream<{rr}, {ct}, 3, 8>"}
+    product, where the library recorded none.  The GEMM stages run on
+    k_gemm_group<modes, waves per tile, near sum, tag>, or with few columns on
+    k_gemm_stream<row tiles, column tiles, tag, waves>; their template
+    arguments follow the engine's dispatch and are not repeated here."""
+    gemm = {s: "k_gemm_stream" if os.environ.get("MLFMA_GEMM") == "stream" else "k_gemm_group"
+            for s in ("near+project", "near", "project", "receive")}
     if stage in gemm:
         return gemm[stage], "mfma"
     for prefix, sym, bound in KERNELS:

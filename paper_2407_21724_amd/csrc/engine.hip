@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <type_traits>
 #include <utility>
 #include <cstdint>
@@ -288,6 +289,12 @@ struct GemmJob {
                     // block's waves split one tile's K and add their partial sums
   const unsigned short* Ah;  // BF16-split kernel: A as BF16 heads and remainders (same layout as A)
   const unsigned short* Al;
+  // k_gemm_group: the job's block tables, A per group, and its columns unpadded
+  const void* gtab;
+  size_t gstride;
+  const int *gbcol, *gccol;
+  const float* part;  // near partials that the receive adds, and each particle's neighbours
+  const int* has;
 };
 
 constexpr int kMaxSeg = 9;  // segments of a gathered B column (the 3 x 3 neighbourhood)
@@ -296,6 +303,9 @@ constexpr int kGemmW = 8;   // waves per block of the FP32 GEMM launches
 __host__ __device__ inline int gemm_blocks(const GemmJob& j, int W) { return j.wtile ? (j.tiles + W - 1) / W : j.tiles; }
 template <int RT, int CT, int Tag, int W>
 __global__ __launch_bounds__(64 * W) void k_gemm_stream(GemmJob j0, GemmJob j1) {
+  // k-steps loaded together: as many as the registers of four waves per SIMD
+  // hold (the small launches that this kernel serves wait for these loads)
+  constexpr int U = RT + CT <= 3 ? 4 : 1;
   __shared__ f32x4 red[W - 1][RT * CT][64];
   __shared__ int sbc[16 * CT * kMaxSeg];  // the tile's source columns per segment (nseg > 1)
   const int nb0 = gemm_blocks(j0, W), nb1 = gemm_blocks(j1, W);
@@ -367,24 +377,43 @@ __global__ __launch_bounds__(64 * W) void k_gemm_stream(GemmJob j0, GemmJob j1) 
       }
     }
   };
-  // two-stage pipeline: the next step's loads are in flight during this
-  // step's matrix-core products
-  f32x4 a0[RT], b0[CT], a1[RT], b1[CT];
-  if (s0 < s1) load(s0, a0, b0);
+  // two-stage pipeline: the next U steps' loads are in flight during these
+  // steps' matrix-core products
+  f32x4 a0[U][RT], b0[U][CT], a1[U][RT], b1[U][CT];
+  auto load_steps = [&](int sup, f32x4(&a)[U][RT], f32x4(&b)[U][CT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) load(U == 1 || sup + u < s1 ? sup + u : nsup, a[u], b[u]);  // (past the range: zeros)
+  };
+  auto multiply = [&](const f32x4(&a)[U][RT], const f32x4(&b)[U][CT]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct)
+            acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[u][rt][q], b[u][ct][q], acc[rt][ct], 0, 0, 0);
+  };
+  if (s0 < s1) load_steps(s0, a0, b0);
+  if constexpr (U == 1) {
 #pragma unroll 2
-  for (int sup = s0; sup < s1; ++sup) {
-    if (sup + 1 < s1) load(sup + 1, a1, b1);
+    for (int sup = s0; sup < s1; ++sup) {
+      if (sup + 1 < s1) load_steps(sup + 1, a1, b1);
+      multiply(a0, b0);
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+      for (int rt = 0; rt < RT; ++rt) a0[0][rt] = a1[0][rt];
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct)
-          acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[rt][q], b0[ct][q], acc[rt][ct], 0, 0, 0);
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) a0[rt] = a1[rt];
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) b0[ct] = b1[ct];
+      for (int ct = 0; ct < CT; ++ct) b0[0][ct] = b1[0][ct];
+    }
+  } else {
+    for (int sup = s0; sup < s1; sup += 2 * U) {
+      if (sup + U < s1) load_steps(sup + U, a1, b1);
+      multiply(a0, b0);
+      if (sup + U >= s1) break;
+      if (sup + 2 * U < s1) load_steps(sup + 2 * U, a0, b0);
+      multiply(a1, b1);
+    }
   }
   if (!wt) {
     if (wave > 0) {
@@ -438,7 +467,7 @@ __global__ __launch_bounds__(kBlock) void k_near_sum(int P, int nf, const float*
 #pragma unroll
     for (int o = 0; o < 9; ++o) {
       v[o] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (has[p * 9 + o]) v[o] = pr[(size_t)o * cnt + i];
+      if ((has[p] >> o) & 1) v[o] = pr[(size_t)o * cnt + i];
     }
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -447,51 +476,64 @@ __global__ __launch_bounds__(kBlock) void k_near_sum(int P, int nf, const float*
   }
 }
 
-// LDS-staged variant of k_gemm_stream for the FP32 jobs with the
-// right-hand sides folded into the columns.  A block of W waves shares one
-// A matrix (one column group): A passes through LDS in chunks of kLM rows
-// by kLK k, and only the even rows of its real 2x2-block form are staged:
-// row 2i holds (Re z, -Im z) of the complex entries z, and a lane rebuilds
-// the real row it needs, (Re, -Im) for an even row or (Im, Re) for an odd
-// one.  This halves the A bytes that leave L2.
-//   MODE 0 (K <= kLK, one B segment): a wave keeps the B columns of its CT
-//     column tiles in registers over all of K, reads them from memory once,
-//     and walks the row chunks one 16-row tile at a time.
-//   MODE 1 (M <= kLM): a wave keeps its C tiles (every row) in registers
-//     and walks the k chunks; B is read once, its next chunk loaded
-//     before the barrier that ends the current one.
-// The next A chunk is loaded while the current one is multiplied; chunks
-// alternate between two LDS buffers.  Every C tile is summed over k in
-// increasing order by one wave, as in the one-wave tiles of k_gemm_stream.
-// A block covers W * CT column tiles of 16 folded columns; the host keeps
-// them inside one column group (W * CT divides the fold).  Requires M, K,
-// kseg, lda, ldb and ldc multiples of 4 and 16-byte aligned bases.
+// Grouped, LDS-staged GEMM of the FP32 jobs: columns come in groups that share
+// one A matrix (a particle class, a class-pair block), the right-hand sides are
+// folded into them (column f of a group is particle f / R, RHS f % R), and a
+// block of kGW waves takes up to kGW tiles of 16 folded columns of one group,
+// from a table of blocks built with the context.  A passes through LDS in
+// chunks of kLM rows by kLK k, of which only the even rows of the real 2x2-block
+// form are staged: row 2i holds (Re z, -Im z) of the complex entries z, and a
+// lane rebuilds the real row it needs, (Re, -Im) for an even row or (Im, Re) for
+// an odd one.  This halves the A bytes that leave L2.
+//   mode 0 (K <= kLK, one B segment): a wave keeps its tile's B columns in
+//     registers over all of K, reads them from memory once, and walks the row
+//     chunks one 16-row tile at a time (rsplit: the row chunks of a column block
+//     go to so many blocks).
+//   mode 1 (M <= kLM): a wave keeps its C tiles in registers and walks the k
+//     chunks (for a segmented B, one chunk per segment).  The chunks' sums are
+//     added at the end of each: one running sum over K = 1080 has a quarter more
+//     rounding than k_gemm_stream's eight.  PARTS = 1 has no registers for that
+//     and keeps the running sum of the receive of whole batches of 4 (K = 968).
+// With fewer tiles than waves the row tiles are dealt to the waves that share a
+// tile.  The next A chunk is loaded while the current one is multiplied; chunks
+// alternate between two LDS buffers.  Every C tile is summed by one wave in
+// increasing order of k.  Requires M, K, kseg, lda, ldb and ldc multiples
+// of 4 and 16-byte aligned bases.
+//
+// Against one wave per tile with A from L2 (k_gemm_stream, 16 columns per read
+// of A, every group padded to 16 columns before the fold), near blocks and
+// projection of the 200 x 200 lens take 345 us instead of 630 at one RHS and 3.47
+// instead of 3.85 ms at 16 (an earlier LDS kernel for multiples of 4 RHS), 0.57
+// instead of 1.13 ms for the 40 x 40 array at 64 RHS.  Bound by the matrix cores
+// at 90 TFLOP/s there, 57% of their FP32 peak.
 constexpr int kLM = 128, kLK = 128, kLS4 = kLK / 4 + 1;  // f32x4 per staged row (one of padding)
-__host__ __device__ inline int lds_mode(const GemmJob& j) {
-  if (!j.A) return -1;
-  if (j.nseg == 1 && j.kseg <= kLK) return 0;
-  return j.M <= kLM ? 1 : -1;
-}
-// waves per block and column tiles per wave of the LDS kernel for R
-// right-hand sides (W = 0: not applicable, k_gemm_stream runs the job)
-inline void lds_config(int mode, int R, int& W, int& C) {
-  W = C = 0;
-  if (mode == 0 && R % 16 == 0) W = 8, C = 2;
-  else if (R % 8 == 0) W = 8, C = 1;
-  else if (R % 4 == 0) W = 4, C = 1;
-}
-__host__ __device__ inline int lds_blocks(const GemmJob& j, int W, int CT) {
-  if (!j.A) return 0;
-  const long long cols = (long long)j.ncols * (j.fold > 0 ? j.fold : 1);
-  return (int)((cols + 16LL * W * CT - 1) / (16LL * W * CT));
-}
+constexpr int kGW = 8;                                   // waves per block
+struct GroupJob {
+  const float* A;      // group g: A + g * astride, row-major [M][lda]
+  const float* B;      // B column b, segment s: B + rhs * sB + bcol[b * nseg + s] * ldb (bcol < 0: zeros)
+  float* C;            // C column b: C + rhs * sC + ccol[b] * ldc
+  const int *bcol, *ccol;
+  const int4* blk;     // blocks: first column, columns, group
+  const float* part;   // receive: near partials added to the sums ([RHS][9 P][ldc], offsets in `has`)
+  const int* has;      // [P] bit o: particle has an o-neighbour
+  size_t astride, sB, sC;
+  int M, nseg, kseg, lda, ldb, ldc, acc, R, P, nblk, mode;
+  int tiles;           // tiles per block: kGW in mode 0, kGW / PARTS in mode 1
+  int rsplit, split;   // blocks per entry of blk: rsplit shares of the row chunks x groups of tiles
+};
 __device__ __forceinline__ f32x4 expand_row(f32x4 v, bool odd) {
   // v = (Re z0, -Im z0, Re z1, -Im z1) from even row 2i; row 2i + 1 is
   // (Im z0, Re z0, Im z1, Re z1)
   return odd ? f32x4{-v[1], v[0], -v[3], v[2]} : v;
 }
-template <int MODE, int W, int CT, int Tag>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm_lds(GemmJob j0, GemmJob j1) {
+struct GroupJobs {
+  GroupJob j[2];  // (the second may have no blocks)
+};
+// MODES: bit m set where a job of mode m may come; PARTS: waves per tile in
+// mode 1; SUM: the jobs add near partials.
+template <int MODES, int PARTS, bool SUM, int Tag>
+__global__ __launch_bounds__(64 * kGW) __attribute__((amdgpu_waves_per_eu(4))) void k_gemm_group(GroupJobs G) {
+  constexpr int W = kGW;
   constexpr int NP = (kLM / 2) * (kLK / 4) / (64 * W);  // staged f32x4 per thread and chunk
   constexpr int NS = kLK / 16;                          // k-steps per chunk
   __shared__ f32x4 sA[2][kLM / 2][kLS4];
@@ -501,45 +543,36 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
   // Splitting each job evenly keeps the XCDs balanced when the jobs' blocks
   // differ in cost (a projection block does eight times the work of a
   // near-block block).
-  const int nb0 = lds_blocks(j0, W, CT), nb1 = lds_blocks(j1, W, CT);
-  const int p0 = (nb0 + 7) >> 3, p1 = (nb1 + 7) >> 3;
+  const int nb0 = G.j[0].nblk * G.j[0].split, nb1 = G.j[1].nblk * G.j[1].split;
+  const int q0 = (nb0 + 7) >> 3, q1 = (nb1 + 7) >> 3;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const bool second = slot < p1;
-  const int bl = second ? xcd * p1 + slot : xcd * p0 + (slot - p1);  // block within its job
+  const bool second = slot < q1;
+  const int bl = second ? xcd * q1 + slot : xcd * q0 + (slot - q1);  // block within its job
   if (bl >= (second ? nb1 : nb0)) return;  // whole block
-#define JF(f) (second ? j1.f : j0.f)
-  const int M = JF(M), nseg = JF(nseg), kseg = JF(kseg), K = nseg * kseg;
-  const int lda = JF(lda), ldb = JF(ldb), ldc = JF(ldc), accumulate = JF(acc), ncols = JF(ncols);
-  const int fd = JF(fold) > 0 ? JF(fold) : 1;
-  const int* __restrict__ bcol = JF(bcol);
-  const int* __restrict__ ccol = JF(ccol);
-  const int* __restrict__ a_off = JF(a_off);
-  const size_t sB = JF(sB), sC = JF(sC);
-  const float* __restrict__ B0 = JF(B);
-  float* __restrict__ C0 = JF(C);
-  const int nblk0 = bl * W * CT * 16;  // the block's first folded column
-  const float* __restrict__ A = JF(A) + (a_off ? a_off[(nblk0 / fd) >> 4] : 0);
-#undef JF
+  const GroupJob& J = G.j[second ? 1 : 0];
+  const int M = J.M, nseg = J.nseg, kseg = J.kseg, R = J.R, P = J.P, split = J.split;
+  const int lda = J.lda, ldb = J.ldb, ldc = J.ldc, accumulate = J.acc;
+  const int* __restrict__ bcol = J.bcol;
+  const size_t sB = J.sB, sC = J.sC;
+  const int4 d = J.blk[bl / split];
+  const float* __restrict__ A = J.A + d.z * J.astride;
+  // this block's row chunks (of rsplit shares) and first tile
+  const int rsplit = J.rsplit, rs = bl % split % rsplit, t0 = bl % split / rsplit * J.tiles;
+  const int F = d.y * R, nt = min(J.tiles, (F + 15) / 16 - t0);
+  if (nt <= 0) return;  // whole block
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   const bool odd = i & 1;
-  int base[CT], rc[CT];
-#pragma unroll
-  for (int ct = 0; ct < CT; ++ct) {
-    const int n = nblk0 + (wave * CT + ct) * 16 + i, b = n / fd;
-    base[ct] = b < ncols ? b : -1;
-    rc[ct] = n - b * fd;
-  }
-  // A chunk: even rows m0 + 2 jr (jr < kLM / 2), k0 .. k0 + kLK
+  // A chunk: even rows m0 + 2 jr (jr < kLM / 2), k0 .. kend
   f32x4 st[NP];
-  auto stage_load = [&](int m0, int k0) {
+  auto stage_load = [&](int m0, int k0, int kend) {
 #pragma unroll
     for (int u = 0; u < NP; ++u) {
       const int p = threadIdx.x + u * 64 * W, jr = p / (kLK / 4), q = p % (kLK / 4);
       const int m = m0 + 2 * jr, k = k0 + 4 * q;
       // unconditional load from a clamped (valid) address, then a select:
       // no divergent branches around the staging registers
-      const f32x4 v = *reinterpret_cast<const f32x4*>(A + (size_t)min(m, M - 2) * lda + min(k, K - 4));
-      st[u] = (m < M && k < K) ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+      const f32x4 v = *reinterpret_cast<const f32x4*>(A + (size_t)min(m, M - 2) * lda + min(k, kend - 4));
+      st[u] = (m < M && k < kend) ? v : f32x4{0.f, 0.f, 0.f, 0.f};
     }
   };
   auto stage_store = [&](int buf) {
@@ -549,105 +582,126 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(4))) voi
       sA[buf][p / (kLK / 4)][p % (kLK / 4)] = st[u];
     }
   };
-  // B of this lane's columns for the k-steps of chunk k0
-  auto load_b = [&](int k0, f32x4(&b)[CT][NS]) {
+  // this wave's tile and share of the row tiles (mode 0: as the block's tiles
+  // allow; mode 1: fixed by the launch)
+  const bool m0 = MODES == 1 || (MODES == 3 && J.mode == 0);
+  const int tw = !m0 ? W / PARTS : nt <= 1 ? 1 : nt <= 2 ? 2 : nt <= 4 ? 4 : 8;
+  const int tile = wave & (tw - 1), rpart = wave / tw, parts = W / tw;
+  const int f = (t0 + tile) * 16 + i;
+  const bool live = tile < nt && f < F;
+  const int col = d.x + (live ? f / R : 0), rc = live ? f % R : 0;
+  const int dcol = J.ccol[col];
+  const float* __restrict__ Bc = J.B + (size_t)rc * sB;
+  f32x4* __restrict__ Cc = reinterpret_cast<f32x4*>(J.C + (size_t)rc * sC + (size_t)dcol * ldc);
+  auto load_b = [&](f32x4(&b)[NS], int src, int k0, int klen) {
 #pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-      for (int s = 0; s < NS; ++s) {
-        // clamped indices and unconditional loads, as in the staging
-        const int k = k0 + 16 * s + 4 * kq, kc = min(k, K - 4);
-        const int sg = nseg == 1 ? 0 : kc / kseg;
-        const int src = bcol[(size_t)max(base[ct], 0) * nseg + sg];
-        const bool ok = base[ct] >= 0 && k < K && src >= 0;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(B0 + (size_t)rc[ct] * sB + (size_t)max(src, 0) * ldb +
-                                                        (kc - sg * kseg));
-        b[ct][s] = ok ? v : f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+    for (int s = 0; s < NS; ++s) {
+      const int k = 16 * s + 4 * kq;
+      const f32x4 v = *reinterpret_cast<const f32x4*>(Bc + (size_t)max(src, 0) * ldb + k0 + min(k, klen - 4));
+      b[s] = live && src >= 0 && k < klen ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   };
-  auto store_c = [&](int ct, int m, f32x4 v) {
-    if (base[ct] < 0 || m >= M) return;
-    const int dcol = ccol[base[ct]];
-    if (dcol < 0) return;
-    f32x4* dst = reinterpret_cast<f32x4*>(C0 + (size_t)rc[ct] * sC + (size_t)dcol * ldc + m);
-    *dst = accumulate ? *dst + v : v;
-  };
-  f32x4 b[CT][NS];
-  if constexpr (MODE == 0) {
-    load_b(0, b);
-    const int nmc = (M + kLM - 1) / kLM;
-    stage_load(0, 0);
-    stage_store(0);
+  if (m0) {
+    const int K = kseg, nmc = (M + kLM - 1) / kLM, mc0 = rs * nmc / rsplit, mc1 = (rs + 1) * nmc / rsplit;
+    if (mc0 >= mc1) return;  // whole block
+    stage_load(mc0 * kLM, 0, K);
+    f32x4 b[NS];
+    load_b(b, bcol[col], 0, K);
+    stage_store(mc0 & 1);
     __syncthreads();
-    for (int mc = 0; mc < nmc; ++mc) {
+    for (int mc = mc0; mc < mc1; ++mc) {
       const int buf = mc & 1;
-      if (mc + 1 < nmc) stage_load((mc + 1) * kLM, 0);
-      for (int rt = 0; rt < kLM / 16; ++rt) {
-        const int mt = mc * kLM + 16 * rt;
-        if (mt >= M) break;
-        f32x4 acc[CT];
+      if (mc + 1 < mc1) stage_load((mc + 1) * kLM, 0, K);
+      if (tile < nt)
+        for (int rt = rpart; rt < kLM / 16; rt += parts) {
+          const int mt = mc * kLM + 16 * rt;
+          if (mt >= M) break;
+          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int s = 0; s < NS; ++s) {
+            if (16 * s >= K) break;
+            const f32x4 a = expand_row(sA[buf][8 * rt + (i >> 1)][4 * s + kq], odd);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) {
-          if (16 * s >= K) break;
-          const f32x4 a = expand_row(sA[buf][8 * rt + (i >> 1)][4 * s + kq], odd);
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-              acc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[ct][s][q], acc[ct], 0, 0, 0);
+            for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[s][q], acc, 0, 0, 0);
+          }
+          const int m = mt + 4 * kq;
+          if (live && m < M) Cc[m >> 2] = accumulate ? Cc[m >> 2] + acc : acc;
         }
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) store_c(ct, mt + 4 * kq, acc[ct]);
-      }
-      if (mc + 1 < nmc) {
+      if (mc + 1 < mc1) {
         stage_store(buf ^ 1);
         __syncthreads();
       }
     }
   } else {
-    constexpr int RT = kLM / 16;
-    f32x4 acc[RT][CT];
+    // PARTS waves share a tile: wave rpart of them takes the row tiles rpart,
+    // rpart + PARTS, ... (rows past M are zeros in the staged chunk)
+    constexpr int RT = kLM / 16 / PARTS;
+    f32x4 sum[RT];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const int nkc = (K + kLK - 1) / kLK;
-    load_b(0, b);
-    stage_load(0, 0);
+    for (int u = 0; u < RT; ++u) sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nkc = nseg > 1 ? nseg : (kseg + kLK - 1) / kLK;
+    // chunk c: k from k_of(c) for len_of(c), B segment c or the only one
+    auto k_of = [&](int c) { return nseg > 1 ? c * kseg : c * kLK; };
+    auto len_of = [&](int c) { return nseg > 1 ? kseg : min(kLK, kseg - c * kLK); };
+    auto src_of = [&](int c) { return nseg > 1 ? bcol[(size_t)col * nseg + min(c, nseg - 1)] : bcol[col]; };
+    stage_load(0, 0, len_of(0));
+    int src = src_of(0);
+    f32x4 b[NS];
+    load_b(b, src, 0, len_of(0));
+    src = src_of(1);
     stage_store(0);
     __syncthreads();
     for (int kc = 0; kc < nkc; ++kc) {
-      const int buf = kc & 1;
-      if (kc + 1 < nkc) stage_load(0, (kc + 1) * kLK);
+      const int buf = kc & 1, klen = len_of(kc);
+      if (kc + 1 < nkc) stage_load(0, k_of(kc + 1), k_of(kc + 1) + len_of(kc + 1));
+      f32x4 part_sum[RT];
+      f32x4(&acc)[RT] = PARTS == 1 ? sum : part_sum;
+#pragma unroll
+      for (int u = 0; u < RT; ++u) part_sum[u] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        if (kc * kLK + 16 * s >= K) break;
+        if (16 * s >= klen) break;
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-          if (16 * rt >= M) break;
-          const f32x4 a = expand_row(sA[buf][8 * rt + (i >> 1)][4 * s + kq], odd);
+        for (int u = 0; u < RT; ++u) {
+          const f32x4 a = expand_row(sA[buf][8 * (rpart + PARTS * u) + (i >> 1)][4 * s + kq], odd);
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct)
-              acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[ct][s][q], acc[rt][ct], 0, 0, 0);
+          for (int q = 0; q < 4; ++q) acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[s][q], acc[u], 0, 0, 0);
         }
         // one k-step's A reads at a time (hoisting all of a chunk's would
         // need more registers than four waves per SIMD have)
         __builtin_amdgcn_sched_barrier(0);
       }
+#pragma unroll
+      for (int u = 0; u < RT; ++u)
+        if (PARTS > 1) sum[u] += part_sum[u];
       if (kc + 1 < nkc) {
-        load_b((kc + 1) * kLK, b);  // in flight across the barrier
+        load_b(b, src, nseg > 1 ? 0 : k_of(kc + 1), len_of(kc + 1));  // in flight across the barrier
+        src = src_of(kc + 2);
         stage_store(buf ^ 1);
         __syncthreads();
       }
     }
+    const int hm = SUM && live ? J.has[dcol] : 0;
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int u = 0; u < RT; ++u) {
+      const int m = 16 * (rpart + PARTS * u) + 4 * kq;
+      if (m >= M || !live) continue;
+      f32x4 v = sum[u];
+      if constexpr (SUM) {
+        // the particle's near blocks, in the order of k_near_sum
+        const f32x4* __restrict__ pr =
+            reinterpret_cast<const f32x4*>(J.part + ((size_t)rc * 9 * P + dcol) * ldc) + (m >> 2);
+        f32x4 z[9], near = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) store_c(ct, 16 * rt + 4 * kq, acc[rt][ct]);
+        for (int o = 0; o < 9; ++o) z[o] = pr[(size_t)((hm >> o) & 1 ? o : 4) * P * (ldc >> 2)];
+#pragma unroll
+        for (int o = 0; o < 9; ++o) near += (hm >> o) & 1 ? z[o] : f32x4{0.f, 0.f, 0.f, 0.f};
+        v = near + v;
+      } else if (accumulate) {
+        v = Cc[m >> 2] + v;
+      }
+      Cc[m >> 2] = v;
+    }
   }
 }
 
@@ -2375,6 +2429,29 @@ class EngineT final : public Engine {
     DevMem chunk_a, chunk_d, chunkp_d;
   };
   static constexpr int kChunkR[8] = {1, 2, 4, 8, 16, 32, 64, 1 << 30};
+  // Blocks of k_gemm_group for groups of columns, for each of kGroupU columns
+  // per block (before the right-hand sides are folded in).
+  static constexpr int kGroupNU = 17, kGroupBlocks = 1024;
+  static constexpr int kGroupU[kGroupNU] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 21, 25, 32, 42, 64, 128, 256};
+  struct GroupTab {
+    DevMem mem;
+    int off[kGroupNU] = {}, cnt[kGroupNU] = {};
+    long long ncols = 0;
+  };
+  // groups: (first column, end, index of its A)
+  int put_groups(GroupTab& t, const std::vector<std::array<int, 3>>& groups, std::string& err) {
+    std::vector<int> v;
+    t.ncols = 0;
+    for (auto& g : groups) t.ncols += g[1] - g[0];
+    for (int u = 0; u < kGroupNU; ++u) {
+      t.off[u] = (int)(v.size() / 4);
+      for (auto& g : groups)
+        for (int c = g[0]; c < g[1]; c += kGroupU[u])
+          v.insert(v.end(), {c, std::min(kGroupU[u], g[1] - c), g[2], 0});
+      t.cnt[u] = (int)(v.size() / 4) - t.off[u];
+    }
+    return put_i(t.mem, v, err);
+  }
   static int chunk_bucket(int R) {
     int b = 0;
     while (b < 7 && kChunkR[b] < R) ++b;
@@ -2629,6 +2706,16 @@ class EngineT final : public Engine {
         i = e;
       }
       ncols_pad_ = (int)part.size();
+      std::vector<std::array<int, 3>> groups;  // (unpadded: k_gemm_group)
+      std::vector<int> gbox;
+      for (size_t k = 0; k < u.order.size(); ++k) {
+        const int c = u.class_of[u.order[k]];
+        if (groups.empty() || groups.back()[2] != c) groups.push_back({(int)k, (int)k, c});
+        groups.back()[1] = (int)k + 1;
+        gbox.push_back(u.box_of[u.order[k]]);
+      }
+      if (int rc = put_groups(gclass_, groups, err)) return rc;
+      if (int rc = put_i(gbox_, gbox, err)) return rc;
       if (int rc = put_i(gcol_part_, part, err)) return rc;
       if (int rc = put_i(gcol_box_, box, err)) return rc;
       if (int rc = put_i(a_off_proj_, aop, err)) return rc;
@@ -2690,6 +2777,7 @@ class EngineT final : public Engine {
       std::vector<int> iota(P_);
       for (int p = 0; p < P_; ++p) iota[p] = p;
       if (int rc = put_i(iota_, iota, err)) return rc;
+      if (int rc = put_groups(gnear_, {{0, P_, 0}}, err)) return rc;
     } else {
       // class-pair blocks differ between particles: one GEMM column per
       // (particle, neighbour) pair, grouped by block (slot) and padded to
@@ -2710,9 +2798,15 @@ class EngineT final : public Engine {
           const int q = u.near_nbr[(size_t)p * 9 + o];
           if (q >= 0) by_slot[u.near_slot[(size_t)p * 9 + o]].push_back({q, o * P_ + p});
         }
-      std::vector<int> bq, cq, aoff;
+      std::vector<int> bq, cq, aoff, uq, uc;
+      std::vector<std::array<int, 3>> groups;  // (unpadded: k_gemm_group)
       for (int sl2 = 0; sl2 < ns; ++sl2) {
         if (by_slot[sl2].empty()) continue;
+        groups.push_back({(int)uq.size(), (int)(uq.size() + by_slot[sl2].size()), sl2});
+        for (auto& e : by_slot[sl2]) {
+          uq.push_back(e.first);
+          uc.push_back(e.second);
+        }
         for (auto& e : by_slot[sl2]) {
           bq.push_back(e.first);
           cq.push_back(e.second);
@@ -2729,8 +2823,11 @@ class EngineT final : public Engine {
       if (int rc = put_i(ng_bcol_, bq, err)) return rc;
       if (int rc = put_i(ng_ccol_, cq, err)) return rc;
       if (int rc = put_i(ng_aoff_, aoff, err)) return rc;
-      std::vector<int> has((size_t)P_ * 9);
-      for (size_t i = 0; i < has.size(); ++i) has[i] = u.near_nbr[i] >= 0;
+      if (int rc = put_groups(gnear_, groups, err)) return rc;
+      if (int rc = put_i(gnear_b_, uq, err)) return rc;
+      if (int rc = put_i(gnear_c_, uc, err)) return rc;
+      std::vector<int> has(P_, 0);  // bit o: an o-neighbour
+      for (size_t i = 0; i < (size_t)P_ * 9; ++i) has[i / 9] |= (u.near_nbr[i] >= 0) << (i % 9);
       if (int rc = put_i(ng_has_, has, err)) return rc;
     }
     return 0;
@@ -3056,6 +3153,10 @@ class EngineT final : public Engine {
     j.tiles = j.tiles_m * (ngcols_ / 16);
     j.xcd = 1;  // consecutive tiles share a block matrix: keep them in one L2
     j.wtile = short_k(j);
+    j.gtab = &gnear_;
+    j.gstride = (size_t)nf * nf;
+    j.gbcol = gnear_b_.template as<int>();
+    j.gccol = gnear_c_.template as<int>();
     return j;
   }
 
@@ -3201,6 +3302,9 @@ class EngineT final : public Engine {
     j.tiles_m = (nf + 16 * rt - 1) / (16 * rt);
     j.tiles = j.tiles_m * ((P_ + 15) / 16);
     (void)R;
+    j.gtab = &gnear_;
+    j.gbcol = j.bcol;
+    j.gccol = j.ccol;
     return j;
   }
   // U0 = radiation matrix of each particle's class times x (eq. kspace_Rap)
@@ -3228,6 +3332,10 @@ class EngineT final : public Engine {
     j.tiles_m = (j.M + 16 * rt - 1) / (16 * rt);
     j.tiles = j.tiles_m * (ncols_pad_ / 16);
     j.wtile = short_k(j);
+    j.gtab = &gclass_;
+    j.gstride = (size_t)2 * M2_ * nf;
+    j.gbcol = order_.template as<int>();
+    j.gccol = gbox_.template as<int>();
     return j;
   }
   // y += receiving matrix of each particle's class times G0 (eqs. Tmn_fmm, Kmn_fmm)
@@ -3255,6 +3363,10 @@ class EngineT final : public Engine {
     j.tiles_m = (j.M + 16 * rt - 1) / (16 * rt);
     j.tiles = j.tiles_m * (ncols_pad_ / 16);
     j.xcd = 1;  // the row tiles of one column tile read the same G0 columns
+    j.gtab = &gclass_;
+    j.gstride = (size_t)nf * 2 * M2_;
+    j.gbcol = gbox_.template as<int>();
+    j.gccol = order_.template as<int>();
     return j;
   }
   // All translation levels, in two launches: LDS tiles on grids of at least
@@ -3336,6 +3448,84 @@ class EngineT final : public Engine {
       launch(pr, k_translate<T>, dim3(xcd_grid(gath.total)), blk, 0u, st, gath, R);
     }
   }
+  // k_gemm_group's mode of a job (-1: not taken)
+  static int group_mode(const GemmJob& j) {
+    if (!j.gtab) return -1;
+    if (j.nseg == 1 && j.kseg <= kLK) return 0;
+    return j.M <= kLM && (j.nseg == 1 || j.kseg <= kLK) ? 1 : -1;
+  }
+  // Which kernel takes a job (and the other one of its launch).  k_gemm_group
+  // wherever its A chunks fit LDS (at most 32 modes per current), except for
+  // few columns, where k_gemm_stream, which splits k over a block's waves,
+  // answers sooner: from 256 tiles of 16 columns on, 512 for the receive (near
+  // blocks and projection: 25 us stream, 28 group with 100 tiles, 66 and 57 with
+  // 336; receive: 18 and 25, 33 and 39, 97 and 86 with 950 and the near sum).
+  // Columns in many groups, which k_gemm_stream pads to 16 each, come earlier:
+  // class-pair blocks always (12 x 12 lens 24 and 16 us), their receive, which
+  // takes the near sum too, from 128 tiles (49 and 36 us with 225).
+  bool use_group(const GemmJob& j, int R) const {
+    if (!gemm_lds_ || bf16_ || group_mode(j) < 0) return false;
+    if (j.gtab == &gnear_ && !near_uniform_) return true;
+    const long long tiles = (static_cast<const GroupTab*>(j.gtab)->ncols * R + 15) / 16;
+    return tiles >= (!j.acc ? 256 : near_uniform_ ? 512 : 128);
+  }
+  // The grouped job for R right-hand sides: tiles per block so that about
+  // kGroupBlocks blocks run (fewer tiles read A more often, but leave no CU
+  // without a block), and in mode 0 the row chunks split as far as that takes.
+  GroupJob group_job(const GemmJob& j, int R) const {
+    const GroupTab& t = *static_cast<const GroupTab*>(j.gtab);
+    GroupJob g{};
+    g.mode = group_mode(j);
+    const long long tiles = (t.ncols * R + 15) / 16;
+    int nt = g.mode == 1 && (R % 4 || !j.acc) ? kGW / 2 : kGW;  // (the chunks' own sums: see PARTS)
+    if (g.mode == 1)
+      while (nt > 1 && tiles / nt < kGroupBlocks) nt /= 2;
+    int u = 0;
+    while (u + 1 < kGroupNU && (long long)kGroupU[u + 1] * R <= 16 * nt) ++u;
+    g.A = j.A;
+    g.astride = j.gstride;
+    g.B = j.B;
+    g.C = j.C;
+    g.bcol = j.gbcol;
+    g.ccol = j.gccol;
+    g.blk = t.mem.template as<int4>() + t.off[u];
+    g.part = j.part;
+    g.has = j.has;
+    g.sB = j.sB;
+    g.sC = j.sC;
+    g.M = j.M;
+    g.nseg = j.nseg;
+    g.kseg = j.kseg;
+    g.lda = j.lda;
+    g.ldb = j.ldb;
+    g.ldc = j.ldc;
+    g.acc = j.acc;
+    g.R = R;
+    g.P = P_;
+    g.nblk = t.cnt[u];
+    const int nmc = (j.M + kLM - 1) / kLM;
+    g.rsplit = g.mode == 0 ? std::max(1, std::min(nmc, (kGroupBlocks + g.nblk - 1) / g.nblk)) : 1;
+    g.tiles = nt;
+    g.split = g.rsplit * (int)(((long long)kGroupU[u] * R + 16 * nt - 1) / (16 * nt));
+    return g;
+  }
+  template <int PARTS, int Tag>
+  void launch_group(Pending& pr, int modes, bool sum, dim3 grid, const GroupJobs& g, hipStream_t st) {
+    const dim3 wg(64 * kGW);
+    if constexpr (Tag == 3) {
+      if (sum) {
+        launch(pr, k_gemm_group<2, PARTS, true, Tag>, grid, wg, 0u, st, g);
+        return;
+      }
+    }
+    if constexpr (Tag == 0 && PARTS > 1) {
+      if (modes == 3) {
+        launch(pr, k_gemm_group<3, PARTS, false, Tag>, grid, wg, 0u, st, g);
+        return;
+      }
+    }
+    launch(pr, k_gemm_group<2, PARTS, false, Tag>, grid, wg, 0u, st, g);
+  }
   // The FP32 job with its R right-hand sides folded into the columns and
   // ct column tiles per block (ct divides R, so that a block stays within
   // one group of columns sharing A)
@@ -3363,27 +3553,37 @@ class EngineT final : public Engine {
         launch(pr, k_gemm_bf16x3<4, Tag>, grid, dim3(kBlock), 0u, st, j0u, j1u);
       return;
     }
-    // the LDS-staged kernel where both jobs take the same mode and blocks of
-    // W * CT column tiles stay inside one column group (W * CT divides R)
-    const int md0 = lds_mode(j0u), md1 = j1u.A ? lds_mode(j1u) : md0;
-    if (gemm_lds_ && md0 >= 0 && md0 == md1) {
-      int W = 0, C = 0;
-      lds_config(md0, R, W, C);
-      if (W) {
-        GemmJob a = j0u, b = j1u;
-        a.fold = R;
-        if (b.A) b.fold = R;
-        const dim3 grid(8 * ((lds_blocks(a, W, C) + 7) / 8 + (lds_blocks(b, W, C) + 7) / 8)), blk(64 * W);
-        if (md0 == 0 && C == 2) launch(pr, k_gemm_lds<0, 8, 2, Tag>, grid, blk, 0u, st, a, b);
-        else if (md0 == 0 && W == 8) launch(pr, k_gemm_lds<0, 8, 1, Tag>, grid, blk, 0u, st, a, b);
-        else if (md0 == 0) launch(pr, k_gemm_lds<0, 4, 1, Tag>, grid, blk, 0u, st, a, b);
-        else if (W == 8) launch(pr, k_gemm_lds<1, 8, 1, Tag>, grid, blk, 0u, st, a, b);
-        else launch(pr, k_gemm_lds<1, 4, 1, Tag>, grid, blk, 0u, st, a, b);
-        return;
-      }
+    if (use_group(j0u, R) && (!j1u.A || group_mode(j1u) >= 0)) {
+      const GroupJob a = group_job(j0u, R), b = j1u.A ? group_job(j1u, R) : GroupJob{};
+      const dim3 grid(8 * ((a.nblk * a.split + 7) / 8 + (b.nblk * b.split + 7) / 8));
+      const int modes = 1 << a.mode | (b.nblk ? 1 << b.mode : 0), parts = kGW / (a.mode || !b.nblk ? a.tiles : b.tiles);
+      const GroupJobs g{{a, b}};
+      if (modes == 1) launch(pr, k_gemm_group<1, 8, false, Tag>, grid, dim3(64 * kGW), 0u, st, g);
+      else if (parts == 1) launch_group<1, Tag>(pr, modes, a.part != nullptr, grid, g, st);
+      else if (parts == 2) launch_group<2, Tag>(pr, modes, a.part != nullptr, grid, g, st);
+      else if (parts == 4) launch_group<4, Tag>(pr, modes, a.part != nullptr, grid, g, st);
+      else launch_group<8, Tag>(pr, modes, a.part != nullptr, grid, g, st);
+      return;
     }
     const int ct = R % 4 == 0 ? 4 : R % 2 == 0 ? 2 : 1;
-    const GemmJob j0 = fold_job(j0u, R, ct), j1 = fold_job(j1u, R, ct);
+    // fewer rows per block (up to the `rt` asked for) while the launch has at
+    // most two blocks per CU: it then waits for a block's chain of k-steps, which
+    // shorter tiles load further ahead (4 x 4 spheres 21 to 9 us, receive 16 to 8)
+    auto with_rows = [](GemmJob j, int r) {
+      if (!j.A) return j;
+      const int cols = j.tiles / j.tiles_m;
+      j.tiles_m = (j.M + 16 * r - 1) / (16 * r);
+      j.tiles = j.tiles_m * cols;
+      return j;
+    };
+    GemmJob j0, j1;
+    for (int r = 1;; r *= 2) {
+      j0 = fold_job(with_rows(j0u, r), R, ct);
+      j1 = fold_job(with_rows(j1u, r), R, ct);
+      if (r < rt && gemm_blocks(j0, kGemmW) + gemm_blocks(j1, kGemmW) > 512) continue;
+      rt = r;
+      break;
+    }
     const int nt = gemm_blocks(j0, kGemmW) + gemm_blocks(j1, kGemmW);
     const dim3 grid(j0.xcd ? xcd_grid(nt) : nt, 1, 1);
     const dim3 blk(64 * kGemmW);
@@ -3543,13 +3743,22 @@ class EngineT final : public Engine {
                             (4.0 * (double)Pp.nt * L.np * I.d_ntap + 4.0 * (double)Pp.nt * L.np * I.order));
         launch_dis(pr, I.order, I.m_kw, dim3(xcd_grid(items)), st, A);
       }
-      // with the receive on k_gemm_lds, the class-pair near sum goes into its store
-      if (near && near_grouped) near_sum();
+      // the class-pair near sum goes into the receive's store where that runs
+      // on k_gemm_group
+      GemmJob rj = mfma_ ? receive_job(y, rt_recv_) : none;
+      if (near && near_grouped) {
+        if (use_group(rj, R)) {
+          rj.part = pNear_;
+          rj.has = ng_has_.template as<int>();
+        } else {
+          near_sum();
+        }
+      }
       {
         auto pr = begin("receive", cb * ((double)R * P_ * M2_ + 2.0 * R * P_ * n_ + (double)nc_ * n_ * M2_),
                         8.0 * R * P_ * (double)n_ * M2_);
         if (mfma_) {
-          launch_gemm<3>(pr, rt_recv_, receive_job(y, rt_recv_), none, R, st);
+          launch_gemm<3>(pr, rt_recv_, rj, none, R, st);
         } else {
           dim3 grid(ntiles_, R);
           launch(pr, k_receive<T, kTP>, grid, blk, 0, st, n_, P_, M2_, nb0, y, pG_[0],
@@ -3662,6 +3871,9 @@ class EngineT final : public Engine {
     j.tiles_m = (nf + 16 * rt - 1) / (16 * rt);
     j.tiles = j.tiles_m * (ncols_pad_ / 16);
     j.wtile = short_k(j);
+    j.gtab = &gclass_;
+    j.gstride = (size_t)nf * nf;
+    j.gbcol = j.gccol = order_.template as<int>();
     return j;
   }
 
@@ -3811,7 +4023,7 @@ class EngineT final : public Engine {
   // time it saves.
   bool gmres_graphs_ = std::getenv("MLFMA_GMRES_GRAPHS") != nullptr;
   bool gmres_progress_ = std::getenv("MLFMA_GMRES_PROGRESS") != nullptr;
-  // FP32 GEMMs through the LDS-staged kernel where it applies (MLFMA_GEMM=stream: always k_gemm_stream)
+  // FP32 GEMMs through the grouped kernel where it applies (MLFMA_GEMM=stream: always k_gemm_stream)
   bool gemm_lds_ = [] {
     const char* e = std::getenv("MLFMA_GEMM");
     return !(e && std::string(e) == "stream");
@@ -3904,6 +4116,8 @@ class EngineT final : public Engine {
   DevMem gcol_part_, gcol_box_, a_off_proj_, a_off_recv_;  // class-grouped GEMM columns
   DevMem A_zinv_, a_off_zinv_;  // the preconditioner's inverse self blocks for the matrix cores
   DevMem ng_bcol_, ng_ccol_, ng_aoff_, ng_has_, near_part_;  // class-pair near GEMM
+  GroupTab gclass_, gnear_;             // k_gemm_group: blocks of the class columns and of the near columns
+  DevMem gbox_, gnear_b_, gnear_c_;     // ... their boxes; near columns' sources and partials
   int ngcols_ = 0;
   int ncols_pad_ = 0;
   std::vector<V3> centers_;
