@@ -179,19 +179,10 @@ int do_prepare(mlfma_ctx* ctx) {
   u.box_of = ctx->box_of;
   u.class_of = ctx->cls;
   u.centers = ctx->centers;
-  // tiles of one class (particle order sorted by class, then index)
-  const int TP = ctx->tp.precision == MLFMA_C128 ? 8 : 16;
-  for (int c = 0; c < ctx->C; ++c) {
-    std::vector<int> mem;
+  // particle order by class, then index
+  for (int c = 0; c < ctx->C; ++c)
     for (int p = 0; p < ctx->P; ++p)
-      if (ctx->cls[p] == c) mem.push_back(p);
-    for (size_t s = 0; s < mem.size(); s += TP) {
-      u.tile_start.push_back((int)u.order.size() + (int)s);
-      u.tile_count.push_back((int)std::min<size_t>(TP, mem.size() - s));
-      u.tile_class.push_back(c);
-    }
-    u.order.insert(u.order.end(), mem.begin(), mem.end());
-  }
+      if (ctx->cls[p] == c) u.order.push_back(p);
   // near blocks between distinct particles: assembled on the GPU in one pass
   {
     std::vector<NearKey> keys;

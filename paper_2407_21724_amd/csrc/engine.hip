@@ -801,103 +801,128 @@ __global__ __launch_bounds__(kBlock) void k_gemm_bf16x3(GemmJob j0, GemmJob j1) 
   }
 }
 
-// ------------------------------------------------------- leaf projection --
-// U[r][box(p)][m] = sum_j Rm[class][j][m] x[r][p][j] for a tile of up to TP
-// particles of one class; one thread per pattern sample m (blocks of 128
-// samples along grid y).
-constexpr int kProjBlock = 128;
-template <typename T, int TP>
-__global__ __launch_bounds__(kProjBlock) void k_project(int n, int P, int M2, int nbox, const C2<T>* __restrict__ x,
-                                                         C2<T>* __restrict__ U, const C2<T>* __restrict__ Rm_all,
-                                                         const int* __restrict__ rm_off, const int* __restrict__ order,
-                                                         const int* __restrict__ tile_start,
-                                                         const int* __restrict__ tile_count,
-                                                         const int* __restrict__ tile_class,
-                                                         const int* __restrict__ box_of) {
-  extern __shared__ unsigned char smem_raw[];
-  C2<T>* xs = reinterpret_cast<C2<T>*>(smem_raw);  // [TP][n]
-  const int tile = blockIdx.x, r = blockIdx.z;
-  const int cnt = tile_count[tile], st = tile_start[tile];
-  const C2<T>* __restrict__ Rm = Rm_all + rm_off[tile_class[tile]];
-  for (int i = threadIdx.x; i < TP * n; i += kProjBlock) {
-    const int t = i / n, j = i - t * n;
-    xs[i] = t < cnt ? x[((size_t)r * P + order[st + t]) * n + j] : C2<T>{0, 0};
+template <typename T>
+struct Mfma16;  // 16 x 16 x 4 product, and the row of result register v in lane group g
+template <>
+struct Mfma16<float> {
+  typedef float vec2 __attribute__((ext_vector_type(2)));
+  typedef float vec4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ vec4 mul(float a, float b, vec4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static constexpr __device__ int row(int g, int v) { return 4 * g + v; }
+};
+template <>
+struct Mfma16<double> {
+  typedef double vec2 __attribute__((ext_vector_type(2)));
+  typedef double vec4 __attribute__((ext_vector_type(4)));
+  static __device__ __forceinline__ vec4 mul(double a, double b, vec4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  static constexpr __device__ int row(int g, int v) { return g + 4 * v; }
+};
+
+// ------------------------------------------------------ complex GEMM --
+// The dense contractions of the FP64 product (leaf projection, receive, the
+// preconditioner, and the near blocks of arrays whose particles share them) on
+// the FP64 matrix cores: C[m] (+)= sum_k A[m][k] B[k] for groups of columns that
+// share one complex A, stored transposed ([K][M]).  A block takes 16 rows of 16
+// columns (the right-hand sides folded into them), its four waves a quarter of
+// the k-steps each; a step of 4 complex k is four real products, Re A Re B,
+// -Im A Im B, Re A Im B, Im A Re B.  Four steps of loads are in flight; the
+// partial sums are added through LDS in a fixed order.  Bound by latency for the
+// arrays FP64 is used on: at 24 x 24 cylinders and 2 RHS the near blocks take 27
+// us, the projection 17, the receive 30, where one output per thread (16
+// particles' terms in registers) took 116, 21 and 68; product 349 to 218 us.
+//
+// FP32 contexts that are told to leave the matrix cores run the same kernel
+// with the product written out (Plain16).
+struct Plain16 : Mfma16<float> {
+  static __device__ __forceinline__ vec4 mul(float a, float b, vec4 c) {
+    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const float bk = __shfl(b, i + 16 * k);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) c[v] = fmaf(__shfl(a, 4 * g + v + 16 * k), bk, c[v]);
+    }
+    return c;
+  }
+};
+template <typename T>
+struct ZJob {
+  const C2<T>* A;      // group g, segment s: A + g * astride + aslot[s] * K M, K = kseg
+  const C2<T>* B;      // column b, segment s: B + rhs * sB + bcol[b * nseg + s] * kseg (< 0: zeros)
+  C2<T>* C;            // column b: C + rhs * sC + ccol[b] * M
+  const int *bcol, *ccol;
+  const int4* blk;     // blocks: first column, columns, group
+  size_t astride, sB, sC;
+  int M, nseg, kseg, R, nblk, split, acc;
+  int aslot[9];
+};
+template <typename T>
+__global__ __launch_bounds__(256) void k_zgemm(ZJob<T> J) {
+  using MM = std::conditional_t<std::is_same<T, float>::value, Plain16, Mfma16<T>>;
+  using V4 = typename MM::vec4;
+  constexpr int U = 4;
+  __shared__ V4 red[3][2][64];
+  __shared__ int src[9][16];
+  const int M = J.M, nseg = J.nseg, kseg = J.kseg, R = J.R, tm = (M + 15) / 16;
+  const int m0 = (int)(blockIdx.x % tm) * 16, rest = blockIdx.x / tm;
+  const int4 d = J.blk[rest / J.split];
+  const int f0 = rest % J.split * 16, F = d.y * R;
+  if (f0 >= F) return;  // whole block
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int f = min(f0 + i, F - 1), col = d.x + f / R, rc = f % R;  // idle lanes repeat the last column
+  if (threadIdx.x < 16)
+    for (int sg = 0; sg < nseg; ++sg) src[sg][i] = J.bcol[(size_t)col * nseg + sg];
+  __syncthreads();
+  const C2<T>* __restrict__ Bc = J.B + (size_t)rc * J.sB;
+  const C2<T>* __restrict__ Ag = J.A + d.z * J.astride + min(m0 + i, M - 1);
+  const bool mok = m0 + i < M;
+  const int ns = (kseg + 3) / 4, n = nseg * ns, s0 = wave * n / 4, s1 = (wave + 1) * n / 4;
+  V4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
+  auto load = [&](int s, C2<T>(&a)[U], C2<T>(&b)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int st = min(s + u, n - 1), sg = st / ns, k = 4 * (st - sg * ns) + kq, kc = min(k, kseg - 1);
+      const int slot = J.aslot[sg], q = src[sg][i];
+      const bool on = s + u < s1 && k < kseg && slot >= 0;
+      const C2<T> av = Ag[((size_t)max(slot, 0) * kseg + kc) * M], bv = Bc[(size_t)max(q, 0) * kseg + kc];
+      a[u] = on && mok ? av : C2<T>{0, 0};
+      b[u] = on && q >= 0 ? bv : C2<T>{0, 0};
+    }
+  };
+  auto multiply = [&](const C2<T>(&a)[U], const C2<T>(&b)[U]) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      re = MM::mul(a[u].x, b[u].x, re);
+      im = MM::mul(a[u].x, b[u].y, im);
+      re = MM::mul(-a[u].y, b[u].y, re);
+      im = MM::mul(a[u].y, b[u].x, im);
+    }
+  };
+  C2<T> a0[U], b0[U], a1[U], b1[U];
+  if (s0 < s1) load(s0, a0, b0);
+  for (int s = s0; s < s1; s += 2 * U) {
+    if (s + U < s1) load(s + U, a1, b1);
+    multiply(a0, b0);
+    if (s + U >= s1) break;
+    if (s + 2 * U < s1) load(s + 2 * U, a0, b0);
+    multiply(a1, b1);
+  }
+  if (wave > 0) {
+    red[wave - 1][0][lane] = re;
+    red[wave - 1][1][lane] = im;
   }
   __syncthreads();
-  const int m = blockIdx.y * kProjBlock + threadIdx.x;
-  if (m < M2) {
-    C2<T> acc[TP];
+  if (wave > 0 || f0 + i >= F) return;
 #pragma unroll
-    for (int t = 0; t < TP; ++t) acc[t] = {0, 0};
-#pragma unroll 4
-    for (int j = 0; j < n; ++j) {
-      const C2<T> z = Rm[(size_t)j * M2 + m];
-#pragma unroll
-      for (int t = 0; t < TP; ++t) cfma(acc[t], z, xs[t * n + j]);
-    }
-#pragma unroll
-    for (int t = 0; t < TP; ++t)
-      if (t < cnt) U[((size_t)r * nbox + box_of[order[st + t]]) * M2 + m] = acc[t];
+  for (int w = 0; w < 3; ++w) {
+    re += red[w][0][lane];
+    im += red[w][1][lane];
   }
-}
-
-// ---------------------------------------------------------------- receive --
-// y[r][p][j] += sum_m Qm[class][m][j] G0[r][box(p)][m].  The tile's pattern
-// samples are staged through LDS in chunks of MC; wave w handles particles
-// w, w+4, ... of the tile; lane = output row (rows lane and lane + 64).
-template <typename T, int TP>
-__global__ __launch_bounds__(kBlock) void k_receive(int n, int P, int M2, int nbox, C2<T>* __restrict__ y,
-                                                     const C2<T>* __restrict__ G, const C2<T>* __restrict__ Qm_all,
-                                                     const int* __restrict__ qm_off, const int* __restrict__ order,
-                                                     const int* __restrict__ tile_start, const int* __restrict__ tile_count,
-                                                     const int* __restrict__ tile_class, const int* __restrict__ box_of) {
-  constexpr int MC = 128;
-  __shared__ C2<T> gs[TP * MC];
-  const int tile = blockIdx.x, r = blockIdx.y;
-  const int cnt = tile_count[tile], st = tile_start[tile];
-  const C2<T>* __restrict__ Qm = Qm_all + qm_off[tile_class[tile]];
-  constexpr int PW = TP / (kBlock / 64);  // particles per wave
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  C2<T> a0[PW], a1[PW];
+  C2<T>* __restrict__ Cc = J.C + (size_t)rc * J.sC + (size_t)J.ccol[col] * M;
 #pragma unroll
-  for (int u = 0; u < PW; ++u) a0[u] = a1[u] = {0, 0};
-  const int j0 = lane, j1 = lane + 64;
-  const bool two = n > 64;
-  for (int m0 = 0; m0 < M2; m0 += MC) {
-    const int mc = min(MC, M2 - m0);
-    __syncthreads();
-    for (int i = threadIdx.x; i < TP * MC; i += kBlock) {
-      const int t = i / MC, m = i - t * MC;
-      gs[i] = (t < cnt && m < mc) ? G[((size_t)r * nbox + box_of[order[st + t]]) * M2 + m0 + m] : C2<T>{0, 0};
-    }
-    __syncthreads();
-    if (two) {
-      for (int m = 0; m < mc; ++m) {
-        const C2<T> q0 = j0 < n ? Qm[(size_t)(m0 + m) * n + j0] : C2<T>{0, 0};
-        const C2<T> q1 = j1 < n ? Qm[(size_t)(m0 + m) * n + j1] : C2<T>{0, 0};
-#pragma unroll
-        for (int u = 0; u < PW; ++u) {
-          const C2<T> g = gs[(wave + u * (kBlock / 64)) * MC + m];
-          cfma(a0[u], q0, g);
-          cfma(a1[u], q1, g);
-        }
-      }
-    } else {
-#pragma unroll 4
-      for (int m = 0; m < mc; ++m) {
-        const C2<T> q0 = j0 < n ? Qm[(size_t)(m0 + m) * n + j0] : C2<T>{0, 0};
-#pragma unroll
-        for (int u = 0; u < PW; ++u) cfma(a0[u], q0, gs[(wave + u * (kBlock / 64)) * MC + m]);
-      }
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < PW; ++u) {
-    const int t = wave + u * (kBlock / 64);
-    if (t >= cnt) continue;
-    C2<T>* yp = y + ((size_t)r * P + order[st + t]) * n;
-    if (j0 < n) { C2<T> v = yp[j0]; yp[j0] = {v.x + a0[u].x, v.y + a0[u].y}; }
-    if (j1 < n) { C2<T> v = yp[j1]; yp[j1] = {v.x + a1[u].x, v.y + a1[u].y}; }
+  for (int v = 0; v < 4; ++v) {
+    const int m = m0 + MM::row(kq, v);
+    if (m < M) Cc[m] = J.acc ? C2<T>{Cc[m].x + re[v], Cc[m].y + im[v]} : C2<T>{re[v], im[v]};
   }
 }
 
@@ -1150,22 +1175,6 @@ __global__ __launch_bounds__(64) void k_agg_stream(InterpArgs<T> A) {
 // chain of rows, 17 to 19 us each instead of 29 to 43.  Eight waves per SIMD
 // would need 64 registers, which spills; a wave over several RHS (2, 4, 8)
 // measured the same to 2% slower.
-template <typename T>
-struct Mfma16;  // 16 x 16 x 4 product, and the row of result register v in lane group g
-template <>
-struct Mfma16<float> {
-  typedef float vec2 __attribute__((ext_vector_type(2)));
-  typedef float vec4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ vec4 mul(float a, float b, vec4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  static constexpr __device__ int row(int g, int v) { return 4 * g + v; }
-};
-template <>
-struct Mfma16<double> {
-  typedef double vec2 __attribute__((ext_vector_type(2)));
-  typedef double vec4 __attribute__((ext_vector_type(4)));
-  static __device__ __forceinline__ vec4 mul(double a, double b, vec4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  static constexpr __device__ int row(int g, int v) { return g + 4 * v; }
-};
 // PK (KW <= 32): both halves' windows are staged by one load per row.
 template <typename T, int ORD, int KW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 5 : 1))) void k_dis_mfma(InterpArgs<T> A) {
@@ -2563,25 +2572,15 @@ class EngineT final : public Engine {
     }
     if (int rc = put_i(class_of_, u.class_of, err)) return rc;
     if (int rc = put_i(order_, u.order, err)) return rc;
-    if (int rc = put_i(tile_start_, u.tile_start, err)) return rc;
-    if (int rc = put_i(tile_count_, u.tile_count, err)) return rc;
-    if (int rc = put_i(tile_class_, u.tile_class, err)) return rc;
-    ntiles_ = (int)u.tile_start.size();
-    tp_ = u.tile_count.empty() ? 0 : *std::max_element(u.tile_count.begin(), u.tile_count.end());
     M2_ = ntl_ > 0 ? 2 * lv_[0].K : 0;
     {
       std::vector<cd> rm, qm;
-      std::vector<int> ro, qo;
       for (int c = 0; c < nc_; ++c) {
-        ro.push_back((int)rm.size());
-        qo.push_back((int)qm.size());
         rm.insert(rm.end(), u.Rm[c].begin(), u.Rm[c].end());
         qm.insert(qm.end(), u.Qm[c].begin(), u.Qm[c].end());
       }
       if (int rc = put_c(Rm_, rm, err)) return rc;
       if (int rc = put_c(Qm_, qm, err)) return rc;
-      if (int rc = put_i(rm_off_, ro, err)) return rc;
-      if (int rc = put_i(qm_off_, qo, err)) return rc;
     }
     {
       std::vector<cd> all;
@@ -2592,13 +2591,6 @@ class EngineT final : public Engine {
       std::vector<cd> zi;
       for (auto& m : u.Zinv) zi.insert(zi.end(), m.begin(), m.end());
       if (int rc = put_c(zinv_, zi, err)) return rc;
-      std::vector<int> self_nbr(P_), self_slot(P_);
-      for (int p = 0; p < P_; ++p) {
-        self_nbr[p] = p;
-        self_slot[p] = u.class_of[p];
-      }
-      if (int rc = put_i(self_nbr_, self_nbr, err)) return rc;
-      if (int rc = put_i(self_slot_, self_slot, err)) return rc;
       // per particle tile and slot: the shared matrix, -1 (none) or -2 (mixed)
       auto tile_slots = [&](const std::vector<int>& nbr, const std::vector<int>& slot, int nsp) {
         const int ntl = (P_ + kTPN - 1) / kTPN;
@@ -2616,7 +2608,6 @@ class EngineT final : public Engine {
         return ts;
       };
       if (int rc = put_i(near_tile_slot_, tile_slots(u.near_nbr, u.near_slot, 9), err)) return rc;
-      if (int rc = put_i(self_tile_slot_, tile_slots(self_nbr, self_slot, 1), err)) return rc;
     }
     centers_ = u.centers;
     nslots_ = (int)u.near_mats.size();
@@ -2648,7 +2639,33 @@ class EngineT final : public Engine {
   int upload_mfma(const Upload& u, std::string& err) {
     mfma_ = std::is_same<T, float>::value && std::getenv("MLFMA_NO_MFMA") == nullptr;
     bf16_ = mfma_ && u.precision == 2;
-    near_uniform_ = false;
+    std::vector<std::array<int, 3>> groups;  // columns by class, unpadded
+    std::vector<int> gbox;
+    for (size_t k = 0; k < u.order.size(); ++k) {
+      const int c = u.class_of[u.order[k]];
+      if (groups.empty() || groups.back()[2] != c) groups.push_back({(int)k, (int)k, c});
+      groups.back()[1] = (int)k + 1;
+      gbox.push_back(u.box_of[u.order[k]]);
+    }
+    if (int rc = put_groups(gclass_, groups, err)) return rc;
+    if (int rc = put_i(gbox_, gbox, err)) return rc;
+    // near blocks: one matrix per offset shared by all particles?
+    std::vector<int> sl(9, -1);
+    near_uniform_ = true;
+    for (int p = 0; p < P_ && near_uniform_; ++p)
+      for (int o = 0; o < 9; ++o) {
+        if (u.near_nbr[(size_t)p * 9 + o] < 0) continue;
+        const int sv = u.near_slot[(size_t)p * 9 + o];
+        if (sl[o] == -1) sl[o] = sv;
+        else if (sl[o] != sv) near_uniform_ = false;
+      }
+    if (near_uniform_) {
+      std::vector<int> iota(P_);
+      for (int p = 0; p < P_; ++p) iota[p] = p;
+      if (int rc = put_i(iota_, iota, err)) return rc;
+      if (int rc = put_groups(gnear_, {{0, P_, 0}}, err)) return rc;
+      std::copy(sl.begin(), sl.end(), near_slot9_);
+    }
     if (!mfma_) return 0;
     const int n = n_, nf = 2 * n_;
     auto put_f = [&](DevMem& d, const std::vector<float>& v) { return put_raw(d, v.data(), v.size(), err); };
@@ -2706,16 +2723,6 @@ class EngineT final : public Engine {
         i = e;
       }
       ncols_pad_ = (int)part.size();
-      std::vector<std::array<int, 3>> groups;  // (unpadded: k_gemm_group)
-      std::vector<int> gbox;
-      for (size_t k = 0; k < u.order.size(); ++k) {
-        const int c = u.class_of[u.order[k]];
-        if (groups.empty() || groups.back()[2] != c) groups.push_back({(int)k, (int)k, c});
-        groups.back()[1] = (int)k + 1;
-        gbox.push_back(u.box_of[u.order[k]]);
-      }
-      if (int rc = put_groups(gclass_, groups, err)) return rc;
-      if (int rc = put_i(gbox_, gbox, err)) return rc;
       if (int rc = put_i(gcol_part_, part, err)) return rc;
       if (int rc = put_i(gcol_box_, box, err)) return rc;
       if (int rc = put_i(a_off_proj_, aop, err)) return rc;
@@ -2752,18 +2759,7 @@ class EngineT final : public Engine {
       if (int rc = put_split(A_proj_h_, A_proj_l_, Ap)) return rc;
       if (int rc = put_split(A_recv_h_, A_recv_l_, Ar)) return rc;
     }
-    // near blocks: one matrix per offset shared by all particles?
-    std::vector<int> sl(9, -1);
-    bool uniform = true;
-    for (int p = 0; p < P_ && uniform; ++p)
-      for (int o = 0; o < 9; ++o) {
-        if (u.near_nbr[(size_t)p * 9 + o] < 0) continue;
-        const int sv = u.near_slot[(size_t)p * 9 + o];
-        if (sl[o] == -1) sl[o] = sv;
-        else if (sl[o] != sv) uniform = false;
-      }
-    near_uniform_ = uniform;
-    if (uniform) {
+    if (near_uniform_) {
       const size_t lda = (size_t)9 * nf;
       std::vector<float> An((size_t)nf * lda, 0.f);
       for (int o = 0; o < 9; ++o) {
@@ -2774,10 +2770,6 @@ class EngineT final : public Engine {
       }
       if (int rc = put_f(A_near_, An)) return rc;
       if (int rc = put_split(A_near_h_, A_near_l_, An)) return rc;
-      std::vector<int> iota(P_);
-      for (int p = 0; p < P_; ++p) iota[p] = p;
-      if (int rc = put_i(iota_, iota, err)) return rc;
-      if (int rc = put_groups(gnear_, {{0, P_, 0}}, err)) return rc;
     } else {
       // class-pair blocks differ between particles: one GEMM column per
       // (particle, neighbour) pair, grouped by block (slot) and padded to
@@ -3687,9 +3679,22 @@ class EngineT final : public Engine {
           launch_gemm<1>(pr, rt_np_, near_grouped ? near_group_job(x, rt_np_) : near_job(x, y, R, rt_np_), none, R,
                          st);
           if (near_grouped) near_sum();
-        } else
+        } else if (near_uniform_) {
+          ZJob<T> j{};
+          j.A = near_mats_.template as<CT>();
+          j.B = x;
+          j.bcol = near_nbr_.template as<int>();
+          j.C = y;
+          j.ccol = iota_.template as<int>();
+          j.sB = j.sC = (size_t)P_ * n_;
+          j.M = j.kseg = n_;
+          j.nseg = 9;
+          std::copy(near_slot9_, near_slot9_ + 9, j.aslot);
+          launch_z(pr, j, R, st, &gnear_);
+        } else {
           launch_near(pr, x, y, R, near_mats_.template as<CT>(), near_nbr_.template as<int>(),
                       near_slot_.template as<int>(), near_tile_slot_.template as<int>(), 9, st);
+        }
       } else {
         const size_t cnt = (size_t)R * P_ * n_;
         hipLaunchKernelGGL(k_fill_zero<T>, dim3(grid1d(cnt)), blk, 0, st, y, cnt);
@@ -3699,13 +3704,7 @@ class EngineT final : public Engine {
         if (mfma_) {
           launch_gemm<2>(pr, rt_np_, project_job(x, rt_np_), none, R, st);
         } else {
-          dim3 grid(ntiles_, (M2_ + kProjBlock - 1) / kProjBlock, R);
-          size_t sh = (size_t)kTP * n_ * sizeof(CT);
-          launch(pr, k_project<T, kTP>, grid, dim3(kProjBlock), sh, st, n_, P_, M2_, nb0, x,
-                             pS_[0], Rm_.template as<CT>(), rm_off_.template as<int>(),
-                             order_.template as<int>(), tile_start_.template as<int>(),
-                             tile_count_.template as<int>(), tile_class_.template as<int>(),
-                             box_of_.template as<int>());
+          launch_z(pr, zproject(x), R, st);
         }
       }
     }
@@ -3760,11 +3759,9 @@ class EngineT final : public Engine {
         if (mfma_) {
           launch_gemm<3>(pr, rt_recv_, rj, none, R, st);
         } else {
-          dim3 grid(ntiles_, R);
-          launch(pr, k_receive<T, kTP>, grid, blk, 0, st, n_, P_, M2_, nb0, y, pG_[0],
-                             Qm_.template as<CT>(), qm_off_.template as<int>(), order_.template as<int>(),
-                             tile_start_.template as<int>(), tile_count_.template as<int>(),
-                             tile_class_.template as<int>(), box_of_.template as<int>());
+          launch_z(pr, zclass(Qm_.template as<CT>(), (size_t)M2_ * n_, pG_[0], gbox_, M2_, (size_t)nb0 * M2_, y, order_, n_,
+                              (size_t)P_ * n_, 1),
+                   R, st);
         }
       }
     }
@@ -3792,12 +3789,7 @@ class EngineT final : public Engine {
     if (mfma_) {
       launch_gemm<2>(none, rt_np_, project_job(x, rt_np_), GemmJob{}, R, st);
     } else {
-      dim3 grid(ntiles_, (M2_ + kProjBlock - 1) / kProjBlock, R);
-      size_t sh = (size_t)kTP * n_ * sizeof(CT);
-      launch(none, k_project<T, kTP>, grid, dim3(kProjBlock), sh, st, n_, P_, M2_, L0.nx * L0.ny, x,
-             L0.S.template as<CT>(), Rm_.template as<CT>(), rm_off_.template as<int>(), order_.template as<int>(),
-             tile_start_.template as<int>(), tile_count_.template as<int>(), tile_class_.template as<int>(),
-             box_of_.template as<int>());
+      launch_z(none, zproject(x), R, st);
     }
     if ((size_t)npts * 3 * sizeof(double) > fld_pts_.bytes) HIP_TRY(fld_pts_.alloc((size_t)npts * 3 * sizeof(double)));
     HIP_TRY(hipMemcpyAsync(fld_pts_.p, points, (size_t)npts * 3 * sizeof(double), hipMemcpyHostToDevice, st));
@@ -3843,9 +3835,9 @@ class EngineT final : public Engine {
       launch_gemm<4>(none, rt_np_, precond_job(reinterpret_cast<const CT*>(xv), reinterpret_cast<CT*>(yv), rt_np_),
                      GemmJob{}, R, st);
     } else {
-      launch_near(none, reinterpret_cast<const CT*>(xv), reinterpret_cast<CT*>(yv), R, zinv_.template as<CT>(),
-                  self_nbr_.template as<int>(), self_slot_.template as<int>(), self_tile_slot_.template as<int>(), 1,
-                  st);
+      launch_z(none, zclass(zinv_.template as<CT>(), (size_t)n_ * n_, reinterpret_cast<const CT*>(xv), order_, n_,
+                            (size_t)P_ * n_, reinterpret_cast<CT*>(yv), order_, n_, (size_t)P_ * n_, 0),
+               R, st);
     }
     HIP_TRY(hipGetLastError());
     return 0;
@@ -3875,6 +3867,40 @@ class EngineT final : public Engine {
     j.gstride = (size_t)nf * nf;
     j.gbcol = j.gccol = order_.template as<int>();
     return j;
+  }
+
+  // k_zgemm jobs over the class columns: A [class][K][M], B and C columns of K
+  // and M values at `bcol` and `ccol`
+  ZJob<T> zclass(const CT* A, size_t astride, const CT* B, const DevMem& bcol, int K, size_t sB, CT* C, const DevMem& ccol,
+                 int M, size_t sC, int acc) const {
+    ZJob<T> j{};
+    j.A = A;
+    j.astride = astride;
+    j.B = B;
+    j.bcol = bcol.template as<int>();
+    j.C = C;
+    j.ccol = ccol.template as<int>();
+    j.sB = sB;
+    j.sC = sC;
+    j.M = M;
+    j.nseg = 1;
+    j.kseg = K;
+    j.acc = acc;
+    return j;
+  }
+  ZJob<T> zproject(const CT* x) const {
+    return zclass(Rm_.template as<CT>(), (size_t)n_ * M2_, x, order_, n_, (size_t)P_ * n_, pS_[0], gbox_, M2_,
+                  (size_t)lv_[0].nx * lv_[0].ny * M2_, 0);
+  }
+  void launch_z(Pending& pr, ZJob<T> j, int R, hipStream_t st, const GroupTab* tab = nullptr) {
+    const GroupTab& t = tab ? *tab : gclass_;
+    int u = 0;
+    while (u + 1 < kGroupNU && (long long)kGroupU[u + 1] * R <= 16) ++u;
+    j.R = R;
+    j.blk = t.mem.template as<int4>() + t.off[u];
+    j.nblk = t.cnt[u];
+    j.split = (int)(((long long)kGroupU[u] * R + 15) / 16);
+    launch(pr, k_zgemm<T>, dim3((unsigned)(j.nblk * j.split * ((j.M + 15) / 16))), dim3(256), 0u, st, j);
   }
 
   void launch_near(Pending& pr, const CT* x, CT* y, int R, const CT* mats, const int* nbr, const int* slot,
@@ -3953,7 +3979,6 @@ class EngineT final : public Engine {
   }
 
  private:
-  static constexpr int kTP = sizeof(T) == 4 ? 16 : 8;
   static constexpr int kTPN = 16;
   int rt_np_ = 4, rt_recv_ = 4;  // MFMA GEMM row tiles (of 16) per block: near+projection, receive
   static constexpr size_t kLdsBudget = 48 * 1024;  // preferred tile size (occupancy)
@@ -4083,21 +4108,21 @@ class EngineT final : public Engine {
     return e;
   }
 
-  int N_ = 0, n_ = 0, P_ = 0, nc_ = 0, ntl_ = 0, nx0_ = 0, ny0_ = 0, ntiles_ = 0, tp_ = 0, M2_ = 0, R_alloc_ = 0;
+  int N_ = 0, n_ = 0, P_ = 0, nc_ = 0, ntl_ = 0, nx0_ = 0, ny0_ = 0, M2_ = 0, R_alloc_ = 0;
   CT* pS_[kMaxTrLv] = {};  // pattern buffers in use (see bind_context_buffers)
   CT* pG_[kMaxTrLv] = {};
   float* pNear_ = nullptr;
   std::vector<Lvl> lv_;
   std::vector<Itp> it_;
   const Tree* tree_ = nullptr;
-  DevMem box_of_, class_of_, order_, tile_start_, tile_count_, tile_class_;
+  DevMem box_of_, class_of_, order_;
   DevMem fld_cen_, fld_tab_, fld_pts_;  // field evaluation: centres, leaf sample table, points
   DevMem fld_exp_, fld_part_;           // expansions, chunk sums
   static constexpr int kFldBlocks = 4096;  // target of k_fields
   double fld_k_ = 0;
   int fld_L_ = 0;
-  DevMem Rm_, Qm_, rm_off_, qm_off_;
-  DevMem near_mats_, near_nbr_, near_slot_, zinv_, self_nbr_, self_slot_, near_tile_slot_, self_tile_slot_;
+  DevMem Rm_, Qm_;
+  DevMem near_mats_, near_nbr_, near_slot_, zinv_, near_tile_slot_;
   bool mfma_ = false, near_uniform_ = false;
   int tr_rpb_ = 1;  // RHS per block of the tiled translation (16 measured slower on the full-scale lens)
   // translation kernel forced on every level: 0 = gathered lists, 1/2/3 = LDS
@@ -4118,6 +4143,7 @@ class EngineT final : public Engine {
   DevMem ng_bcol_, ng_ccol_, ng_aoff_, ng_has_, near_part_;  // class-pair near GEMM
   GroupTab gclass_, gnear_;             // k_gemm_group: blocks of the class columns and of the near columns
   DevMem gbox_, gnear_b_, gnear_c_;     // ... their boxes; near columns' sources and partials
+  int near_slot9_[9] = {};              // near_uniform_: the block of each offset (-1: none)
   int ngcols_ = 0;
   int ncols_pad_ = 0;
   std::vector<V3> centers_;

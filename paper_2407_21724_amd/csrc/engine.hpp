@@ -21,9 +21,7 @@ struct Upload {
   const Tree* tree = nullptr;
   std::vector<int> box_of;     // [P] leaf box of each particle
   std::vector<int> class_of;   // [P]
-  // particle tiles of one class: particles order[tile_start[t] ..
-  // tile_start[t] + tile_count[t]) share class tile_class[t]
-  std::vector<int> order, tile_start, tile_count, tile_class;
+  std::vector<int> order;      // [P] particles by class, then index
   // per class, radiation matrix Rm [n][2 K0] (column m = comp*K0 + sample)
   // and receiving matrix Qm [2 K0][n] (quadrature weight and -jk folded in)
   std::vector<std::vector<cd>> Rm, Qm;
