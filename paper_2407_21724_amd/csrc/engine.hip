@@ -2008,6 +2008,20 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// sum of p[0..n) in every thread of a block, in a fixed order
+__device__ inline double block_sum(const double* __restrict__ p, int n) {
+  __shared__ double red[kBlock / 64];
+  double a = 0;
+  for (int b = threadIdx.x; b < n; b += kBlock) a += p[b];
+  a = wave_sum(a);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+  __syncthreads();
+  double o = 0;
+#pragma unroll
+  for (int q = 0; q < kBlock / 64; ++q) o += red[q];
+  return o;
+}
+
 constexpr int kDotE = 4;  // vector elements per lane and sweep of k_dots
 constexpr int kDotMaxBlocks = 512;
 constexpr int kDotMinBlocks = 2048;  // blocks k_dots aims for, over stretches and vector groups
@@ -2017,8 +2031,15 @@ constexpr int kDotMinBlocks = 2048;  // blocks k_dots aims for, over stretches a
 // in VB precision, products accumulated in FP64).  Grid: stretches of w x
 // groups of gsz basis vectors x RHS (the norm goes with group 0), so that a
 // short basis still fills the chip.  The four waves of a block share one
-// stretch of w; partial[((r * ldp) + slot) * gridDim.x + blockIdx.x].  RHS r
-// is skipped where gate[r] == 0.  With jd, the basis has *jd + 1 vectors
+// stretch of w; partial[((r * ldp) + slot) * gridDim.x + blockIdx.x].  The
+// first pass reads the product's result in its own precision S.
+//
+// The second pass (npart given) is taken for RHS r only where the first one
+// removed more than half of |w|^2, i.e. |w'| < |w| / sqrt(2) (selective
+// reorthogonalisation, Daniel-Gragg-Kaufman-Stewart), or always.  Every block
+// sums the nblk_s partials of |w'|^2 for that itself and the first leaves the
+// answer in gate[r]: a reduction and a gate kernel of their own took 3.4 and 3.7
+// us per step, as much as the dots.  With jd, the basis has *jd + 1 vectors
 // (the Arnoldi step index on the device) and the group size is derived
 // from it as the host derives it (dot_group); groups past the basis exit.
 template <typename VB>
@@ -2030,16 +2051,21 @@ __host__ __device__ inline int dot_group(int nv, int VU, int gcap) {
   const int want = steps < gcap ? (steps > 1 ? steps : 1) : (gcap > 1 ? gcap : 1);
   return VU * ((steps + want - 1) / want);
 }
-template <typename VB>
+template <typename VB, typename S>
 __global__ __launch_bounds__(kBlock) void k_dots(int nv, int want_norm, int gsz, int gcap, size_t Nt, size_t vstride,
-                                                  const C2<VB>* __restrict__ V, const Z* __restrict__ w,
-                                                  Z* __restrict__ partial, int ldp, const int* __restrict__ gate,
-                                                  const int* __restrict__ jd) {
+                                                  const C2<VB>* __restrict__ V, const C2<S>* __restrict__ w,
+                                                  Z* __restrict__ partial, int ldp, const double* __restrict__ npart,
+                                                  int nblk_s, const Z* __restrict__ h1, int always,
+                                                  int* __restrict__ gate, const int* __restrict__ jd) {
   const int r = blockIdx.z;
-  if (gate && !gate[r]) return;
   if (jd) {
     nv = *jd + 1;
     gsz = dot_group(nv, dot_vu<VB>(), gcap);
+  }
+  if (npart) {
+    const bool again = always || block_sum(npart + (size_t)r * nblk_s, nblk_s) < 0.5 * h1[(size_t)r * ldp + nv].x;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) gate[r] = again;
+    if (!again) return;
   }
   // per wave: its stretches of w (E elements per lane and sweep) against
   // the group's basis vectors; the wave's sum for each vector goes to LDS
@@ -2055,7 +2081,7 @@ __global__ __launch_bounds__(kBlock) void k_dots(int nv, int want_norm, int gsz,
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   for (int i = threadIdx.x; i < ns * NW; i += kBlock) red[i] = Z{0, 0};
   __syncthreads();
-  const Z* wr = w + (size_t)r * Nt;
+  const C2<S>* wr = w + (size_t)r * Nt;
   const C2<VB>* Vr = V + (size_t)r * Nt + (size_t)v0 * vstride;
   const size_t sweep = (size_t)nblk * NW * 64 * E;
   const size_t first = ((size_t)blk * NW + wave) * 64 * E;
@@ -2073,7 +2099,8 @@ __global__ __launch_bounds__(kBlock) void k_dots(int nv, int want_norm, int gsz,
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const size_t k = base + (size_t)e * 64 + lane;
-        wv[e] = k < Nt ? wr[k] : Z{0, 0};
+        const C2<S> z = k < Nt ? wr[k] : C2<S>{0, 0};
+        wv[e] = Z{(double)z.x, (double)z.y};
       }
       C2<VB> v[VU][E];
 #pragma unroll
@@ -2104,8 +2131,8 @@ __global__ __launch_bounds__(kBlock) void k_dots(int nv, int want_norm, int gsz,
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const size_t k = base + (size_t)e * 64 + lane;
-        const Z z = k < Nt ? wr[k] : Z{0, 0};
-        nn += z.x * z.x + z.y * z.y;
+        const C2<S> z = k < Nt ? wr[k] : C2<S>{0, 0};
+        nn += (double)z.x * (double)z.x + (double)z.y * (double)z.y;
       }
     }
     nn = wave_sum(nn);
@@ -2205,12 +2232,13 @@ __global__ __launch_bounds__(kBlock) void k_reduce(int nblk, const Z* __restrict
   }
 }
 
-// w[r] -= sum_{i<nv} V_i[r] c[r][i]; block partial sums of |w[r]|^2 after the
-// update go to partial[r * gridDim.x + blockIdx.x] (imaginary part 0).
-template <typename VB>
+// w[r] = src[r] - sum_{i<nv} V_i[r] c[r][i]; block partial sums of |w[r]|^2
+// go to npart[r * gridDim.x + blockIdx.x].  src is the product's result (S its
+// precision) or w itself.
+template <typename VB, typename S>
 __global__ __launch_bounds__(kBlock) void k_subtract_norm(int nv, size_t Nt, size_t vstride, const C2<VB>* __restrict__ V,
-                                                           const Z* __restrict__ c, int ldc, Z* __restrict__ w,
-                                                           Z* __restrict__ partial, const int* __restrict__ gate,
+                                                           const Z* __restrict__ c, int ldc, const C2<S>* src, Z* w,
+                                                           double* __restrict__ npart, const int* __restrict__ gate,
                                                            const int* __restrict__ jd) {
   const int r = blockIdx.y;
   if (gate && !gate[r]) return;
@@ -2219,10 +2247,12 @@ __global__ __launch_bounds__(kBlock) void k_subtract_norm(int nv, size_t Nt, siz
   constexpr int VU = sizeof(VB) == 4 ? 8 : 4;  // basis vectors loaded together
   const Z* cr = c + (size_t)r * ldc;
   Z* wr = w + (size_t)r * Nt;
+  const C2<S>* sr = src + (size_t)r * Nt;
   const C2<VB>* Vr = V + (size_t)r * Nt;
   double s2 = 0;
   for (size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x; k < Nt; k += (size_t)gridDim.x * kBlock) {
-    Z acc = wr[k];
+    const C2<S> z = sr[k];
+    Z acc{(double)z.x, (double)z.y};
     int i = 0;
     for (; i + VU <= nv; i += VU) {
       Z v[VU];
@@ -2253,61 +2283,65 @@ __global__ __launch_bounds__(kBlock) void k_subtract_norm(int nv, size_t Nt, siz
   if (threadIdx.x == 0) {
     double o = 0;
     for (int q = 0; q < kBlock / 64; ++q) o += red[q];
-    partial[(size_t)r * gridDim.x + blockIdx.x] = Z{o, 0};
+    npart[(size_t)r * gridDim.x + blockIdx.x] = o;
   }
 }
 
-// Selective reorthogonalisation (Daniel-Gragg-Kaufman-Stewart): a second
-// Gram-Schmidt pass is taken where the first removed more than half of
-// |w|^2, i.e. |w'| < |w| / sqrt(2); always when `always`.
-__global__ void k_dgks_gate(int R, const Z* __restrict__ h1, int ld, int nv, const Z* __restrict__ n1,
-                            int* __restrict__ gate, int always, const int* __restrict__ jd) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= R) return;
-  if (jd) nv = *jd + 1;
-  gate[r] = (always || n1[r].x < 0.5 * h1[(size_t)r * ld + nv].x) ? 1 : 0;
-}
-
-// Hessenberg column: col[r][i] = h1 + h2 (i < nv), col[r][nv] = |w| after the
-// last pass, col[r][nv+1] = gate; scale[r] = 1 / |w| (0 for a zero vector).
-__global__ __launch_bounds__(kBlock) void k_arnoldi_col(int nv, int ld, const Z* __restrict__ h1,
-                                                         const Z* __restrict__ n1, const Z* __restrict__ h2,
-                                                         const Z* __restrict__ n2, const int* __restrict__ gate,
-                                                         Z* __restrict__ col, double* __restrict__ scale,
-                                                         const int* __restrict__ jd) {
-  const int r = blockIdx.x;
-  const int g = gate[r];
-  if (jd) nv = *jd + 1;
-  for (int i = threadIdx.x; i < nv; i += kBlock) {
-    const Z a = h1[(size_t)r * ld + i];
-    const Z b = g ? h2[(size_t)r * ld + i] : Z{0, 0};
-    col[(size_t)r * ld + i] = Z{a.x + b.x, a.y + b.y};
+// End of an Arnoldi step, with nn = |w| after the last pass taken:
+// v_{j+1} = w / nn (0 for a zero vector) rounded to the basis precision, and the
+// same values in the product's precision D in conv (if not null), the input of
+// the next product.  The Hessenberg column goes straight to pinned host memory:
+// col[r][i] = h1 + h2 (i < nv), col[r][nv] = nn, col[r][nv + 1] = gate.  Every
+// block sums the partials of nn itself (npart: the first pass's [R][nblk_s], then
+// the second's): one launch instead of a reduction, a column kernel, a scaling and
+// a copy to the host, which with the conversion, the gate and its reduction made 11
+// of a step's kernels.  40 x 40 cylinders, 1 RHS, 40 steps: 10.1 to 9.65 ms, 218 us
+// of kernels per step of which the product takes 188.  With jd (the Arnoldi step
+// index on the device), out is V_{*jd + 1} of the basis at out.
+template <typename VB, typename D>
+__global__ __launch_bounds__(kBlock) void k_arnoldi_end(int nv, int ld, size_t Nt, size_t vstride, int R, int nblk_s,
+                                                        const Z* __restrict__ w, const Z* __restrict__ h1,
+                                                        const Z* __restrict__ h2, const double* __restrict__ npart,
+                                                        const int* __restrict__ gate, Z* __restrict__ col,
+                                                        C2<VB>* __restrict__ out, C2<D>* __restrict__ conv,
+                                                        const int* __restrict__ jd) {
+  const int r = blockIdx.y, g = gate[r];
+  const double nn = sqrt(fmax(0.0, block_sum(npart + ((size_t)(g ? R : 0) + r) * nblk_s, nblk_s)));
+  const double c = nn > 0 ? 1.0 / nn : 0.0;
+  if (jd) {
+    nv = *jd + 1;
+    out += (size_t)nv * vstride;
   }
-  if (threadIdx.x == 0) {
-    const double nn = sqrt(fmax(0.0, g ? n2[r].x : n1[r].x));
-    col[(size_t)r * ld + nv] = Z{nn, 0};
-    col[(size_t)r * ld + nv + 1] = Z{(double)g, 0};
-    scale[r] = nn > 0 ? 1.0 / nn : 0.0;
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < nv; i += kBlock) {
+      const Z a = h1[(size_t)r * ld + i];
+      const Z b = g ? h2[(size_t)r * ld + i] : Z{0, 0};
+      col[(size_t)r * ld + i] = Z{a.x + b.x, a.y + b.y};
+    }
+    if (threadIdx.x < 2) col[(size_t)r * ld + nv + threadIdx.x] = Z{threadIdx.x ? (double)g : nn, 0};
+  }
+  for (size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x; k < Nt; k += (size_t)gridDim.x * kBlock) {
+    const Z v = w[(size_t)r * Nt + k];
+    const C2<VB> q{(VB)(v.x * c), (VB)(v.y * c)};
+    out[(size_t)r * Nt + k] = q;
+    if (conv) conv[(size_t)r * Nt + k] = C2<D>{(D)q.x, (D)q.y};
   }
 }
 
 // out[r] = a[r] * s[r] with a real per-RHS factor (rounded to the basis
-// precision); conv (if not null) receives the same rounded values in the
-// product's precision D, the input of the next product.  With jd (the
-// Arnoldi step index on the device), out is V_{*jd + 1} of the basis at out.
+// precision); conv receives the same rounded values in the product's
+// precision D, the input of the next product.
 template <typename VB, typename D>
 __global__ __launch_bounds__(kBlock) void k_scale_real(size_t Nt, const Z* __restrict__ a,
                                                         const double* __restrict__ s, C2<VB>* __restrict__ out,
-                                                        C2<D>* __restrict__ conv, size_t vstride,
-                                                        const int* __restrict__ jd) {
+                                                        C2<D>* __restrict__ conv) {
   const int r = blockIdx.y;
   const double c = s[r];
-  if (jd) out += (size_t)(*jd + 1) * vstride;
   for (size_t k = (size_t)blockIdx.x * kBlock + threadIdx.x; k < Nt; k += (size_t)gridDim.x * kBlock) {
     const Z v = a[(size_t)r * Nt + k];
     const C2<VB> q{(VB)(v.x * c), (VB)(v.y * c)};
     out[(size_t)r * Nt + k] = q;
-    if (conv) conv[(size_t)r * Nt + k] = C2<D>{(D)q.x, (D)q.y};
+    conv[(size_t)r * Nt + k] = C2<D>{(D)q.x, (D)q.y};
   }
 }
 __global__ void k_set_step(int* __restrict__ jd, int v, int add) {
@@ -4151,7 +4185,7 @@ class EngineT final : public Engine {
   long long nnear_ = 0;
   std::vector<long long> pairs_;
   // GMRES workspace
-  DevMem gV_, gw_, gx_, gb_, gtmp_, gtmpT_, gtmpT2_, gpart_, gh_, gh2_, gcol_, gn_, ggate_, gscale_, gstep_;
+  DevMem gV_, gw_, gx_, gb_, gtmp_, gtmpT_, gtmpT2_, gpart_, gh_, gh2_, gnp_, gn_, ggate_, gscale_, gstep_;
   HostMem hcol_, hy_;
   hipEvent_t col_ev_ = nullptr;
 };
@@ -4191,10 +4225,10 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
   HIP_TRY(gtmp_.alloc(tot * sizeof(Z)));
   HIP_TRY(gtmpT_.alloc(tot * sizeof(CT)));
   HIP_TRY(gtmpT2_.alloc(tot * sizeof(CT)));
-  HIP_TRY(gpart_.alloc((size_t)R * ld * std::max(nblk_d, nblk_s) * sizeof(Z)));
+  HIP_TRY(gpart_.alloc((size_t)R * ld * nblk_d * sizeof(Z)));
   HIP_TRY(gh_.alloc((size_t)R * ld * sizeof(Z)));
   HIP_TRY(gh2_.alloc((size_t)R * ld * sizeof(Z)));
-  HIP_TRY(gcol_.alloc((size_t)R * ld * sizeof(Z)));
+  HIP_TRY(gnp_.alloc((size_t)2 * R * nblk_s * sizeof(double)));
   HIP_TRY(gn_.alloc((size_t)2 * R * sizeof(Z)));
   HIP_TRY(ggate_.alloc((size_t)R * sizeof(int)));
   HIP_TRY(gstep_.alloc(sizeof(int)));
@@ -4212,9 +4246,9 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
   Z* part = gpart_.as<Z>();
   Z* h1 = gh_.as<Z>();
   Z* h2 = gh2_.as<Z>();
-  Z* col = gcol_.as<Z>();
+  double* np1 = gnp_.as<double>();
+  double* np2 = np1 + (size_t)R * nblk_s;
   Z* n1 = gn_.as<Z>();
-  Z* n2 = n1 + R;
   int* gate = ggate_.as<int>();
   double* scale = gscale_.as<double>();
   Z* hcol = hcol_.as<Z>();
@@ -4228,8 +4262,9 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
   // launch is shaped for the longest basis, m vectors, and the kernels read
   // the basis length from the device.
   const int gcap = (kDotMinBlocks + nblk_d - 1) / nblk_d;
-  auto dots_on = [&](hipStream_t s, int nv, int want_norm, const Z* ww, Z* out, int ldo, const int* g,
+  auto dots_on = [&](hipStream_t s, int nv, int want_norm, const auto* ww, Z* out, int ldo, const double* np,
                      const int* jd) {
+    using SV = decltype(std::decay_t<decltype(*ww)>{}.x);
     constexpr int VU = dot_vu<VB>();
     const int nl = jd ? m : nv;
     int gsz = dot_group(nl, VU, gcap), ng = nl > 0 ? (nl + gsz - 1) / gsz : 1;
@@ -4239,43 +4274,43 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
         gsz = std::max(gsz, gn);
         ng = std::max(ng, (n + gn - 1) / gn);
       }
-    hipLaunchKernelGGL(k_dots<VB>, dim3(nblk_d, ng, R), blk, (uint32_t)((gsz + want_norm) * (kBlock / 64) * sizeof(Z)),
-                       s, nv, want_norm, gsz, gcap, Nt, vstride, (const CV*)V, ww, part, ld, g, jd);
-    hipLaunchKernelGGL(k_reduce, dim3(nl + want_norm, R), blk, 0, s, nblk_d, part, ld, out, ldo, g, jd, want_norm);
+    hipLaunchKernelGGL((k_dots<VB, SV>), dim3(nblk_d, ng, R), blk,
+                       (uint32_t)((gsz + want_norm) * (kBlock / 64) * sizeof(Z)), s, nv, want_norm, gsz, gcap, Nt,
+                       vstride, (const CV*)V, ww, part, ld, np, nblk_s, (const Z*)h1, always_reorth ? 1 : 0, gate, jd);
+    hipLaunchKernelGGL(k_reduce, dim3(nl + want_norm, R), blk, 0, s, nblk_d, part, ld, out, ldo,
+                       np ? gate : (const int*)nullptr, jd, want_norm);
   };
-  auto dots = [&](int nv, int want_norm, const Z* ww, Z* out, int ldo, const int* g) {
-    dots_on(st, nv, want_norm, ww, out, ldo, g, nullptr);
+  auto dots = [&](int nv, int want_norm, const Z* ww, Z* out, int ldo) {
+    dots_on(st, nv, want_norm, ww, out, ldo, nullptr, nullptr);
   };
-  // ww -= sum_i V_i c_i; nout[r] = |ww_r|^2
-  auto subtract_on = [&](hipStream_t s, int nv, const Z* c, Z* ww, Z* nout, const int* g, const int* jd) {
-    hipLaunchKernelGGL(k_subtract_norm<VB>, dim3(nblk_s, R), blk, 0, s, nv, Nt, vstride, (const CV*)V, c, ld, ww,
-                       part, g, jd);
-    hipLaunchKernelGGL(k_reduce, dim3(1, R), blk, 0, s, nblk_s, part, 1, nout, 1, g, nullptr, 0);
+  // w = src - sum_i V_i c_i; partials of |w_r|^2 to np
+  auto subtract_on = [&](hipStream_t s, int nv, const Z* c, const auto* src, double* np, const int* g, const int* jd) {
+    using SV = decltype(std::decay_t<decltype(*src)>{}.x);
+    hipLaunchKernelGGL((k_subtract_norm<VB, SV>), dim3(nblk_s, R), blk, 0, s, nv, Nt, vstride, (const CV*)V, c, ld, src,
+                       w, np, g, jd);
   };
-  // Arnoldi step j on w = A v_j: two Gram-Schmidt passes, the second where
-  // DGKS asks for it; the Hessenberg column to col (and to the host), v_{j+1}
+  // Arnoldi step j on A v_j, which is in tT: two Gram-Schmidt passes, the
+  // second where DGKS asks for it; the Hessenberg column to the host, v_{j+1}
   // = w / |w|, also written to tT for the next product when conv_next.  With
   // jd: j is read from the device, v_{j+1} always goes to tT, and *jd
   // advances, so that the same launches (one captured graph) serve every
   // step.
   auto arnoldi_step = [&](hipStream_t s, int j, const int* jd, bool conv_next) -> int {
     const int nv = j + 1;
-    dots_on(s, nv, 1, w, h1, ld, nullptr, jd);
-    subtract_on(s, nv, h1, w, n1, nullptr, jd);
-    hipLaunchKernelGGL(k_dgks_gate, dim3((R + 63) / 64), dim3(64), 0, s, R, h1, ld, nv, n1, gate,
-                       always_reorth ? 1 : 0, jd);
-    dots_on(s, nv, 0, w, h2, ld, gate, jd);
-    subtract_on(s, nv, h2, w, n2, gate, jd);
-    hipLaunchKernelGGL(k_arnoldi_col, dim3(R), blk, 0, s, nv, ld, h1, n1, h2, n2, gate, col, scale, jd);
-    hipLaunchKernelGGL((k_scale_real<VB, T>), gv, blk, 0, s, Nt, (const Z*)w, (const double*)scale,
-                       jd ? V : V + (size_t)(j + 1) * vstride, (jd || conv_next) ? tT : (CT*)nullptr, vstride, jd);
-    HIP_TRY(hipMemcpyAsync(hcol, col, (size_t)R * ld * sizeof(Z), hipMemcpyDeviceToHost, s));
+    dots_on(s, nv, 1, (const CT*)tT, h1, ld, nullptr, jd);
+    subtract_on(s, nv, h1, (const CT*)tT, np1, nullptr, jd);
+    dots_on(s, nv, 0, (const Z*)w, h2, ld, np1, jd);
+    subtract_on(s, nv, h2, (const Z*)w, np2, gate, jd);
+    hipLaunchKernelGGL((k_arnoldi_end<VB, T>), gv, blk, 0, s, nv, ld, Nt, vstride, R, nblk_s, (const Z*)w,
+                       (const Z*)h1, (const Z*)h2, (const double*)np1, (const int*)gate, hcol,
+                       jd ? V : V + (size_t)(j + 1) * vstride, (jd || conv_next) ? tT : (CT*)nullptr, jd);
     if (jd) hipLaunchKernelGGL(k_set_step, dim3(1), dim3(64), 0, s, jd_dev, 1, 1);
     return 0;
   };
   // operator A z = Z (P^-1 z) -> result FP64 in `out`; z is a basis vector
   // (precond) or an FP64 iterate
-  // (A_converted: z already converted into tT)
+  // (A_converted: z already converted into tT; without `out` the result stays
+  // in tT, with precond, for the Arnoldi step)
   auto apply_A_converted = [&](Z* out, bool precond) -> int {
     const CT* src = tT;
     if (precond) {
@@ -4291,7 +4326,7 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
       if (R_alloc_ != old_alloc) clear_graphs();
       if (int rc = enqueue(src, dst, R, 3, st, err)) return rc;
     }
-    hipLaunchKernelGGL(k_to_z<T>, dim3(grid1d(tot)), blk, 0, st, dst, out, tot);
+    if (out) hipLaunchKernelGGL(k_to_z<T>, dim3(grid1d(tot)), blk, 0, st, dst, out, tot);
     return 0;
   };
   auto apply_A_from = [&](auto* z, Z* out, bool precond) -> int {
@@ -4301,7 +4336,7 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
   };
   auto apply_A = [&](const Z* z, Z* out, bool precond) -> int { return apply_A_from(z, out, precond); };
   auto norms = [&](const Z* vec, std::vector<double>& out) -> int {
-    dots(0, 1, vec, n1, 1, nullptr);
+    dots(0, 1, vec, n1, 1);
     HIP_TRY(hipMemcpyAsync(hcol, n1, (size_t)R * sizeof(Z), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     out.resize(R);
@@ -4407,12 +4442,11 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
       if (!done[r]) cycles[r]++;
     }
     HIP_TRY(hipMemcpyAsync(scale, s0.data(), (size_t)R * sizeof(double), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL((k_scale_real<VB, T>), gv, blk, 0, st, Nt, (const Z*)w, (const double*)scale, V, tT, vstride,
-                       (const int*)nullptr);
+    hipLaunchKernelGGL((k_scale_real<VB, T>), gv, blk, 0, st, Nt, (const Z*)w, (const double*)scale, V, tT);
     int j = 0;
     std::vector<char> active(R);
     for (int r = 0; r < R; ++r) active[r] = !done[r];
-    if (int rc = apply_A_converted(w, true)) return rc;  // v_0 is in tT
+    if (int rc = apply_A_converted(nullptr, true)) return rc;  // v_0 is in tT
     if (graph_steps) {
       if (!step_graph.e)
         if (int rc = capture_step()) return rc;
@@ -4431,7 +4465,7 @@ int EngineT<T>::gmres_t(const void* bv, void* xv, int R, double rtol, int max_it
       // queue the next product (its input v_{j+1} is in tT) before the host
       // looks at the column
       if (next)
-        if (int rc = apply_A_converted(w, true)) return rc;
+        if (int rc = apply_A_converted(nullptr, true)) return rc;
       HIP_TRY(hipGetLastError());
       HIP_TRY(hipEventSynchronize(col_ev_));
       bool any_active = false;
