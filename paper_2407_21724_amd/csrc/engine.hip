@@ -1573,9 +1573,17 @@ __global__ __launch_bounds__(kBlock) void k_translate_tiled(TrLevels<T> L, int R
 // and 64 consecutive samples (one per lane).  A lane holds the 40 operators
 // of its sample that a tile uses (offsets with |dx| or |dy| >= 2) and, one
 // field component at a time, the 16 boxes' sums in registers, and reads
-// each of the tile's 10 x 10 source boxes once per component; the interaction lists are known at compile time (a
-// tile starts at even box indices, so a receiver's parity fixes its list).
-// Terms are added in the order of the gathered lists (dy outer, dx inner).
+// each of the tile's 10 x 10 source boxes once per component; the interaction
+// lists are known at compile time (a tile starts at even box indices, so a
+// receiver's parity fixes its list).  Terms are added in the order of the
+// gathered lists (dy outer, dx inner).  A block takes `ipb` items, an item being
+// one component of one right-hand side, with the operators loaded once.
+// Bound by the source reads that two waves per SIMD keep in flight (9 TB/s of L2
+// reads on the 200 x 200 lens at 16 RHS, 3.7 TB/s of HBM traffic where a copy
+// reaches 4.7; 50% of the vector rate).  Blocks of one component for small launches
+// and prefetched rows at the grid's edge: 4 x 4 spheres 10.1 to 6.4 us, 40 x 40
+// cylinders 22.5 to 18.5 (874 to 814 at 64 RHS), 83 x 61 lens at 3 RHS 131 to 124,
+// 200 x 200 at 16 RHS 5400 to 5290.
 constexpr int kTrRegTile = 4;
 constexpr int kTrBand = 8;  // tile columns per band in the block order of k_translate_reg
 __host__ __device__ constexpr bool tr_in_list(int rx, int ry, int dx, int dy) {
@@ -1606,54 +1614,54 @@ __device__ __forceinline__ void tr_reg_row(C2<float> (&acc)[kTrRegTile * kTrRegT
       }
   }
 }
-// INTERIOR: the 10 x 10 source window lies inside the grid.  Its rows are
-// loaded DEPTH rows ahead of the row being summed, with no bounds test
-// between a load and its use (a load inside a conditional block makes the
-// compiler wait for every outstanding load there).  CHK (a slower variant
-// kept for measurement): a column test per source, a branch the compiler
+// The rows of the source window are loaded DEPTH rows ahead of the row being
+// summed, with no bounds test between a load and its use (a load inside a
+// conditional block makes the compiler wait for every outstanding load there).
+// INTERIOR: the window lies inside the grid; otherwise loads are clamped to the
+// grid and sources outside it are zeroed when their row is summed.  CHK (a slower
+// variant for interior tiles, kept for measurement): a column test per source, a branch the compiler
 // cannot remove, with a scheduling barrier after each row, holds the loads
 // to that schedule; without it the compiler is free to issue all of a
 // component's source loads at the top.
 template <bool INTERIOR, int DEPTH, bool CHK>
 __device__ __forceinline__ void tr_reg_tile(const C2<float>* Sr, C2<float>* __restrict__ Gr,
                                             const C2<float> (&t)[7][7], int bx0, int by0, int nx, int ny, int K,
-                                            bool live) {
+                                            bool live, int i0, int i1) {
   constexpr int TT = kTrRegTile, H = TT + 6;
 #pragma unroll 1
-  for (int comp = 0; comp < 2; ++comp) {
+  for (int it = i0; it < i1; ++it) {
     C2<float> acc[TT * TT];
 #pragma unroll
     for (int b = 0; b < TT * TT; ++b) acc[b] = C2<float>{0.f, 0.f};
-    const C2<float>* Sc = Sr + (size_t)comp * K;
-    if constexpr (INTERIOR) {
+    const size_t off = ((size_t)(it >> 1) * ny * nx * 2 + (it & 1)) * K;  // right-hand side, component
+    const C2<float>* Sc = Sr + off;
+    {
       // rows DEPTH ahead of the one being summed, in a ring of DEPTH + 1
       C2<float> rb[DEPTH + 1][H];
       auto load_row = [&](int hy, C2<float>(&dst)[H]) {
-        const C2<float>* row = Sc + ((size_t)(by0 - 3 + hy) * nx + (bx0 - 3)) * 2 * K;
+        const int gy = by0 - 3 + hy, gx = bx0 - 3;
+        const C2<float>* row = Sc + (size_t)(INTERIOR ? gy : min(max(gy, 0), ny - 1)) * nx * 2 * K;
 #pragma unroll
-        for (int hx = 0; hx < H; ++hx) dst[hx] = row[(size_t)hx * 2 * K];
+        for (int hx = 0; hx < H; ++hx) dst[hx] = row[(size_t)(INTERIOR ? gx + hx : min(max(gx + hx, 0), nx - 1)) * 2 * K];
       };
 #pragma unroll
       for (int d = 0; d < DEPTH; ++d) load_row(d, rb[d]);
 #pragma unroll
       for (int hy = 0; hy < H; ++hy) {
         if (hy + DEPTH < H) load_row(hy + DEPTH, rb[(hy + DEPTH) % (DEPTH + 1)]);
-        tr_reg_row<CHK>(acc, t, rb[hy % (DEPTH + 1)], hy, bx0, nx);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    } else {
-#pragma unroll
-      for (int hy = 0; hy < H; ++hy) {
+        C2<float>(&v)[H] = rb[hy % (DEPTH + 1)];
         const int gy = by0 - 3 + hy;
-        if (gy < 0 || gy >= ny) continue;
-        C2<float> sv[H];
-        const C2<float>* row = Sc + ((size_t)gy * nx + (bx0 - 3)) * 2 * K;
+        if (INTERIOR || (gy >= 0 && gy < ny)) {
+          if constexpr (!INTERIOR) {
 #pragma unroll
-        for (int hx = 0; hx < H; ++hx) {
-          const int gx = bx0 - 3 + hx;
-          sv[hx] = (gx >= 0 && gx < nx) ? row[(ptrdiff_t)hx * 2 * K] : C2<float>{0.f, 0.f};
+            for (int hx = 0; hx < H; ++hx) {
+              const int gx = bx0 - 3 + hx;
+              v[hx] = gx >= 0 && gx < nx ? v[hx] : C2<float>{0.f, 0.f};
+            }
+          }
+          tr_reg_row<INTERIOR && CHK>(acc, t, v, hy, bx0, nx);
         }
-        tr_reg_row<true>(acc, t, sv, hy, bx0, nx);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     if (live) {
@@ -1663,7 +1671,7 @@ __device__ __forceinline__ void tr_reg_tile(const C2<float>* Sr, C2<float>* __re
         for (int rx = 0; rx < TT; ++rx) {
           const int gx = bx0 + rx, gy = by0 + ry;
           if (!INTERIOR && (gx >= nx || gy >= ny)) continue;
-          Gr[((size_t)gy * nx + gx) * 2 * K + (size_t)comp * K] = acc[ry * TT + rx];
+          Gr[((size_t)gy * nx + gx) * 2 * K + off] = acc[ry * TT + rx];
         }
     }
   }
@@ -1683,7 +1691,7 @@ __device__ __forceinline__ void tr_load_ops(C2<float> (&t)[7][7], const CP<float
   (tr_put_pair<Q>(t, e[Q]), ...);
 }
 template <int DEPTH, bool CHK>
-__global__ __launch_bounds__(64) void k_translate_reg(TrLevels<float> L, int R) {
+__global__ __launch_bounds__(64) void k_translate_reg(TrLevels<float> L, int R, int ipb) {
   constexpr int TT = kTrRegTile, H = TT + 6;
   const int gb = xcd_block(blockIdx.x, L.total);
   if (gb >= L.total) return;
@@ -1696,7 +1704,7 @@ __global__ __launch_bounds__(64) void k_translate_reg(TrLevels<float> L, int R) 
   // measured 2% slower on the 200 x 200 lens)
   const int nch = (K + 63) / 64;
   const int tile = lb % ntile, rest = lb / ntile;
-  const int ch = rest % nch, r = rest / nch;
+  const int ch = rest % nch, i0 = rest / nch * ipb, i1 = min(i0 + ipb, 2 * R);
   // tiles in vertical bands of kTrBand tile columns, row by row within a
   // band: a tile's upper neighbour (which shares 6 of its 10 source rows)
   // runs kTrBand blocks earlier instead of a whole tile row earlier, so the
@@ -1716,9 +1724,8 @@ __global__ __launch_bounds__(64) void k_translate_reg(TrLevels<float> L, int R) 
   const int s = ch * 64 + (int)threadIdx.x;
   const bool live = s < K;
   const int sl = live ? s : K - 1;
-  const size_t nb = (size_t)nx * ny;
-  const C2<float>* Sr = V.S + (size_t)r * nb * 2 * K + sl;
-  C2<float>* __restrict__ Gr = V.G + (size_t)r * nb * 2 * K + sl;
+  const C2<float>* Sr = V.S + sl;
+  C2<float>* __restrict__ Gr = V.G + sl;
   // the 40 operators of this sample, two per 16-byte load
   C2<float> t[7][7];
 #pragma unroll
@@ -1726,14 +1733,11 @@ __global__ __launch_bounds__(64) void k_translate_reg(TrLevels<float> L, int R) 
 #pragma unroll
     for (int dx = 0; dx < 7; ++dx) t[dy][dx] = C2<float>{0.f, 0.f};
   tr_load_ops(t, V.TLp + sl, K, std::make_integer_sequence<int, 20>{});
-  // tiles whose 10 x 10 source window lies inside the grid take a path with
-  // no bounds tests, so that no branch separates a load from its use and
-  // the loads of later sources stay in flight (a load inside a conditional
-  // block makes the compiler wait for every outstanding load there)
+  // tiles whose 10 x 10 source window lies inside the grid need no clamps
   if (bx0 >= 3 && by0 >= 3 && bx0 + TT + 3 <= nx && by0 + TT + 3 <= ny)
-    tr_reg_tile<true, DEPTH, CHK>(Sr, Gr, t, bx0, by0, nx, ny, K, live);
+    tr_reg_tile<true, DEPTH, CHK>(Sr, Gr, t, bx0, by0, nx, ny, K, live, i0, i1);
   else
-    tr_reg_tile<false, DEPTH, CHK>(Sr, Gr, t, bx0, by0, nx, ny, K, live);
+    tr_reg_tile<false, DEPTH, CHK>(Sr, Gr, t, bx0, by0, nx, ny, K, live, i0, i1);
 }
 
 // ----------------------------------------------------------------- fields --
@@ -3413,7 +3417,7 @@ class EngineT final : public Engine {
           V = TrLevel<float>{pS_[l], pG_[l],     L.TL.template as<CT>(), nullptr, nullptr, nullptr, L.nx,
                              L.ny,   L.K,    reg.total,                  L.TLp.template as<CP<float>>()};
           reg.total += ((L.nx + kTrRegTile - 1) / kTrRegTile) * ((L.ny + kTrRegTile - 1) / kTrRegTile) *
-                       ((L.K + 63) / 64) * R;
+                       ((L.K + 63) / 64);
           bytes += cb * (4.0 * R * L.nx * L.ny * L.K + 40.0 * L.K);
           flops += 16.0 * R * (double)pairs_[l] * L.K;
         }
@@ -3421,12 +3425,23 @@ class EngineT final : public Engine {
         // mode 4 (the default): no column tests in interior tiles; modes 5-8:
         // column tests, source rows of interior tiles loaded 0, 1, 3 or 2 rows
         // ahead of the row being summed
+        // items (a right-hand side's component) per block: one where that fills
+        // at most the 2048 waves that run at once (40 x 40 cylinders, 1 RHS: 18.5
+        // us, 20 with two; 37 x 29 at 5 RHS, 5255 tiles: 46 to 48, 45 to 47 with
+        // two); four, half the reads of the operators, for blocks of four that
+        // fill them eight times over and divide the batch (200 x 200 lens at 16
+        // RHS: 5290 us, 5440 with two, 5350 with eight; 83 x 61 lens at 3 RHS,
+        // which four do not divide: 151 us, 124 with two)
+        const long long nt = (long long)reg.total * R;
+        const int ipb = nt <= 2048 ? 1 : R % 2 == 0 && nt / 2 >= 16384 ? 4 : 2, per = 2 * R / ipb;
+        for (int l = 0; l < reg.n; ++l) reg.lv[l].start *= per;
+        reg.total *= per;
         const dim3 g(xcd_grid(reg.total)), b(64);
-        if (tr_force_ == 5) launch(pr, k_translate_reg<0, true>, g, b, 0u, st, reg, R);
-        else if (tr_force_ == 6) launch(pr, k_translate_reg<1, true>, g, b, 0u, st, reg, R);
-        else if (tr_force_ == 7) launch(pr, k_translate_reg<3, true>, g, b, 0u, st, reg, R);
-        else if (tr_force_ == 8) launch(pr, k_translate_reg<2, true>, g, b, 0u, st, reg, R);
-        else launch(pr, k_translate_reg<2, false>, g, b, 0u, st, reg, R);
+        if (tr_force_ == 5) launch(pr, k_translate_reg<0, true>, g, b, 0u, st, reg, R, ipb);
+        else if (tr_force_ == 6) launch(pr, k_translate_reg<1, true>, g, b, 0u, st, reg, R, ipb);
+        else if (tr_force_ == 7) launch(pr, k_translate_reg<3, true>, g, b, 0u, st, reg, R, ipb);
+        else if (tr_force_ == 8) launch(pr, k_translate_reg<2, true>, g, b, 0u, st, reg, R, ipb);
+        else launch(pr, k_translate_reg<2, false>, g, b, 0u, st, reg, R, ipb);
         return;
       }
     }
