@@ -150,16 +150,19 @@ __global__ __launch_bounds__(256) void k_layer(LayerArgs a) {
 // flight during the current U.  Training (MODE 1) goes on to the deltas of
 // every layer (W^T as the operand) and writes activations and deltas
 // feature-major, the layout in which the weight gradients contract over
-// samples.  Bound by the matrix cores at 62 TFLOP/s (102,400 samples of the
-// 43-256-256-256-120 network in 0.62 ms, features and phases included; 2.6 ms
-// with a GEMM per layer and the features formed on the host).
+// samples.  Bound by the matrix cores at 78 TFLOP/s (102,400 samples of the
+// 43-256-256-256-120 network in 0.48 ms, features and phases included; 2.6 ms
+// with a GEMM per layer and the features formed on the host).  Two blocks of 8
+// waves share a CU, so that one's inputs, phases and barriers hide behind the
+// other's products: two steps of weights in flight and 124 registers, where four
+// steps took 162, one block per CU and 0.62 ms.
 //
 // Used from kNetFrom samples on, where its blocks of 16 (CT = 1, 16 waves)
 // cover half of the chip (training step: 106 against 89 us by layers at 1024
 // samples, 115 against 131 at 2048, 144 against 217 at 4096).  From kNetWide
 // on (twice that in training, whose blocks do three times the work) CT = 4 and
-// 8 waves read the weights a quarter as often (forward 83 us both ways at 8192
-// samples, 85 against 162 at 16384; training 308 against 273 and 405 against
+// 8 waves read the weights a quarter as often (forward 75 against 83 us at
+// 8192 samples, 76 against 162 at 16384; training 308 against 262 and 390 against
 // 523).  Networks wider than kNetWidth or deeper than kNetLayers take k_layer
 // for every batch.
 constexpr int kNetLayers = 8, kNetWidth = 512, kNetFrom = 2048, kNetWide = 8192;
@@ -202,8 +205,8 @@ __device__ __forceinline__ float guess_feature(const GuessArgs& q, int s, int f)
 
 // acc = sum_k A(m, k) h[sample][k] for this wave's feature tiles: A = W [M][K]
 // row-major, or its transpose (W [K][M]).  Rows and k past the end are zero.
-template <int CT, int W, int RT, int U, bool TRANS>
-__device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* __restrict__ Wl, bool vec, int M, int K,
+template <int CT, int W, int RT, int U, bool TRANS, bool VEC>
+__device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* __restrict__ Wl, int M, int K,
                                             const float* h, int stride, int wave, int i, int kq) {
   const int nk = pad16(K) / 16;
 #pragma unroll
@@ -216,7 +219,7 @@ __device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* _
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const int m = 16 * (wave + W * rt) + i, k = 16 * (k0 + u) + 4 * kq;
-        a[u][rt] = TRANS ? col4(Wl, M, K, m, k) : row4(Wl, M, K, K, vec, m, k);
+        a[u][rt] = TRANS ? col4(Wl, M, K, m, k) : row4(Wl, M, K, K, VEC, m, k);
       }
   };
   auto multiply = [&](int k0, const f32x4(&a)[U][RT]) {
@@ -239,19 +242,33 @@ __device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* _
   if (16 * wave >= pad16(M)) return;  // no tile of this layer is this wave's
   f32x4 a0[U][RT], a1[U][RT];
   load(0, a0);
-  for (int k0 = 0; k0 < nk; k0 += 2 * U) {
-    if (k0 + U < nk) load(k0 + U, a1);
-    multiply(k0, a0);
-    if (k0 + U >= nk) break;
-    if (k0 + 2 * U < nk) load(k0 + 2 * U, a0);
-    multiply(k0 + U, a1);
+  if constexpr (CT == 4 && RT == 2) {
+    // steps past the end load clamped: a load that a branch may skip makes the
+    // compiler wait for every load in flight where the branches meet.  With the
+    // long strides of the narrow blocks the loads past the end cost more (8192
+    // samples in training: 266 us, 313 so)
+    for (int k0 = 0; k0 < nk; k0 += 2 * U) {
+      load(k0 + U, a1);
+      multiply(k0, a0);
+      load(k0 + 2 * U, a0);
+      multiply(k0 + U, a1);
+    }
+  } else {
+    for (int k0 = 0; k0 < nk; k0 += 2 * U) {
+      if (k0 + U < nk) load(k0 + U, a1);
+      multiply(k0, a0);
+      if (k0 + U >= nk) break;
+      if (k0 + 2 * U < nk) load(k0 + 2 * U, a0);
+      multiply(k0 + U, a1);
+    }
   }
 }
 
 // MODE 0: Y = net(X); 1: activations, deltas and squared error of a training
 // batch; 2, 3: the learned guess in complex float, double.
 template <int CT, int W, int RT, int U, int MODE>
-__global__ __launch_bounds__(64 * W) void k_net(NetArgs a, GuessArgs q) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(CT == 4 && RT == 2 && MODE != 1 ? 4 : 1))) void k_net(
+    NetArgs a, GuessArgs q) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   float* h = reinterpret_cast<float*>(smem_raw);  // [S][stride]
   __shared__ double red[W];
@@ -262,10 +279,24 @@ __global__ __launch_bounds__(64 * W) void k_net(NetArgs a, GuessArgs q) {
     for (int e = tid; e < S * inp; e += NT) {
       const int s = e / inp, f = e - s * inp;
       float v = 0.f;
-      if (f < in && s0 + s < a.n) v = MODE >= 2 ? guess_feature(q, s0 + s, f) : a.X[(long)(s0 + s) * in + f];
+      if (MODE < 2 && f < in && s0 + s < a.n) v = a.X[(long)(s0 + s) * in + f];
       h[s * a.stride + f] = v;
     }
     __syncthreads();
+    if (MODE >= 2) {  // (all of a sample's chains of dependent reads at once, one per thread)
+      for (int e = tid; e < S * 9; e += NT) {
+        const int s = e / 9, o = e - 9 * s;
+        if (s0 + s >= a.n) continue;
+        float* hs = h + s * a.stride;
+        if (o < 8) {
+          hs[q.C + o] = guess_feature(q, s0 + s, q.C + o);
+        } else {
+          hs[q.cls[(s0 + s) % q.P]] = 1.f;
+          for (int f = q.C + 8; f < q.C + 11; ++f) hs[f] = guess_feature(q, s0 + s, f);
+        }
+      }
+      __syncthreads();
+    }
     if (MODE == 1)
       for (int e = tid; e < S * in; e += NT) a.H[0][(long)(e / S) * a.ldn + s0 + e % S] = h[(e % S) * a.stride + e / S];
   }
@@ -293,7 +324,10 @@ __global__ __launch_bounds__(64 * W) void k_net(NetArgs a, GuessArgs q) {
   for (int l = 0; l < a.L; ++l) {
     const int K = a.size[l], M = a.size[l + 1];
     const bool last = l + 1 == a.L;
-    net_product<CT, W, RT, U, false>(acc, a.P + a.woff[l], K % 4 == 0 && a.woff[l] % 4 == 0, M, K, h, a.stride, wave, i, kq);
+    if (K % 4 == 0 && a.woff[l] % 4 == 0)
+      net_product<CT, W, RT, U, false, true>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
+    else
+      net_product<CT, W, RT, U, false, false>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
     const float* __restrict__ bias = a.P + a.boff[l];
     __syncthreads();  // every wave has read the layer's inputs
     store(M, MODE != 1 ? nullptr : last ? a.G[l] : a.H[l + 1], [&](int m, int s, float c) {
@@ -309,7 +343,7 @@ __global__ __launch_bounds__(64 * W) void k_net(NetArgs a, GuessArgs q) {
   if constexpr (MODE == 1) {
     for (int l = a.L - 1; l > 0; --l) {
       const int K = a.size[l + 1], M = a.size[l];
-      net_product<CT, W, RT, U, true>(acc, a.P + a.woff[l], false, M, K, h, a.stride, wave, i, kq);
+      net_product<CT, W, RT, U, true, false>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
       const float* H = a.H[l];  // written by this thread in the forward pass
       __syncthreads();
       store(M, a.G[l - 1], [&](int m, int s, float c) { return H[(long)m * a.ldn + s] > 0.f ? c : 0.f; });
@@ -565,7 +599,7 @@ class Mlp {
     const bool narrow = widest() <= 256;
     constexpr int U = MODE == 1 ? 6 : 8;  // (training keeps more in registers)
     if (S == 16) return narrow ? run(k_net<1, 16, 1, U, MODE>, 16) : run(k_net<1, 16, 2, U / 2, MODE>, 16);
-    return narrow ? run(k_net<4, 8, 2, 4, MODE>, 8) : run(k_net<4, 8, 4, 2, MODE>, 8);
+    return narrow ? run(k_net<4, 8, 2, 2, MODE>, 8) : run(k_net<4, 8, 4, 2, MODE>, 8);
   }
   // The layers one launch each, forward: outputs to Y (inference), or the last
   // layer's deltas and squared errors (training: fin, fdel, part).
