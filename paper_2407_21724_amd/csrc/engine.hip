@@ -3792,10 +3792,11 @@ class EngineT final : public Engine {
         launch_dis(pr, I.order, I.m_kw, dim3(xcd_grid(items)), st, A);
       }
       // the class-pair near sum goes into the receive's store where that runs
-      // on k_gemm_group
+      // on k_gemm_group in mode 1, the only one that adds it (mode 0: leaf
+      // spheres of at most 32 samples, whose k fit one chunk)
       GemmJob rj = mfma_ ? receive_job(y, rt_recv_) : none;
       if (near && near_grouped) {
-        if (use_group(rj, R)) {
+        if (use_group(rj, R) && group_mode(rj) == 1) {
           rj.part = pNear_;
           rj.has = ng_has_.template as<int>();
         } else {
