@@ -558,12 +558,10 @@ class Mlp {
   std::vector<DevBuf> fin, fdel;
   int f_cap = 0, h_cap = 0;
   double* hpart = nullptr;
-  hipEvent_t done = nullptr;
   DevBuf act[2], gtab, gx, gy;
   int layers() const { return (int)sizes.size() - 1; }
   ~Mlp() {
     if (hpart) (void)hipHostFree(hpart);
-    if (done) (void)hipEventDestroy(done);
   }
 
   int widest() const { return *std::max_element(sizes.begin(), sizes.end()); }
@@ -660,8 +658,9 @@ class Mlp {
     return 0;
   }
   // Activations and deltas of a batch, then the gradients into `grads` or,
-  // with an Adam step, straight into the parameters.  Returns once the loss is
-  // on the host; the gradient kernel may still run.
+  // with an Adam step, straight into the parameters.  Returns when they are
+  // written: the callers read parameters and gradients by copies that no stream
+  // orders after this one, and use the workspaces on other streams.
   int train_batch(const float* X, const float* T, int n, const Adam* A, double* loss, hipStream_t st, std::string& err) {
     const int L = layers();
     const bool net = fused(n);
@@ -684,7 +683,6 @@ class Mlp {
       MLP_TRY(hipHostMalloc(reinterpret_cast<void**>(&hpart), nb * sizeof(double), hipHostMallocDefault));
       h_cap = nb;
     }
-    if (!done) MLP_TRY(hipEventCreateWithFlags(&done, hipEventDisableTiming));
     void* dpart = nullptr;
     MLP_TRY(hipHostGetDevicePointer(&dpart, hpart, 0));
     if (net) {
@@ -701,7 +699,6 @@ class Mlp {
     } else if (int rc = forward_layers(X, T, n, ldn, nullptr, static_cast<double*>(dpart), st, err)) {
       return rc;
     }
-    MLP_TRY(hipEventRecord(done, st));
     if (!net)
       if (int rc = backward_layers(n, ldn, st, err)) return rc;
     for (int l0 = 0; l0 < L; l0 += kNetLayers) {
@@ -725,7 +722,7 @@ class Mlp {
       hipLaunchKernelGGL(k_net_grad, dim3(g.first[g.L]), dim3(256), 0, st, g);
     }
     MLP_TRY(hipGetLastError());
-    MLP_TRY(hipEventSynchronize(done));
+    MLP_TRY(hipStreamSynchronize(st));
     double s2 = 0;
     for (int b = 0; b < nb; ++b) s2 += hpart[b];
     if (loss) *loss = 0.5 * s2 / n;
@@ -809,7 +806,6 @@ int mlp_loss_grad(Mlp* m, const float* X, const float* T, int n, double* loss, f
                   std::string& err) {
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   if (int rc = m->train_batch(X, T, n, nullptr, loss, st, err)) return rc;
-  MLP_TRY(hipStreamSynchronize(st));
   if (grads) MLP_TRY(hipMemcpy(grads, m->grads.p, m->nparam * sizeof(float), hipMemcpyDeviceToHost));
   return 0;
 }
