@@ -1,8 +1,8 @@
 // Learned initial guess network on gfx950, FP32 on the matrix cores.  Small
-// batches take one launch per layer and direction (k_layer), large ones a
-// kernel that runs a tile of samples through the whole network (k_net); in
-// training k_net_grad then forms all weight gradients and applies Adam.  See
-// mlp.hpp.
+// batches, and wide or deep networks, take one launch per layer and direction
+// (k_layer, k_layer_tile), large batches a kernel that runs a tile of samples
+// through the whole network (k_net); in training k_net_grad then forms all
+// weight gradients and applies Adam.  See mlp.hpp.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,14 +36,10 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // contracts over kq, so that operands come in 16-byte loads.
 __device__ __forceinline__ int pad16(int v) { return (v + 15) & ~15; }
 // Elements k .. k + 3 of row r of a row-major [rows][K] matrix (row stride ld),
-// zero past its end; vec: 16-byte loads are aligned and K a multiple of 4.
-__device__ __forceinline__ f32x4 row4(const float* __restrict__ A, int rows, int K, long ld, bool vec, int r, int k) {
+// zero past its end.
+__device__ __forceinline__ f32x4 row4(const float* __restrict__ A, int rows, int K, long ld, int r, int k) {
   f32x4 o;
   const long at = (long)min(r, rows - 1) * ld;
-  if (vec) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(A + at + min(k, K - 4));
-    return r < rows && k < K ? v : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const float v = A[at + min(k + q, K - 1)];
@@ -51,7 +47,19 @@ __device__ __forceinline__ f32x4 row4(const float* __restrict__ A, int rows, int
   }
   return o;
 }
-// The same of column r of a [K][rows] matrix.
+// The same by one 16-byte load (any 4-byte alignment), of memory that may be read
+// up to 3 elements past a row: its padding, or what follows.  Four loads in its
+// place, as rows of other than a multiple of 4 elements took, cost 65,536 samples
+// of the 43-301-303-77 network 543 us.
+__device__ __forceinline__ f32x4 row4_over(const float* __restrict__ A, int rows, int K, long ld, int r, int k) {
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  const f32x4 v = *reinterpret_cast<const f32x4u*>(A + (long)min(r, rows - 1) * ld + min(k, (K - 1) & ~3));
+  f32x4 o;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o[q] = r < rows && k + q < K ? v[q] : 0.f;
+  return o;
+}
+// Column r of a [K][rows] matrix.
 __device__ __forceinline__ f32x4 col4(const float* __restrict__ A, int rows, int K, int r, int k) {
   f32x4 o;
 #pragma unroll
@@ -64,14 +72,7 @@ __device__ __forceinline__ f32x4 col4(const float* __restrict__ A, int rows, int
 
 // ------------------------------------------------------ one layer a launch --
 // out[sample][m] = sum_k W(m, k) in[sample][k], W the layer's matrix or (back)
-// its transpose, with the layer's epilogue.  A block takes 16 features x 16
-// samples, its four waves a quarter of k each, all of a wave's loads for K up
-// to 256 in flight at once: 256 samples of the 256-wide layers make 256 blocks
-// of one memory latency.  Bound by that latency and the launch for the batches
-// it is used for (n < kNetFrom): a training step of 256 samples took
-// 412 us with a 64 x 64 LDS GEMM per product (16 chunks of k, one at a time)
-// and takes 60 us now; 101 us with k_net, whose 16 blocks leave most of the
-// chip idle.
+// its transpose, with the layer's epilogue.
 struct LayerArgs {
   const float* W;     // [M][K], back: [K][M]
   const float* bias;  // forward
@@ -82,8 +83,55 @@ struct LayerArgs {
   float* outT;        // training: feature-major [M][ldn]
   float* inT;         // first layer in training: its inputs, feature-major [K][ldn]
   double* part;       // last layer in training: squared error of each block
-  int M, K, n, ldi, ldo, ldn, relu, back, vecw, veci;
+  int M, K, n, ldi, ldo, ldn, relu, back;
+  int over;           // rows of `in` may be read past their end (row4_over; those of W always, what follows is
+                      // the biases and the parameters' padding)
+  int over_out;       // rows of `out` may be written up to a multiple of 4, and are 16-byte aligned
 };
+// The epilogue of outputs m .. m + 3 (m < M) of sample s (below max(n, ldn)) and
+// their stores.
+__device__ __forceinline__ void layer_store(const LayerArgs& a, int m, int s, f32x4 c, double& s2) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    if (m + v >= a.M) break;
+    if (a.back) {
+      c[v] = a.mask[(long)(m + v) * a.ldn + s] > 0.f ? c[v] : 0.f;
+    } else {
+      c[v] += a.bias[m + v];
+      if (a.relu) c[v] = fmaxf(c[v], 0.f);
+      if (a.T) {  // the delta of 0.5 / n sum (Y - T)^2
+        const float d = s < a.n ? c[v] - a.T[(long)s * a.M + m + v] : 0.f;
+        s2 += (double)d * d;
+        c[v] = d / (float)a.n;
+      }
+    }
+    if (a.outT) a.outT[(long)(m + v) * a.ldn + s] = c[v];
+  }
+  if (!a.out || s >= a.n) return;
+  float* o = a.out + (long)s * a.ldo + m;
+  if (a.over_out) {
+    *reinterpret_cast<f32x4*>(o) = c;
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (m + v < a.M) o[v] = c[v];
+  }
+}
+// The first layer's inputs of `ns` samples from n0 on, feature-major.
+__device__ __forceinline__ void layer_inputs(const LayerArgs& a, int n0, int ns) {
+  for (int e = threadIdx.x; e < ns * a.K; e += 256) {
+    const int s = n0 + e % ns, k = e / ns;
+    if (s < a.ldn) a.inT[(long)k * a.ldn + s] = s < a.n ? a.in[(long)s * a.ldi + k] : 0.f;
+  }
+}
+
+// Small launches: a block takes 16 features x 16 samples, its four waves a
+// quarter of k each, all of a wave's loads for K up to 256 in flight at once:
+// 256 samples of the 256-wide layers make 256 blocks of one memory latency.
+// Bound by that latency and the launch: a training step of 256 samples took
+// 412 us with a 64 x 64 LDS GEMM per product (16 chunks of k, one at a time)
+// and takes 80 us now; about 125 us with k_net, whose 16 blocks leave most of
+// the chip idle.
 __global__ __launch_bounds__(256) void k_layer(LayerArgs a) {
   __shared__ f32x4 red[3][64];
   const int tm = (a.M + 15) / 16, m0 = (blockIdx.x % tm) * 16, n0 = (blockIdx.x / tm) * 16;
@@ -96,49 +144,125 @@ __global__ __launch_bounds__(256) void k_layer(LayerArgs a) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = s + u < k1 ? 16 * (s + u) + 4 * kq : a.K;  // past the wave's range: zeros
-      x[u] = a.back ? col4(a.W, a.M, a.K, m0 + i, k) : row4(a.W, a.M, a.K, a.K, a.vecw, m0 + i, k);
-      y[u] = row4(a.in, a.n, a.K, a.ldi, a.veci, n0 + i, k);
+      x[u] = a.back ? col4(a.W, a.M, a.K, m0 + i, k) : row4_over(a.W, a.M, a.K, a.K, m0 + i, k);
+      y[u] = a.over ? row4_over(a.in, a.n, a.K, a.ldi, n0 + i, k) : row4(a.in, a.n, a.K, a.ldi, n0 + i, k);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][q], y[u][q], acc, 0, 0, 0);
   }
-  if (a.inT && m0 == 0)
-    for (int e = threadIdx.x; e < 16 * a.K; e += 256) {
-      const int s = n0 + e % 16, k = e / 16;
-      a.inT[(long)k * a.ldn + s] = s < a.n ? a.in[(long)s * a.ldi + k] : 0.f;
-    }
+  if (a.inT && m0 == 0) layer_inputs(a, n0, 16);
   if (wave > 0) red[wave - 1][lane] = acc;
   __syncthreads();
   if (wave > 0) return;
 #pragma unroll
   for (int w = 0; w < 3; ++w) acc += red[w][lane];
-  const int s = n0 + i;
   double s2 = 0;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int m = m0 + 4 * kq + v;
-    if (m >= a.M) continue;
-    float c = acc[v];
-    if (a.back) {
-      c = a.mask[(long)m * a.ldn + s] > 0.f ? c : 0.f;
-    } else {
-      c += a.bias[m];
-      if (a.relu) c = fmaxf(c, 0.f);
-      if (a.T) {  // the delta of 0.5 / n sum (Y - T)^2
-        const float d = s < a.n ? c - a.T[(long)s * a.M + m] : 0.f;
-        s2 += (double)d * d;
-        c = d / (float)a.n;
-      }
-    }
-    if (a.out && s < a.n) a.out[(long)s * a.ldo + m] = c;
-    if (a.outT) a.outT[(long)m * a.ldn + s] = c;
-  }
+  if (m0 + 4 * kq < a.M) layer_store(a, m0 + 4 * kq, n0 + i, acc, s2);
   if (a.T) {
     for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
     if (lane == 0) a.part[blockIdx.x] = s2;
   }
+}
+
+// Large launches (kTileFrom): a block takes 32 RT features x 32 CT samples, its
+// four waves 2 x 2 shares of 16 RT x 16 CT, whose operands come from L1 and L2
+// with the next k-step's in flight.  The 16 x 16 blocks read 16 bytes of L2 for
+// 64 products, this one RT CT / (RT + CT) times less.  Sums are set aside every
+// 256 k, so that a chain is no longer than a wave's quarter of a 1024-wide layer
+// above.
+// OVER: as LayerArgs::over.
+template <int RT, int CT, bool BACK, bool OVER>
+__global__ __launch_bounds__(256) void k_layer_tile(LayerArgs a) {
+  __shared__ double red[4];
+  const int tm = (a.M + 32 * RT - 1) / (32 * RT);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int b0 = (int)(blockIdx.x / tm) * 32 * CT;
+  const int m0 = (int)(blockIdx.x % tm) * 32 * RT + (wave & 1) * 16 * RT, n0 = b0 + (wave >> 1) * 16 * CT;
+  const int nk = pad16(a.K) / 16;
+  f32x4 acc[RT][CT], sum[RT][CT];
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[rt][ct] = sum[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto load = [&](int st, f32x4(&x)[RT], f32x4(&y)[CT]) {  // (past the last step: zeros)
+    const int k = 16 * st + 4 * kq;
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+      x[rt] = BACK ? col4(a.W, a.M, a.K, m0 + 16 * rt + i, k) : row4_over(a.W, a.M, a.K, a.K, m0 + 16 * rt + i, k);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      y[ct] = OVER ? row4_over(a.in, a.n, a.K, a.ldi, n0 + 16 * ct + i, k)
+                   : row4(a.in, a.n, a.K, a.ldi, n0 + 16 * ct + i, k);
+  };
+  auto multiply = [&](const f32x4(&x)[RT], const f32x4(&y)[CT]) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          acc[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[rt][q], y[ct][q], acc[rt][ct], 0, 0, 0);
+  };
+  f32x4 x0[RT], y0[CT], x1[RT], y1[CT];
+  load(0, x0, y0);
+  for (int st = 0; st < nk; st += 2) {
+    load(st + 1, x1, y1);
+    multiply(x0, y0);
+    load(st + 2, x0, y0);
+    multiply(x1, y1);
+    if ((st & 14) == 14)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+          sum[rt][ct] += acc[rt][ct];
+          acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+  }
+  if (a.inT && blockIdx.x % tm == 0) layer_inputs(a, b0, 32 * CT);
+  double s2 = 0;
+  const int ns = max(a.n, a.ldn);
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int m = m0 + 16 * rt + 4 * kq, s = n0 + 16 * ct + i;
+      if (m < a.M && s < ns) layer_store(a, m, s, sum[rt][ct] + acc[rt][ct], s2);
+    }
+  if (a.T) {
+    for (int o = 32; o > 0; o >>= 1) s2 += __shfl_xor(s2, o);
+    if (lane == 0) red[wave] = s2;
+    __syncthreads();
+    if (threadIdx.x == 0) a.part[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  }
+}
+// Features and samples per block of a layer's launch: 16 x 16 below kTileFrom
+// blocks (back: twice that, as the transposed weights come in 4-byte loads) of
+// 128 x 64 or, where that pads the features less, 64 x 128.  Times in us, 16 x 16
+// against the tiles, of 2048, 4096 and 32,768 samples of the 43-1024-1024-120
+// network (256, 512 and 4096 blocks a layer): forward 176 and 100, 335 and 158,
+// 2558 and 986 (a 64 x 64 LDS GEMM: 378, -, 1489); training 444 and 368, 831 and
+// 611, 6621 and 4689.  With 128 blocks the tiles lose: 97 and 142 (1024 samples).
+constexpr long kTileFrom = 256;
+struct LayerTile {
+  int m, n;
+  long blocks(int M, int S) const { return (long)((M + m - 1) / m) * ((S + n - 1) / n); }
+};
+inline LayerTile layer_tile(int M, int n, bool back) {
+  const LayerTile t = (M + 127) / 128 * 128 == (M + 63) / 64 * 64 ? LayerTile{128, 64} : LayerTile{64, 128};
+  return t.blocks(M, n) >= (back ? 2 : 1) * kTileFrom ? t : LayerTile{16, 16};
+}
+template <bool BACK>
+void launch_layer(const LayerArgs& a, hipStream_t st) {
+  const LayerTile t = layer_tile(a.M, a.n, BACK);
+  const dim3 grid((unsigned)t.blocks(a.M, a.n)), block(256);
+  if (t.m == 16) hipLaunchKernelGGL(k_layer, grid, block, 0, st, a);
+  else if (t.m == 128 && a.over) hipLaunchKernelGGL((k_layer_tile<4, 2, BACK, true>), grid, block, 0, st, a);
+  else if (t.m == 128) hipLaunchKernelGGL((k_layer_tile<4, 2, BACK, false>), grid, block, 0, st, a);
+  else if (a.over) hipLaunchKernelGGL((k_layer_tile<2, 4, BACK, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_layer_tile<2, 4, BACK, false>), grid, block, 0, st, a);
 }
 
 // ------------------------------------------------------ fused network --
@@ -163,8 +287,8 @@ __global__ __launch_bounds__(256) void k_layer(LayerArgs a) {
 // on (twice that in training, whose blocks do three times the work) CT = 4 and
 // 8 waves read the weights a quarter as often (forward 75 against 83 us at
 // 8192 samples, 76 against 162 at 16384; training 308 against 262 and 390 against
-// 523).  Networks wider than kNetWidth or deeper than kNetLayers take k_layer
-// for every batch.
+// 523).  Networks wider than kNetWidth or deeper than kNetLayers take a launch
+// per layer for every batch.
 constexpr int kNetLayers = 8, kNetWidth = 512, kNetFrom = 2048, kNetWide = 8192;
 struct NetArgs {
   const float* P;                                       // parameters
@@ -205,7 +329,7 @@ __device__ __forceinline__ float guess_feature(const GuessArgs& q, int s, int f)
 
 // acc = sum_k A(m, k) h[sample][k] for this wave's feature tiles: A = W [M][K]
 // row-major, or its transpose (W [K][M]).  Rows and k past the end are zero.
-template <int CT, int W, int RT, int U, bool TRANS, bool VEC>
+template <int CT, int W, int RT, int U, bool TRANS>
 __device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* __restrict__ Wl, int M, int K,
                                             const float* h, int stride, int wave, int i, int kq) {
   const int nk = pad16(K) / 16;
@@ -219,7 +343,7 @@ __device__ __forceinline__ void net_product(f32x4 (&acc)[RT][CT], const float* _
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const int m = 16 * (wave + W * rt) + i, k = 16 * (k0 + u) + 4 * kq;
-        a[u][rt] = TRANS ? col4(Wl, M, K, m, k) : row4(Wl, M, K, K, VEC, m, k);
+        a[u][rt] = TRANS ? col4(Wl, M, K, m, k) : row4_over(Wl, M, K, K, m, k);
       }
   };
   auto multiply = [&](int k0, const f32x4(&a)[U][RT]) {
@@ -324,10 +448,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(CT == 4 
   for (int l = 0; l < a.L; ++l) {
     const int K = a.size[l], M = a.size[l + 1];
     const bool last = l + 1 == a.L;
-    if (K % 4 == 0 && a.woff[l] % 4 == 0)
-      net_product<CT, W, RT, U, false, true>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
-    else
-      net_product<CT, W, RT, U, false, false>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
+    net_product<CT, W, RT, U, false>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
     const float* __restrict__ bias = a.P + a.boff[l];
     __syncthreads();  // every wave has read the layer's inputs
     store(M, MODE != 1 ? nullptr : last ? a.G[l] : a.H[l + 1], [&](int m, int s, float c) {
@@ -343,7 +464,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(CT == 4 
   if constexpr (MODE == 1) {
     for (int l = a.L - 1; l > 0; --l) {
       const int K = a.size[l + 1], M = a.size[l];
-      net_product<CT, W, RT, U, true, false>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
+      net_product<CT, W, RT, U, true>(acc, a.P + a.woff[l], M, K, h, a.stride, wave, i, kq);
       const float* H = a.H[l];  // written by this thread in the forward pass
       __syncthreads();
       store(M, a.G[l - 1], [&](int m, int s, float c) { return H[(long)m * a.ldn + s] > 0.f ? c : 0.f; });
@@ -617,9 +738,9 @@ class Mlp {
       a.n = n;
       a.ldn = ldn;
       a.relu = !last;
-      a.vecw = a.K % 4 == 0 && woff[l] % 4 == 0;
-      a.veci = a.K % 4 == 0 && (l > 0 || reinterpret_cast<uintptr_t>(X) % 16 == 0);
+      a.over = l > 0 || a.K % 4 == 0;
       a.out = last && !T ? Y : act[l % 2].f();
+      a.over_out = !last || T || (a.M % 4 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0);
       a.ldo = last && !T ? a.M : ld;
       if (T) {
         a.inT = l ? nullptr : fin[0].f();
@@ -629,7 +750,7 @@ class Mlp {
           a.part = part;
         }
       }
-      hipLaunchKernelGGL(k_layer, dim3(((a.M + 15) / 16) * ((n + 15) / 16)), dim3(256), 0, st, a);
+      launch_layer<false>(a, st);
     }
     MLP_TRY(hipGetLastError());
     return 0;
@@ -647,12 +768,12 @@ class Mlp {
       a.n = n;
       a.ldn = ldn;
       a.back = 1;
-      a.veci = a.K % 4 == 0;
+      a.over = a.over_out = 1;
       a.mask = fin[l].f();
       a.out = act[(l - 1) % 2].f();
       a.ldo = ld;
       a.outT = fdel[l - 1].f();
-      hipLaunchKernelGGL(k_layer, dim3(((a.M + 15) / 16) * ((n + 15) / 16)), dim3(256), 0, st, a);
+      launch_layer<true>(a, st);
     }
     MLP_TRY(hipGetLastError());
     return 0;
@@ -665,7 +786,7 @@ class Mlp {
     const int L = layers();
     const bool net = fused(n);
     const int ldn = net ? net_args(n, true).ldn : (n + 15) / 16 * 16;
-    const int nb = net ? ldn / tile(n, true) : ((sizes[L] + 15) / 16) * (ldn / 16);
+    const int nb = net ? ldn / tile(n, true) : (int)layer_tile(sizes[L], n, false).blocks(sizes[L], n);
     if (ldn > f_cap) {
       f_cap = 0;
       fin.resize(L);
@@ -780,7 +901,7 @@ int mlp_get_params(const Mlp* m, float* host, std::string& err) {
 
 int mlp_set_params(Mlp* m, const float* host, std::string& err) {
   const size_t b = m->nparam * sizeof(float);
-  MLP_TRY(m->params.ensure(b));
+  MLP_TRY(m->params.ensure(b + 3 * sizeof(float)));  // (row4_over of the last weights)
   MLP_TRY(m->grads.ensure(b));
   MLP_TRY(m->m1.ensure(b));
   MLP_TRY(m->m2.ensure(b));
