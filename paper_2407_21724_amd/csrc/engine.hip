@@ -831,20 +831,12 @@ struct Mfma16<double> {
 // us, the projection 17, the receive 30, where one output per thread (16
 // particles' terms in registers) took 116, 21 and 68; product 349 to 218 us.
 //
-// FP32 contexts that are told to leave the matrix cores run the same kernel
-// with the product written out (Plain16).
-struct Plain16 : Mfma16<float> {
-  static __device__ __forceinline__ vec4 mul(float a, float b, vec4 c) {
-    const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const float bk = __shfl(b, i + 16 * k);
-#pragma unroll
-      for (int v = 0; v < 4; ++v) c[v] = fmaf(__shfl(a, 4 * g + v + 16 * k), bk, c[v]);
-    }
-    return c;
-  }
-};
+// FP32 contexts that are told to leave the matrix cores run the same kernel on
+// the vector unit: a lane holds the same 4 x 1 results and reads its 4 rows and
+// its column of each k back from LDS, 3 reads for 16 multiply-adds.  (With the
+// 80 lane exchanges of the matrix instruction's operand layout for 64, 40 x 40
+// cylinders at 8 RHS took 282 us for the near blocks, 101 now, and 142 with a
+// kernel of one output per thread.)
 template <typename T>
 struct ZJob {
   const C2<T>* A;      // group g, segment s: A + g * astride + aslot[s] * K M, K = kseg
@@ -856,33 +848,47 @@ struct ZJob {
   int M, nseg, kseg, R, nblk, split, acc;
   int aslot[9];
 };
-template <typename T>
+// LDS written by a wave is visible to the wave's other lanes
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+// SPLIT: a block's waves share one tile of 16 columns and split its k.  Otherwise
+// (launches that fill the chip: launch_z) each wave takes a tile of its own, summed
+// over the same quarters of k in the same order, so the results are the same.
+template <typename T, bool SPLIT>
 __global__ __launch_bounds__(256) void k_zgemm(ZJob<T> J) {
-  using MM = std::conditional_t<std::is_same<T, float>::value, Plain16, Mfma16<T>>;
+  using MM = Mfma16<T>;
   using V4 = typename MM::vec4;
   constexpr int U = 4;
-  __shared__ V4 red[3][2][64];
-  __shared__ int src[9][16];
+  constexpr bool PLAIN = sizeof(T) == 4;
+  constexpr int NW = SPLIT ? 1 : 4;  // column tiles per block
+  __shared__ V4 red[SPLIT ? 3 : 1][2][64];
+  __shared__ __align__(16) C2<T> sa[PLAIN ? 4 : 1][4 * U][16], sb[PLAIN ? 4 : 1][4 * U][16];  // [wave][k][row, column]
+  __shared__ int src[NW][9][16];
   const int M = J.M, nseg = J.nseg, kseg = J.kseg, R = J.R, tm = (M + 15) / 16;
   const int m0 = (int)(blockIdx.x % tm) * 16, rest = blockIdx.x / tm;
-  const int4 d = J.blk[rest / J.split];
-  const int f0 = rest % J.split * 16, F = d.y * R;
-  if (f0 >= F) return;  // whole block
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
+  const int ws = SPLIT ? 0 : wave;
+  const int4 d = J.blk[rest / J.split];
+  const int f0 = (rest % J.split * NW + ws) * 16, F = d.y * R;
+  if (f0 >= F) return;  // whole block; without SPLIT, which has no barriers, a wave
   const int f = min(f0 + i, F - 1), col = d.x + f / R, rc = f % R;  // idle lanes repeat the last column
-  if (threadIdx.x < 16)
-    for (int sg = 0; sg < nseg; ++sg) src[sg][i] = J.bcol[(size_t)col * nseg + sg];
-  __syncthreads();
+  if (SPLIT ? threadIdx.x < 16 : lane < 16)
+    for (int sg = 0; sg < nseg; ++sg) src[ws][sg][i] = J.bcol[(size_t)col * nseg + sg];
+  if constexpr (SPLIT) __syncthreads();
+  else wave_sync();
   const C2<T>* __restrict__ Bc = J.B + (size_t)rc * J.sB;
   const C2<T>* __restrict__ Ag = J.A + d.z * J.astride + min(m0 + i, M - 1);
   const bool mok = m0 + i < M;
-  const int ns = (kseg + 3) / 4, n = nseg * ns, s0 = wave * n / 4, s1 = (wave + 1) * n / 4;
+  const int ns = (kseg + 3) / 4, n = nseg * ns;  // steps
   V4 re = {0, 0, 0, 0}, im = {0, 0, 0, 0};
-  auto load = [&](int s, C2<T>(&a)[U], C2<T>(&b)[U]) {
+  auto load = [&](int s, int s1, C2<T>(&a)[U], C2<T>(&b)[U]) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int st = min(s + u, n - 1), sg = st / ns, k = 4 * (st - sg * ns) + kq, kc = min(k, kseg - 1);
-      const int slot = J.aslot[sg], q = src[sg][i];
+      const int slot = J.aslot[sg], q = src[ws][sg][i];
       const bool on = s + u < s1 && k < kseg && slot >= 0;
       const C2<T> av = Ag[((size_t)max(slot, 0) * kseg + kc) * M], bv = Bc[(size_t)max(q, 0) * kseg + kc];
       a[u] = on && mok ? av : C2<T>{0, 0};
@@ -890,34 +896,89 @@ __global__ __launch_bounds__(256) void k_zgemm(ZJob<T> J) {
     }
   };
   auto multiply = [&](const C2<T>(&a)[U], const C2<T>(&b)[U]) {
+    if constexpr (PLAIN) {
+      wave_sync();  // the previous steps have been read
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      re = MM::mul(a[u].x, b[u].x, re);
-      im = MM::mul(a[u].x, b[u].y, im);
-      re = MM::mul(-a[u].y, b[u].y, re);
-      im = MM::mul(a[u].y, b[u].x, im);
+      for (int u = 0; u < U; ++u) {
+        sa[wave][4 * u + kq][i] = a[u];
+        sb[wave][4 * u + kq][i] = b[u];
+      }
+      wave_sync();
+#pragma unroll
+      for (int k = 0; k < 4 * U; ++k) {
+        const f32x4* pa = reinterpret_cast<const f32x4*>(&sa[wave][k][4 * kq]);
+        const f32x4 p = pa[0], q = pa[1];
+        const C2<T> z = sb[wave][k][i];
+        const C2<T> r[4] = {{p[0], p[1]}, {p[2], p[3]}, {q[0], q[1]}, {q[2], q[3]}};
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          re[v] = fmadd(-r[v].y, z.y, fmadd(r[v].x, z.x, re[v]));
+          im[v] = fmadd(r[v].y, z.x, fmadd(r[v].x, z.y, im[v]));
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        re = MM::mul(a[u].x, b[u].x, re);
+        im = MM::mul(a[u].x, b[u].y, im);
+        re = MM::mul(-a[u].y, b[u].y, re);
+        im = MM::mul(a[u].y, b[u].x, im);
+      }
     }
   };
   C2<T> a0[U], b0[U], a1[U], b1[U];
-  if (s0 < s1) load(s0, a0, b0);
-  for (int s = s0; s < s1; s += 2 * U) {
-    if (s + U < s1) load(s + U, a1, b1);
-    multiply(a0, b0);
-    if (s + U >= s1) break;
-    if (s + 2 * U < s1) load(s + 2 * U, a0, b0);
-    multiply(a1, b1);
-  }
-  if (wave > 0) {
-    red[wave - 1][0][lane] = re;
-    red[wave - 1][1][lane] = im;
-  }
-  __syncthreads();
-  if (wave > 0 || f0 + i >= F) return;
+  if constexpr (SPLIT) {
+    const int s0 = wave * n / 4, s1 = (wave + 1) * n / 4;
+    if (s0 < s1) load(s0, s1, a0, b0);
+    for (int s = s0; s < s1; s += 2 * U) {
+      if (s + U < s1) load(s + U, s1, a1, b1);
+      multiply(a0, b0);
+      if (s + U >= s1) break;
+      if (s + 2 * U < s1) load(s + 2 * U, s1, a0, b0);
+      multiply(a1, b1);
+    }
+    if (wave > 0) {
+      red[wave - 1][0][lane] = re;
+      red[wave - 1][1][lane] = im;
+    }
+    __syncthreads();
+    if (wave > 0) return;
 #pragma unroll
-  for (int w = 0; w < 3; ++w) {
-    re += red[w][0][lane];
-    im += red[w][1][lane];
+    for (int w = 0; w < 3; ++w) {
+      re += red[w][0][lane];
+      im += red[w][1][lane];
+    }
+  } else {
+    V4 tre = re, tim = im;
+    int w = 0, s = 0, s1 = n / 4;  // quarter, next step and end of the quarter
+    auto enter = [&] {             // past the end of a quarter: the next one that has steps
+      while (s >= s1 && w < 4) {
+        ++w;
+        s = s1;
+        s1 = (w + 1) * n / 4;
+      }
+    };
+    // multiplies a, b with the steps after them on the way to an, bn; false at the end
+    auto chunk = [&](const C2<T>(&a)[U], const C2<T>(&b)[U], C2<T>(&an)[U], C2<T>(&bn)[U]) {
+      const int was = w;
+      s += U;
+      enter();
+      if (w < 4) load(s, s1, an, bn);
+      multiply(a, b);
+      if (w != was) {
+        tre += re;
+        tim += im;
+        re = im = V4{0, 0, 0, 0};
+      }
+      return w < 4;
+    };
+    enter();
+    load(s, s1, a0, b0);
+    while (chunk(a0, b0, a1, b1) && chunk(a1, b1, a0, b0)) {}
+    re = tre;
+    im = tim;
   }
+  if (f0 + i >= F) return;
   C2<T>* __restrict__ Cc = J.C + (size_t)rc * J.sC + (size_t)J.ccol[col] * M;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
@@ -3944,13 +4005,23 @@ class EngineT final : public Engine {
   }
   void launch_z(Pending& pr, ZJob<T> j, int R, hipStream_t st, const GroupTab* tab = nullptr) {
     const GroupTab& t = tab ? *tab : gclass_;
+    const int tm = (j.M + 15) / 16;
+    // tiles from which each wave takes one of its own.  FP64 (us, split and
+    // whole): the preconditioner (15 steps of k) 10.3 and 14.1 with 1280 tiles,
+    // 15.4 and 15.0 with 1600, 30.2 and 22.2 with 3840; the receive (121) 119 and
+    // 116 with 2560, 170 and 138 with 3840; near blocks (135) 145 and 146 with
+    // 3200, 156 and 149 with 3840.  FP32 on the vector unit: 11.3 and 13.2 with 1600
+    // and 20.2 and 18.4 with 3840, 64 and 95, 114 and 113
+    const int steps = j.nseg * ((j.kseg + 3) / 4);
+    const bool split = (t.ncols * R + 15) / 16 * tm < (sizeof(T) == 4 ? 4096 : steps <= 32 ? 1536 : 3072);
+    const int cols = split ? 16 : 64;  // per block
     int u = 0;
-    while (u + 1 < kGroupNU && (long long)kGroupU[u + 1] * R <= 16) ++u;
+    while (u + 1 < kGroupNU && (long long)kGroupU[u + 1] * R <= cols) ++u;
     j.R = R;
     j.blk = t.mem.template as<int4>() + t.off[u];
     j.nblk = t.cnt[u];
-    j.split = (int)(((long long)kGroupU[u] * R + 15) / 16);
-    launch(pr, k_zgemm<T>, dim3((unsigned)(j.nblk * j.split * ((j.M + 15) / 16))), dim3(256), 0u, st, j);
+    j.split = (int)(((long long)kGroupU[u] * R + cols - 1) / cols);
+    launch(pr, split ? k_zgemm<T, true> : k_zgemm<T, false>, dim3((unsigned)(j.nblk * j.split * tm)), dim3(256), 0u, st, j);
   }
 
   void launch_near(Pending& pr, const CT* x, CT* y, int R, const CT* mats, const int* nbr, const int* slot,
