@@ -3566,7 +3566,7 @@ class EngineT final : public Engine {
   // class-pair blocks always (12 x 12 lens 24 and 16 us), their receive, which
   // takes the near sum too, from 128 tiles (49 and 36 us with 225).
   bool use_group(const GemmJob& j, int R) const {
-    if (!gemm_lds_ || bf16_ || group_mode(j) < 0) return false;
+    if (!gemm_lds_ || (bf16_ && j.Ah) || group_mode(j) < 0) return false;
     if (j.gtab == &gnear_ && !near_uniform_) return true;
     const long long tiles = (static_cast<const GroupTab*>(j.gtab)->ncols * R + 15) / 16;
     return tiles >= (!j.acc ? 256 : near_uniform_ ? 512 : 128);
@@ -3574,16 +3574,24 @@ class EngineT final : public Engine {
   // The grouped job for R right-hand sides: tiles per block so that about
   // kGroupBlocks blocks run (fewer tiles read A more often, but leave no CU
   // without a block), and in mode 0 the row chunks split as far as that takes.
-  GroupJob group_job(const GemmJob& j, int R) const {
+  // pc: the preconditioner, whose rows are one chunk: half the tiles per block
+  // until there is a block for each CU, and the columns cut where that makes the
+  // fewest blocks.  Against 8 tiles per block and cuts of 8 tiles' whole columns,
+  // 1600 particles: 15.5 to 9.6 us at 4 RHS, 15.9 to 11.4 at 8, 26.9 to 17.4 at 20,
+  // 37.2 to 28.3 at 36 (blocks of 4 waves with a tile each: 12.0, 16.3, 18.5, 34.2)
+  GroupJob group_job(const GemmJob& j, int R, bool pc = false) const {
     const GroupTab& t = *static_cast<const GroupTab*>(j.gtab);
     GroupJob g{};
     g.mode = group_mode(j);
     const long long tiles = (t.ncols * R + 15) / 16;
     int nt = g.mode == 1 && (R % 4 || !j.acc) ? kGW / 2 : kGW;  // (the chunks' own sums: see PARTS)
-    if (g.mode == 1)
-      while (nt > 1 && tiles / nt < kGroupBlocks) nt /= 2;
+    if (g.mode == 1 || pc)
+      while (nt > 1 && tiles / nt < (pc ? 256 : kGroupBlocks)) nt /= 2;
+    auto split_of = [&](int v) { return (int)(((long long)kGroupU[v] * R + 16 * nt - 1) / (16 * nt)); };
     int u = 0;
-    while (u + 1 < kGroupNU && (long long)kGroupU[u + 1] * R <= 16 * nt) ++u;
+    for (int v = 1; v < kGroupNU; ++v)
+      if (pc ? (long long)t.cnt[v] * split_of(v) < (long long)t.cnt[u] * split_of(u) : (long long)kGroupU[v] * R <= 16 * nt)
+        u = v;
     g.A = j.A;
     g.astride = j.gstride;
     g.B = j.B;
@@ -3608,7 +3616,7 @@ class EngineT final : public Engine {
     const int nmc = (j.M + kLM - 1) / kLM;
     g.rsplit = g.mode == 0 ? std::max(1, std::min(nmc, (kGroupBlocks + g.nblk - 1) / g.nblk)) : 1;
     g.tiles = nt;
-    g.split = g.rsplit * (int)(((long long)kGroupU[u] * R + 16 * nt - 1) / (16 * nt));
+    g.split = g.rsplit * split_of(u);
     return g;
   }
   template <int PARTS, int Tag>
@@ -3644,7 +3652,7 @@ class EngineT final : public Engine {
   // BF16-split: one grid layer per RHS.
   template <int Tag>
   void launch_gemm(Pending& pr, int rt, const GemmJob& j0u, const GemmJob& j1u, int R, hipStream_t st) {
-    if (bf16_) {
+    if (bf16_ && j0u.Ah) {
       const int nt = gemm_blocks(j0u, 4) + gemm_blocks(j1u, 4);
       const dim3 grid(j0u.xcd ? xcd_grid(nt) : nt, 1, R);
       if (rt == 1)
@@ -3656,7 +3664,7 @@ class EngineT final : public Engine {
       return;
     }
     if (use_group(j0u, R) && (!j1u.A || group_mode(j1u) >= 0)) {
-      const GroupJob a = group_job(j0u, R), b = j1u.A ? group_job(j1u, R) : GroupJob{};
+      const GroupJob a = group_job(j0u, R, Tag == 4), b = j1u.A ? group_job(j1u, R) : GroupJob{};
       const dim3 grid(8 * ((a.nblk * a.split + 7) / 8 + (b.nblk * b.split + 7) / 8));
       const int modes = 1 << a.mode | (b.nblk ? 1 << b.mode : 0), parts = kGW / (a.mode || !b.nblk ? a.tiles : b.tiles);
       const GroupJobs g{{a, b}};
@@ -3667,10 +3675,13 @@ class EngineT final : public Engine {
       else launch_group<8, Tag>(pr, modes, a.part != nullptr, grid, g, st);
       return;
     }
-    const int ct = R % 4 == 0 ? 4 : R % 2 == 0 ? 2 : 1;
-    // fewer rows per block (up to the `rt` asked for) while the launch has at
-    // most two blocks per CU: it then waits for a block's chain of k-steps, which
-    // shorter tiles load further ahead (4 x 4 spheres 21 to 9 us, receive 16 to 8)
+    // fewer rows per block (up to the `rt` asked for), and then fewer column
+    // tiles, while the launch has at most two blocks per CU: it waits for a
+    // block's chain of k-steps, which smaller tiles load further ahead (4 x 4
+    // spheres 21 to 9 us, receive 16 to 8; at 8 RHS, with 1 column tile instead
+    // of 4, 23 to 10 and 24 to 9)
+    const int most = R % 4 == 0 ? 4 : R % 2 == 0 ? 2 : 1;
+    int ct = 1;
     auto with_rows = [](GemmJob j, int r) {
       if (!j.A) return j;
       const int cols = j.tiles / j.tiles_m;
@@ -3679,10 +3690,17 @@ class EngineT final : public Engine {
       return j;
     };
     GemmJob j0, j1;
-    for (int r = 1;; r *= 2) {
+    for (int r = 1;; r = r ? 2 * r : 1) {
       j0 = fold_job(with_rows(j0u, r), R, ct);
       j1 = fold_job(with_rows(j1u, r), R, ct);
-      if (r < rt && gemm_blocks(j0, kGemmW) + gemm_blocks(j1, kGemmW) > 512) continue;
+      if (gemm_blocks(j0, kGemmW) + gemm_blocks(j1, kGemmW) > 512) {
+        if (r < rt) continue;
+        if (ct < most) {
+          ct *= 2;
+          r = 0;  // (1 next)
+          continue;
+        }
+      }
       rt = r;
       break;
     }
@@ -3942,7 +3960,7 @@ class EngineT final : public Engine {
   int precondition(const void* xv, void* yv, int R, void* stream, std::string& err) override {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     Pending none;
-    if (mfma_ && !bf16_) {  // FP32: each class's inverse self block on the matrix cores, columns grouped by class
+    if (mfma_) {  // each class's inverse self block, FP32 on the matrix cores, columns grouped by class
       launch_gemm<4>(none, rt_np_, precond_job(reinterpret_cast<const CT*>(xv), reinterpret_cast<CT*>(yv), rt_np_),
                      GemmJob{}, R, st);
     } else {
