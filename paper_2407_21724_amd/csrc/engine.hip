@@ -867,8 +867,10 @@ __global__ __launch_bounds__(256) void k_zgemm(ZJob<T> J) {
   __shared__ V4 red[SPLIT ? 3 : 1][2][64];
   __shared__ __align__(16) C2<T> sa[PLAIN ? 4 : 1][4 * U][16], sb[PLAIN ? 4 : 1][4 * U][16];  // [wave][k][row, column]
   __shared__ int src[NW][9][16];
-  const int M = J.M, nseg = J.nseg, kseg = J.kseg, R = J.R, tm = (M + 15) / 16;
-  const int m0 = (int)(blockIdx.x % tm) * 16, rest = blockIdx.x / tm;
+  const int M = J.M, nseg = J.nseg, kseg = J.kseg, R = J.R;
+  // (rows along x, which run together and share their columns; see launch_z)
+  const int m0 = blockIdx.x * 16, rest = blockIdx.z * gridDim.y + blockIdx.y;
+  if (rest >= J.nblk * J.split) return;  // whole block
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, i = lane & 15, kq = lane >> 4;
   const int ws = SPLIT ? 0 : wave;
   const int4 d = J.blk[rest / J.split];
@@ -2012,7 +2014,7 @@ __global__ __launch_bounds__(256) void k_fld_sum(size_t cnt, int nch, double sca
                                                   C2<T>* __restrict__ E) {
   __shared__ double red[16][17][2];
   const int v = threadIdx.x & 15, row = threadIdx.x >> 4;
-  const size_t i = (size_t)blockIdx.x * 16 + v;
+  const size_t i = ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + v;
   double x = 0, y = 0;
   if (i < cnt) {
 #pragma unroll 4
@@ -3950,7 +3952,9 @@ class EngineT final : public Engine {
     if (rb == 1) sum_terms(k_fields<1>);
     else if (rb == 2) sum_terms(k_fields<2>);
     else sum_terms(k_fields<4>);
-    launch(none, k_fld_sum<T>, dim3((unsigned)((cnt + 15) / 16)), dim3(256), 0u, st, cnt, nsum,
+    // (a launch may have less than 2^32 threads along x)
+    const size_t blocks = (cnt + 15) / 16, gx = std::min<size_t>(blocks, 1u << 20);
+    launch(none, k_fld_sum<T>, dim3((unsigned)gx, (unsigned)((blocks + gx - 1) / gx)), dim3(256), 0u, st, cnt, nsum,
            -fld_k_ * fld_k_ / (16.0 * kPi * kPi), (const C2<float>*)part, reinterpret_cast<CT*>(Ev));
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));  // the host point array may be released on return
@@ -4039,7 +4043,9 @@ class EngineT final : public Engine {
     j.blk = t.mem.template as<int4>() + t.off[u];
     j.nblk = t.cnt[u];
     j.split = (int)(((long long)kGroupU[u] * R + cols - 1) / cols);
-    launch(pr, split ? k_zgemm<T, true> : k_zgemm<T, false>, dim3((unsigned)(j.nblk * j.split * tm)), dim3(256), 0u, st, j);
+    // (a launch may have less than 2^32 threads along x, and 65,535 blocks along y and z)
+    const unsigned total = (unsigned)(j.nblk * j.split), gy = std::min(total, 32768u);
+    launch(pr, split ? k_zgemm<T, true> : k_zgemm<T, false>, dim3(tm, gy, (total + gy - 1) / gy), dim3(256), 0u, st, j);
   }
 
   void launch_near(Pending& pr, const CT* x, CT* y, int R, const CT* mats, const int* nbr, const int* slot,
