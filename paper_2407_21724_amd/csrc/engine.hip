@@ -2547,6 +2547,16 @@ class EngineT final : public Engine {
     DevMem mem;
     int off[kGroupNU] = {}, cnt[kGroupNU] = {};
     long long ncols = 0;
+    // The cut (index into kGroupU) that launches the fewest blocks of nt tiles for
+    // R right-hand sides: within a column's right-hand sides where whole columns
+    // would leave a block's tiles part empty.
+    int cut(int R, int nt) const {
+      auto blocks = [&](int u) { return (long long)cnt[u] * (((long long)kGroupU[u] * R + 16 * nt - 1) / (16 * nt)); };
+      int best = 0;
+      for (int u = 1; u < kGroupNU; ++u)
+        if (blocks(u) < blocks(best)) best = u;
+      return best;
+    }
   };
   // groups: (first column, end, index of its A)
   int put_groups(GroupTab& t, const std::vector<std::array<int, 3>>& groups, std::string& err) {
@@ -3561,26 +3571,36 @@ class EngineT final : public Engine {
   // Which kernel takes a job (and the other one of its launch).  k_gemm_group
   // wherever its A chunks fit LDS (at most 32 modes per current), except for
   // few columns, where k_gemm_stream, which splits k over a block's waves,
-  // answers sooner: from 256 tiles of 16 columns on, 512 for the receive (near
-  // blocks and projection: 25 us stream, 28 group with 100 tiles, 66 and 57 with
-  // 336; receive: 18 and 25, 33 and 39, 97 and 86 with 950 and the near sum).
-  // Columns in many groups, which k_gemm_stream pads to 16 each, come earlier:
-  // class-pair blocks always (12 x 12 lens 24 and 16 us), their receive, which
-  // takes the near sum too, from 128 tiles (49 and 36 us with 225).
-  bool use_group(const GemmJob& j, int R) const {
+  // answers sooner.  Times in us, stream and group, by tiles of 16 columns:
+  //   near blocks and projection of one class, R a multiple of 4: 36 and 42 with
+  //   200, 84 and 61 with 300, 164 and 134 with 800; other R: 62 and 58 with 336,
+  //   87 and 97 with 600, 137 and 146 with 1000, 225 and 214 with 1500, 300 and 250
+  //   with 2200
+  //   its receive: 40 and 51 with 500, 96 and 75 with 600, 145 and 120 with 1200;
+  //   other R: 74 and 93 with 900, 146 and 177 with 1800, 163 and 151 with 2200
+  //   (a multiple of 4 streams 64 columns per read of A in few, long blocks)
+  //   class-pair blocks, which k_gemm_stream pads to 16 columns each: always (12 x
+  //   12 lens 24 and 16); their receive, which takes the near sum too: 27 and 33
+  //   with 128, 43 and 32 with 192, 43 and 34 with 225, 102 and 54 with 450
+  //   (other R: 28 and 32 with 169, 53 and 51 with 394, 112 and 127 with 1125)
+  //   the preconditioner (pc): 10.6 and 9.6 with 400, 16.0 and 11.4 with 800
+  bool use_group(const GemmJob& j, int R, bool pc = false) const {
     if (!gemm_lds_ || (bf16_ && j.Ah) || group_mode(j) < 0) return false;
     if (j.gtab == &gnear_ && !near_uniform_) return true;
     const long long tiles = (static_cast<const GroupTab*>(j.gtab)->ncols * R + 15) / 16;
-    return tiles >= (!j.acc ? 256 : near_uniform_ ? 512 : 128);
+    if (pc || !near_uniform_) return tiles >= (j.acc ? 128 : 256);
+    return tiles >= (!j.acc ? 256 : R % 4 ? 2048 : 512);
   }
   // The grouped job for R right-hand sides: tiles per block so that about
   // kGroupBlocks blocks run (fewer tiles read A more often, but leave no CU
   // without a block), and in mode 0 the row chunks split as far as that takes.
   // pc: the preconditioner, whose rows are one chunk: half the tiles per block
-  // until there is a block for each CU, and the columns cut where that makes the
-  // fewest blocks.  Against 8 tiles per block and cuts of 8 tiles' whole columns,
-  // 1600 particles: 15.5 to 9.6 us at 4 RHS, 15.9 to 11.4 at 8, 26.9 to 17.4 at 20,
-  // 37.2 to 28.3 at 36 (blocks of 4 waves with a tile each: 12.0, 16.3, 18.5, 34.2)
+  // until there is a block for each CU.  Against 8 tiles per block, 1600 particles:
+  // 15.5 to 9.6 us at 4 RHS, 15.9 to 11.4 at 8, 26.9 to 17.4 at 20 (blocks of 4
+  // waves with a tile each: 12.0, 16.3, 18.5).
+  // Cutting at whole columns only left up to half of a block's tiles empty: 40 x
+  // 40 cylinders at 9, 18, 20 and 36 RHS 716, 1428, 1496 and 2311 us, with the
+  // cut of fewest blocks 628, 1176, 1271 and 1999.
   GroupJob group_job(const GemmJob& j, int R, bool pc = false) const {
     const GroupTab& t = *static_cast<const GroupTab*>(j.gtab);
     GroupJob g{};
@@ -3589,11 +3609,7 @@ class EngineT final : public Engine {
     int nt = g.mode == 1 && (R % 4 || !j.acc) ? kGW / 2 : kGW;  // (the chunks' own sums: see PARTS)
     if (g.mode == 1 || pc)
       while (nt > 1 && tiles / nt < (pc ? 256 : kGroupBlocks)) nt /= 2;
-    auto split_of = [&](int v) { return (int)(((long long)kGroupU[v] * R + 16 * nt - 1) / (16 * nt)); };
-    int u = 0;
-    for (int v = 1; v < kGroupNU; ++v)
-      if (pc ? (long long)t.cnt[v] * split_of(v) < (long long)t.cnt[u] * split_of(u) : (long long)kGroupU[v] * R <= 16 * nt)
-        u = v;
+    const int u = t.cut(R, nt);
     g.A = j.A;
     g.astride = j.gstride;
     g.B = j.B;
@@ -3618,7 +3634,7 @@ class EngineT final : public Engine {
     const int nmc = (j.M + kLM - 1) / kLM;
     g.rsplit = g.mode == 0 ? std::max(1, std::min(nmc, (kGroupBlocks + g.nblk - 1) / g.nblk)) : 1;
     g.tiles = nt;
-    g.split = g.rsplit * split_of(u);
+    g.split = g.rsplit * (int)(((long long)kGroupU[u] * R + 16 * nt - 1) / (16 * nt));
     return g;
   }
   template <int PARTS, int Tag>
@@ -3665,7 +3681,7 @@ class EngineT final : public Engine {
         launch(pr, k_gemm_bf16x3<4, Tag>, grid, dim3(kBlock), 0u, st, j0u, j1u);
       return;
     }
-    if (use_group(j0u, R) && (!j1u.A || group_mode(j1u) >= 0)) {
+    if (use_group(j0u, R, Tag == 4) && (!j1u.A || group_mode(j1u) >= 0)) {
       const GroupJob a = group_job(j0u, R, Tag == 4), b = j1u.A ? group_job(j1u, R) : GroupJob{};
       const dim3 grid(8 * ((a.nblk * a.split + 7) / 8 + (b.nblk * b.split + 7) / 8));
       const int modes = 1 << a.mode | (b.nblk ? 1 << b.mode : 0), parts = kGW / (a.mode || !b.nblk ? a.tiles : b.tiles);
