@@ -3940,38 +3940,44 @@ class EngineT final : public Engine {
     }
     if ((size_t)npts * 3 * sizeof(double) > fld_pts_.bytes) HIP_TRY(fld_pts_.alloc((size_t)npts * 3 * sizeof(double)));
     HIP_TRY(hipMemcpyAsync(fld_pts_.p, points, (size_t)npts * 3 * sizeof(double), hipMemcpyHostToDevice, st));
-    // the expansions, in the incoming leaf patterns' buffer (free between
-    // products) or, where its sphere is too coarse for them, one of their own
-    const size_t a_bytes = (size_t)R * P_ * kFldRow * sizeof(C2<float>);
-    if (a_bytes > L0.G.bytes && a_bytes > fld_exp_.bytes) HIP_TRY(fld_exp_.alloc(a_bytes));
-    C2<float>* A = (a_bytes > L0.G.bytes ? fld_exp_ : L0.G).template as<C2<float>>();
-    launch(none, k_fld_expand<T>, dim3((P_ + kFldExpP - 1) / kFldExpP, R), dim3(kFldExpT),
-           (uint32_t)(kFldExpP * M2_ * sizeof(C2<float>)), st, P_, M2_, L0.nx * L0.ny,
-           (const int*)box_of_.template as<int>(), (const CT*)L0.S.template as<CT>(),
-           (const float*)fld_tab_.template as<float>(), A);
     // sets of 64 points per block, and chunks of particles for about kFldBlocks
     // blocks, each a multiple of the particles staged together (4096 points of
     // 6400 particles: 3.6, 3.2, 3.0 ms with 1024, 2048, 4096 blocks).  Neither
     // depends on R, so a right-hand side's sums do not depend on the batch.
-    const int rb = R >= 3 ? 4 : R, pw = npts > 128 ? 4 : npts > 64 ? 2 : 1;
-    const int nwp = (npts + 64 * pw - 1) / (64 * pw), nrg = (R + rb - 1) / rb, fg = fld_group<1>();
+    const int pw = npts > 128 ? 4 : npts > 64 ? 2 : 1, nwp = (npts + 64 * pw - 1) / (64 * pw), fg = fld_group<1>();
     const int want = std::max(1, std::min((P_ + fg - 1) / fg, (kFldBlocks + nwp - 1) / nwp));
     const int per = ((P_ + want - 1) / want + fg - 1) / fg * fg, nch = (P_ + per - 1) / per, nsum = nch * (4 / pw);
-    const size_t cnt = (size_t)R * npts * 3;
-    if (nsum * cnt * sizeof(C2<float>) > fld_part_.bytes) HIP_TRY(fld_part_.alloc(nsum * cnt * sizeof(C2<float>)));
+    // right-hand sides in groups whose chunk sums take at most kFldPartBytes and
+    // whose expansions fit the incoming leaf patterns' buffer (free between
+    // products), at least 4: only what these need is allocated
+    const size_t a_one = (size_t)P_ * kFldRow * sizeof(C2<float>), p_one = (size_t)nsum * npts * 3 * sizeof(C2<float>);
+    const int fit = (int)std::min<size_t>({(size_t)R, kFldPartBytes / p_one, L0.G.bytes / a_one});
+    const int group = std::min(R, std::max(4, fit / 4 * 4));
+    if (group * a_one > L0.G.bytes && group * a_one > fld_exp_.bytes) HIP_TRY(fld_exp_.alloc(group * a_one));
+    C2<float>* A = (group * a_one > L0.G.bytes ? fld_exp_ : L0.G).template as<C2<float>>();
+    if (group * p_one > fld_part_.bytes) HIP_TRY(fld_part_.alloc(group * p_one));
     C2<float>* part = fld_part_.template as<C2<float>>();
-    auto sum_terms = [&](auto kernel) {
-      launch(none, kernel, dim3(nwp, nch, nrg), dim3(256), 0u, st, P_, fld_L_, fld_k_,
-             (const double*)fld_cen_.template as<double>(), (const C2<float>*)A, npts,
-             (const double*)fld_pts_.template as<double>(), R, per, pw, part);
-    };
-    if (rb == 1) sum_terms(k_fields<1>);
-    else if (rb == 2) sum_terms(k_fields<2>);
-    else sum_terms(k_fields<4>);
-    // (a launch may have less than 2^32 threads along x)
-    const size_t blocks = (cnt + 15) / 16, gx = std::min<size_t>(blocks, 1u << 20);
-    launch(none, k_fld_sum<T>, dim3((unsigned)gx, (unsigned)((blocks + gx - 1) / gx)), dim3(256), 0u, st, cnt, nsum,
-           -fld_k_ * fld_k_ / (16.0 * kPi * kPi), (const C2<float>*)part, reinterpret_cast<CT*>(Ev));
+    for (int r0 = 0; r0 < R; r0 += group) {
+      const int nr = std::min(group, R - r0), rb = nr >= 3 ? 4 : nr, nrg = (nr + rb - 1) / rb;
+      launch(none, k_fld_expand<T>, dim3((P_ + kFldExpP - 1) / kFldExpP, nr), dim3(kFldExpT),
+             (uint32_t)(kFldExpP * M2_ * sizeof(C2<float>)), st, P_, M2_, L0.nx * L0.ny,
+             (const int*)box_of_.template as<int>(),
+             (const CT*)L0.S.template as<CT>() + (size_t)r0 * L0.nx * L0.ny * M2_,
+             (const float*)fld_tab_.template as<float>(), A);
+      auto sum_terms = [&](auto kernel) {
+        launch(none, kernel, dim3(nwp, nch, nrg), dim3(256), 0u, st, P_, fld_L_, fld_k_,
+               (const double*)fld_cen_.template as<double>(), (const C2<float>*)A, npts,
+               (const double*)fld_pts_.template as<double>(), nr, per, pw, part);
+      };
+      if (rb == 1) sum_terms(k_fields<1>);
+      else if (rb == 2) sum_terms(k_fields<2>);
+      else sum_terms(k_fields<4>);
+      // (a launch may have less than 2^32 threads along x)
+      const size_t cnt = (size_t)nr * npts * 3, blocks = (cnt + 15) / 16, gx = std::min<size_t>(blocks, 1u << 20);
+      launch(none, k_fld_sum<T>, dim3((unsigned)gx, (unsigned)((blocks + gx - 1) / gx)), dim3(256), 0u, st, cnt, nsum,
+             -fld_k_ * fld_k_ / (16.0 * kPi * kPi), (const C2<float>*)part,
+             reinterpret_cast<CT*>(Ev) + (size_t)r0 * npts * 3);
+    }
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(st));  // the host point array may be released on return
     return 0;
@@ -4280,6 +4286,7 @@ class EngineT final : public Engine {
   DevMem fld_cen_, fld_tab_, fld_pts_;  // field evaluation: centres, leaf sample table, points
   DevMem fld_exp_, fld_part_;           // expansions, chunk sums
   static constexpr int kFldBlocks = 4096;  // target of k_fields
+  static constexpr size_t kFldPartBytes = 256u << 20;
   double fld_k_ = 0;
   int fld_L_ = 0;
   DevMem Rm_, Qm_;
