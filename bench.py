@@ -34,8 +34,8 @@ FP32_VALU_PEAK = 157.3e12   # MI355X FP32 vector peak
 ENGINE_SRC = os.path.join(ROOT, "paper_2407_21724_amd", "csrc", "engine.hip")
 
 # product stages (as named by mlfma_profile_read) -> kernel symbol prefix and
-# the roofline that bounds it (FP32 product; the GEMM stages are named by
-# kernel_of from the dispatch rules of the engine)
+# the roofline that bounds it (FP32 product; the GEMM stages' kernels are the
+# ones the library recorded)
 KERNELS = [
     ("aggregate_l", "k_agg_stream", "hbm"),
     ("translate", "k_translate_reg", "hbm"),          # FP32: every level in one launch, tiles in registers
@@ -44,16 +44,12 @@ KERNELS = [
 ]
 
 
-def kernel_of(stage, gemm_rows=(4, 4), R=1, multi_class=True):
+def kernel_of(stage):
     """Kernel symbol and roofline bound of a product stage of the FP32
-    product, where the library recorded none.  The GEMM stages run on
-    k_gemm_group<modes, waves per tile, near sum, tag>, or with few columns on
-    k_gemm_stream<row tiles, column tiles, tag, waves>; their template
-    arguments follow the engine's dispatch and are not repeated here."""
-    gemm = {s: "k_gemm_stream" if os.environ.get("MLFMA_GEMM") == "stream" else "k_gemm_group"
-            for s in ("near+project", "near", "project", "receive")}
-    if stage in gemm:
-        return gemm[stage], "mfma"
+    product, where the library recorded none.  Which kernel a GEMM stage runs
+    on depends on the array, the batch and the precision, so it is not named."""
+    if stage in ("near+project", "near", "project", "receive"):
+        return "unknown", "mfma"
     for prefix, sym, bound in KERNELS:
         if stage == prefix or (prefix.endswith("_l") and stage.startswith(prefix)):
             return sym, bound
@@ -66,14 +62,15 @@ def source_digest():
         return hashlib.sha256(f.read()).hexdigest()
 
 
-def kernel_table(stages, gemm_rows=(4, 4), R=1, multi_class=True):
+def kernel_table(stages, *_):
     """Group per-stage event timings by the symbol of the kernel each stage
     launched (the unit rocprofv3 reports, template arguments included, as
     the library records it): total time, launches, algorithmic bytes and
-    flops.  Stages without a recorded symbol fall back to kernel_of."""
+    flops.  Stages without a recorded symbol fall back to kernel_of.
+    (Further arguments, once the batch and the tiles, are not used.)"""
     groups = {}
     for s in stages:
-        fsym, bound = kernel_of(s["name"], gemm_rows, R, multi_class)
+        fsym, bound = kernel_of(s["name"])
         sym = s.get("kernel") or fsym
         bound = "mfma" if sym.startswith("k_gemm") else bound
         g = groups.setdefault(sym, {"kernel": sym, "bound": bound, "total_ms": 0.0, "launches": 0,
@@ -589,7 +586,7 @@ def main():
 
     # roofline of the dominant kernel (largest share of the product's time)
     gemm_rows = ctx.get_gemm_tiles()
-    groups = kernel_table(stages, gemm_rows, R, len(set(wl.class_id.tolist())) > 1)
+    groups = kernel_table(stages)
     dom = max(groups.values(), key=lambda g: g["total_ms"])
     avg_s = dom["total_ms"] / dom["launches"] * 1e-3
     if dom["bound"] == "hbm":

@@ -306,7 +306,7 @@ typedef struct {
   double flops_per_launch;     /* algorithmic real floating-point ops      */
   char kernel[96];             /* symbol of the launched kernel with its
                                   template arguments, e.g.
-                                  "k_dis_stream<float, 6, 12, 16>" (the unit
+                                  "k_dis_mfma<float, 6, 32>" (the unit
                                   kernel traces report; "" if unknown)     */
 } mlfma_stage_time;
 

@@ -159,14 +159,14 @@ int scratch_address(void** out, std::string& err) {
 // is staged once (STAGE_M) and shared, otherwise (tile_slot == -2) each
 // particle reads its own matrix.  tile_slot == -1: no o-neighbour at all.
 template <typename T, int TPN, bool STAGE_M>
-__global__ __launch_bounds__(kBlock) void k_near(int n, int P, int nsp, const C2<T>* __restrict__ x,
+__global__ __launch_bounds__(kBlock) void k_near(int n, int P, const C2<T>* __restrict__ x,
                                                   C2<T>* __restrict__ y, const C2<T>* __restrict__ mats,
                                                   const int* __restrict__ nbr, const int* __restrict__ slot,
                                                   const int* __restrict__ tile_slot) {
   extern __shared__ unsigned char smem_raw[];
   C2<T>* xs = reinterpret_cast<C2<T>*>(smem_raw);  // [TPN][n]
   C2<T>* ms = xs + TPN * n;                         // [n][n]
-  constexpr int PW = TPN / (kBlock / 64);
+  constexpr int PW = TPN / (kBlock / 64), nsp = 9;  // (the 3 x 3 neighbourhood)
   const int tile = blockIdx.x, r = blockIdx.y;
   const int p0 = tile * TPN;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -2703,7 +2703,8 @@ class EngineT final : public Engine {
       for (auto& m : u.Zinv) zi.insert(zi.end(), m.begin(), m.end());
       if (int rc = put_c(zinv_, zi, err)) return rc;
       // per particle tile and slot: the shared matrix, -1 (none) or -2 (mixed)
-      auto tile_slots = [&](const std::vector<int>& nbr, const std::vector<int>& slot, int nsp) {
+      auto tile_slots = [&](const std::vector<int>& nbr, const std::vector<int>& slot) {
+        const int nsp = 9;
         const int ntl = (P_ + kTPN - 1) / kTPN;
         std::vector<int> ts((size_t)ntl * nsp, -1);
         for (int t = 0; t < ntl; ++t)
@@ -2718,7 +2719,7 @@ class EngineT final : public Engine {
           }
         return ts;
       };
-      if (int rc = put_i(near_tile_slot_, tile_slots(u.near_nbr, u.near_slot, 9), err)) return rc;
+      if (int rc = put_i(near_tile_slot_, tile_slots(u.near_nbr, u.near_slot), err)) return rc;
     }
     centers_ = u.centers;
     nslots_ = (int)u.near_mats.size();
@@ -3646,7 +3647,7 @@ class EngineT final : public Engine {
         return;
       }
     }
-    if constexpr (Tag == 0 && PARTS > 1) {
+    if constexpr (Tag == 0) {
       if (modes == 3) {
         launch(pr, k_gemm_group<3, PARTS, false, Tag>, grid, wg, 0u, st, g);
         return;
@@ -3687,7 +3688,7 @@ class EngineT final : public Engine {
       const int modes = 1 << a.mode | (b.nblk ? 1 << b.mode : 0), parts = kGW / (a.mode || !b.nblk ? a.tiles : b.tiles);
       const GroupJobs g{{a, b}};
       if (modes == 1) launch(pr, k_gemm_group<1, 8, false, Tag>, grid, dim3(64 * kGW), 0u, st, g);
-      else if (parts == 1) launch_group<1, Tag>(pr, modes, a.part != nullptr, grid, g, st);
+      else if (parts == 1) launch_group<Tag == 3 ? 1 : 2, Tag>(pr, modes, a.part != nullptr, grid, g, st);  // (receive only)
       else if (parts == 2) launch_group<2, Tag>(pr, modes, a.part != nullptr, grid, g, st);
       else if (parts == 4) launch_group<4, Tag>(pr, modes, a.part != nullptr, grid, g, st);
       else launch_group<8, Tag>(pr, modes, a.part != nullptr, grid, g, st);
@@ -3839,7 +3840,7 @@ class EngineT final : public Engine {
           launch_z(pr, j, R, st, &gnear_);
         } else {
           launch_near(pr, x, y, R, near_mats_.template as<CT>(), near_nbr_.template as<int>(),
-                      near_slot_.template as<int>(), near_tile_slot_.template as<int>(), 9, st);
+                      near_slot_.template as<int>(), near_tile_slot_.template as<int>(), st);
         }
       } else {
         const size_t cnt = (size_t)R * P_ * n_;
@@ -4071,15 +4072,15 @@ class EngineT final : public Engine {
   }
 
   void launch_near(Pending& pr, const CT* x, CT* y, int R, const CT* mats, const int* nbr, const int* slot,
-                   const int* tile_slot, int nsp, hipStream_t st) {
+                   const int* tile_slot, hipStream_t st) {
     dim3 grid((P_ + kTPN - 1) / kTPN, R);
     const size_t xs_bytes = (size_t)kTPN * n_ * sizeof(CT);
     const size_t m_bytes = (size_t)n_ * n_ * sizeof(CT);
     if (xs_bytes + m_bytes <= 64 * 1024)
-      launch(pr, k_near<T, kTPN, true>, grid, dim3(kBlock), (uint32_t)(xs_bytes + m_bytes), st, n_, P_, nsp, x, y,
+      launch(pr, k_near<T, kTPN, true>, grid, dim3(kBlock), (uint32_t)(xs_bytes + m_bytes), st, n_, P_, x, y,
              mats, nbr, slot, tile_slot);
     else
-      launch(pr, k_near<T, kTPN, false>, grid, dim3(kBlock), (uint32_t)xs_bytes, st, n_, P_, nsp, x, y, mats, nbr,
+      launch(pr, k_near<T, kTPN, false>, grid, dim3(kBlock), (uint32_t)xs_bytes, st, n_, P_, x, y, mats, nbr,
              slot, tile_slot);
   }
 
