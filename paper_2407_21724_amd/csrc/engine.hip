@@ -1903,11 +1903,13 @@ __global__ __launch_bounds__(kFldExpT) void k_fld_expand(int P, int M2, int nb0,
 // times pw sets of 64 points (pw = 4 from 193 points on, fewer where a block
 // would have idle waves).  The expansions of fld_group particles pass through
 // LDS for the whole block and are read as broadcasts.  RB right-hand sides
-// share a pair's harmonics.  Bound by vector issue (FP64 distance, phase and
-// Hankel functions, then about 1000 FP32 multiply-adds a pair and RHS) and by
-// the broadcasts.  4096 points of 6400 particles: 42 ms with the Legendre
-// series at every sample, 3.0 ms now; with the expansions read through the
-// scalar unit 3.6 ms, and for 4 RHS 10.4 against 7.7 ms.
+// share a pair's harmonics.  For 4096 points of 6400 particles the vector unit
+// issues 62% of the cycles (FP64 distance, phase and Hankel functions, then about
+// 1000 FP32 multiply-adds a pair and RHS) and the LDS returns the broadcasts about
+// 46%, with 2.6 waves per SIMD, as many as the registers hold: bound by the
+// dependent chains between them, not by one unit.  42 ms with the Legendre series
+// at every sample, 2.6 now; with the expansions read through the scalar unit 3.6
+// ms, and for 4 RHS 10.4 against 7.7 ms.
 template <int RB>
 constexpr int fld_group() { return RB == 1 ? 8 : 4; }  // particles staged at a time (28 to 55 KB)
 template <int RB>

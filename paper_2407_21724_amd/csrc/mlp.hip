@@ -274,9 +274,11 @@ void launch_layer(const LayerArgs& a, hipStream_t st) {
 // flight during the current U.  Training (MODE 1) goes on to the deltas of
 // every layer (W^T as the operand) and writes activations and deltas
 // feature-major, the layout in which the weight gradients contract over
-// samples.  Bound by the matrix cores at 78 TFLOP/s (102,400 samples of the
-// 43-256-256-256-120 network in 0.48 ms, features and phases included; 2.6 ms
-// with a GEMM per layer and the features formed on the host).  Two blocks of 8
+// samples.  102,400 samples of the 43-256-256-256-120 network take 0.45 ms,
+// features and phases included (2.6 ms with a GEMM per layer and the features
+// formed on the host): the matrix cores are busy 63% of it, with 42.8 GFLOP for
+// the network's 35.4 (the 120 outputs fill one of a wave's two tiles, the 43
+// inputs 43 of 48 k); the rest goes to barriers and epilogues.  Two blocks of 8
 // waves share a CU, so that one's inputs, phases and barriers hide behind the
 // other's products: two steps of weights in flight and 124 registers, where four
 // steps took 162, one block per CU and 0.62 ms.
